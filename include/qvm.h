@@ -169,8 +169,13 @@ qvm_status qvm_apply_kraus(qvm_sv* sv, int32_t qubit, int32_t n_ops, const doubl
                            int32_t* chosen, double* probs);
 
 /* Apply a gate list in order with the plain per-gate path, in one call (the
- * per-gate call overhead the paper measures at small n is paid once).
- * The list is validated in full before anything is enqueued. */
+ * per-gate call overhead the paper measures at small n is paid once).  Each
+ * gate is applied with its own matrix (consecutive uncontrolled one-target
+ * gates on a qubit as their product, formed in double precision); gates
+ * share passes over the state, so two gates that commute because they share
+ * no qubit, or are both diagonal on the qubits they share, may trade places.
+ * The list is validated in full before anything is enqueued.  Asynchronous;
+ * uses the workspace's plan area. */
 qvm_status qvm_run(qvm_sv* sv, const qvm_gate* gates, size_t n_gates);
 
 /* Current logical-to-physical qubit layout: perm_out[q] = physical bit of
@@ -489,7 +494,7 @@ qvm_status qvm_stream_copy(void* dst, const void* src, size_t bytes, void* strea
  * flops (complex multiply-adds of dense and fused matrices, 8 flops each).
  * Used to report achieved bandwidth and throughput against the roofline. */
 typedef struct qvm_kernel_stat {
-    char name[24];           /* dense1..dense3, diag, phase, swappair, tile, basis, rdm1 */
+    char name[24];           /* dense1..dense3, diag, phase, swappair, tile, basis, rdm1, gates */
     int64_t launches;
     double total_ms;
     double bytes;
@@ -505,7 +510,7 @@ qvm_status qvm_profile_begin(qvm_sv* sv);
 qvm_status qvm_profile_end(qvm_sv* sv, qvm_kernel_stat* out, int32_t max, int32_t* count);
 
 /* Per-launch durations (ms) and kernel classes (index into the class list
- * above: 0 dense1 .. 7 basis, 8 rdm1) of the last profiled interval, in launch
+ * above: 0 dense1 .. 7 basis, 8 rdm1, 9 gates) of the last profiled interval, in launch
  * order; up to max entries, *count = the number recorded. */
 qvm_status qvm_profile_launches(const qvm_sv* sv, double* ms, int32_t* kind, int32_t max,
                                 int32_t* count);

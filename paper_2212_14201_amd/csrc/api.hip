@@ -11,6 +11,7 @@
 #include <array>
 #include <cmath>
 #include <cstring>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -448,14 +449,11 @@ qvm_status qvm_run(qvm_sv* sv, const qvm_gate* gates, size_t n_gates) {
         qvm_status st = validate_gate(gates[i], sv->n, false);
         if (st) return fail(st, "gate " + std::to_string(i) + ": " + g_err);
     }
-    std::vector<cd> u;
-    for (size_t i = 0; i < n_gates; ++i) {
-        qvm_status st = gate_matrix(gates[i], u);
-        if (st) return st;
-        st = launch_op(sv, lower(sv, gates[i], u));
-        if (st) return st;
+    try {
+        return run_gates(sv, gates, n_gates);
+    } catch (const std::bad_alloc&) {
+        return fail(QVM_ENOMEM, "host allocation failed");
     }
-    return QVM_OK;
 }
 
 qvm_status qvm_get_layout(const qvm_sv* sv, int32_t* perm_out) {

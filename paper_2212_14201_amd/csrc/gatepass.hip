@@ -1,0 +1,885 @@
+// Gate passes: a gate list applied gate by gate, many gates per pass over the
+// state (qvm_run).
+//
+// A gate on its own reads and writes the state for at most 16 multiply-adds
+// per amplitude pair, so one kernel per gate is bound by HBM (measured 5.6 ms
+// per 30-qubit complex128 gate) and, below about 20 qubits, by its launch
+// (2.7-4 us).  A gate pass keeps tiles of up to 2^13 (complex64) / 2^12
+// (complex128) amplitudes in LDS and applies every gate of the list that can
+// run on the tile's qubits, each gate with its own matrix and the arithmetic
+// of the one-gate kernels (gates.hip): unlike a fused plan no matrices of
+// different qubits are multiplied together.
+//
+//   pass   one workgroup per tile: the 2^L amplitudes that share all
+//          non-tile physical bits; the tile always holds the c lowest bits
+//          (128-byte runs).  Targets of non-diagonal gates must be tile
+//          bits; controls and diagonal gates may sit anywhere.
+//   round  a thread holds the 16 (8 in passes of few tiles) amplitudes that
+//          differ in four (three) of the tile bits, the slots, in registers
+//          and applies, in order, the gates whose targets are slots; then the
+//          amplitudes go back to LDS and the next round takes other slots.
+//          16 amplitudes (32 or 64 VGPRs) keep four waves per SIMD in
+//          complex64 and two in complex128; a round's LDS traffic (1,024
+//          cycles per 64 KiB tile and CU) costs about one dense gate's
+//          arithmetic.
+//
+// What bounds it: the vector unit (a dense gate takes 16 multiply-adds per
+// pair and, for the register moves of the in-place update, about 20% more
+// instructions).  28 qubits, complex128, 8 layers of U3 + CZ (332 gates):
+// 361 ms with one kernel per gate, 31.5 ms in 6 passes, of which the
+// multiply-adds alone take 12 ms and the passes' traffic 8 ms; the first
+// pass (72 dense gates) issues vector instructions in 74% of its cycles.
+// 25 qubits, complex64, 4 layers of rotations + CNOTs (400 gates): 35.3 ->
+// 1.9 ms.  12 qubits, complex128, 20 layers (350 gates, one workgroup): 1.38
+// -> 0.19 ms.
+//
+// The list's records are written to the workspace by k_put kernels, which
+// carry them as kernel arguments: no copy from host memory that the caller
+// or this call would have to keep alive, and a captured graph holds them.
+// A k_put takes 2 to 5 us (its argument block is read from host memory), so
+// it carries up to 16,000 bytes (3,840: 165 -> 155 us for 200 mixed gates on
+// 12 qubits).
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cmath>
+#include <cstring>
+#include <vector>
+
+#include "internal.hpp"
+#include "tile.hpp"
+
+namespace qvm {
+
+namespace {
+
+constexpr int kSlots = 4;                        // slots of a round, at most
+
+template <typename R> struct GT;
+template <> struct GT<float> {
+    using T = float2;
+    using V16 = float __attribute__((ext_vector_type(4)));
+    static constexpr int EP = 2, C = 4, LMAX = 13;
+};
+template <> struct GT<double> {
+    using T = double2;
+    using V16 = double __attribute__((ext_vector_type(2)));
+    static constexpr int EP = 1, C = 3, LMAX = 12;
+};
+
+// Op codes.  D1 + s: dense gate on slot s; D2 + pair: on the slot pair (0,1),
+// (0,2), (0,3), (1,2), (1,3), (2,3); D3 + s: on the three slots other than s;
+// PHASE: one factor; SIGN: a factor of -1; DIAG: two factors chosen by the
+// parity of some index bits (RZ, RZZ); MOVE + x: amplitudes j and j ^ x
+// exchanged (x = 1..15 over the slots).
+enum : uint32_t { GP_D1 = 0, GP_D2 = 4, GP_D3 = 10, GP_PHASE = 14, GP_SIGN = 15, GP_DIAG = 16, GP_MOVE = 16 };
+
+// One op: 8 words, then its values (R).  A record applies to register j of
+// thread (local index) t in tile w when bit j of jbits is set, (t & tm) ==
+// tv and (w & om) == ov.  t is the tile element with the slot bits at zero.
+struct OpHead {
+    uint32_t code;          // op code | words to the next record << 8
+    uint32_t jbits;         // registers it applies to (D1..D3: by the first of each group) |
+                            // DIAG: registers with odd slot parity << 16
+    uint32_t tm, tv;
+    uint32_t om, ov;
+    uint32_t pt, po;        // DIAG: parity masks over t and w
+};
+static_assert(sizeof(OpHead) == 32, "eight words");
+
+// A round: 16 words.  The slots' addresses are worked out on the host: the
+// same uniform arithmetic in every wave cost more scalar instructions per
+// round (about 1,250) than the round's gates take vector ones.
+struct RoundHead {
+    uint32_t bit[kSlots];   // tile-local bit of each slot, ascending
+    uint32_t lds[kSlots];   // its LDS byte address (linear over GF(2))
+    uint32_t nops;
+    uint32_t phys[kSlots];  // its physical bit's position, for a direct round
+    uint32_t pad[3];
+};
+static_assert(sizeof(RoundHead) == 64, "sixteen words");
+constexpr uint32_t RND_WORDS = 16;
+
+struct PassArgs {
+    uint64_t qmask;         // physical tile bits
+    uint32_t L;
+    uint32_t nrounds;
+    uint32_t words;         // offset of the pass's records in the table
+    uint32_t direct;        // bit 0: the first round loads from memory, bit 1: the last one stores there
+    uint32_t top[kSlots];   // positions of the four highest tile bits (a thread's pieces), ascending
+};
+
+constexpr uint32_t kPutWords = 4000;              // 16,000 bytes of records per k_put launch
+struct PutArgs {
+    uint32_t* dst;
+    uint32_t n, pad;
+    uint32_t w[kPutWords];
+};
+
+__global__ __launch_bounds__(256) void k_put(PutArgs a) {
+    // the records straight from the argument block (a dynamic index into the
+    // by-value struct would copy it to scratch first)
+    const uint32_t* arg = (const uint32_t*)__builtin_amdgcn_kernarg_segment_ptr();
+    uint32_t* dst = a.dst;
+    for (uint32_t i = threadIdx.x; i < a.n; i += 256) dst[i] = arg[4 + i];
+}
+
+// Bits of x placed on the set bits of mask, ascending, a run at a time.
+__device__ __forceinline__ uint64_t place(uint64_t x, uint64_t mask) {
+    uint64_t r = 0;
+    while (mask) {
+        const uint64_t low = mask & (~mask + 1);
+        const uint64_t run = ((mask + low) & ~mask) - low;       // the lowest run of ones
+        const int len = __builtin_popcountll(run);
+        r |= (x * low) & run;
+        x = len < 64 ? x >> len : 0;
+        mask &= ~run;
+    }
+    return r;
+}
+
+// XOR (for disjoint bits: OR) of the entries at the bits set in j.
+template <int N, typename U>
+__device__ __forceinline__ U subset(const U (&v)[N], int j) {
+    U r = 0;
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+        if ((j >> k) & 1) r ^= v[k];
+    return r;
+}
+
+template <typename T>
+__device__ __forceinline__ T gld(uint32_t off) {
+    return *(const __attribute__((address_space(3))) T*)(size_t)off;
+}
+template <typename T>
+__device__ __forceinline__ void gst(uint32_t off, T v) {
+    *(__attribute__((address_space(3))) T*)(size_t)off = v;
+}
+template <typename R> struct Vec2;
+template <> struct Vec2<float> { using V = float __attribute__((ext_vector_type(2))); };
+template <> struct Vec2<double> { using V = double __attribute__((ext_vector_type(2))); };
+
+// ------------------------------------------------- ops on the 16 registers
+__device__ __forceinline__ float flip_sign(float x, uint32_t f) { return __uint_as_float(__float_as_uint(x) ^ f); }
+__device__ __forceinline__ double flip_sign(double x, uint32_t f) {
+    return __hiloint2double(__double2hiint(x) ^ (int)f, __double2loint(x));
+}
+
+template <typename R, typename T>
+__device__ __forceinline__ void pair2(const R* m, T& v0, T& v1) {
+    T o0, o1;
+    o0.x = m[0] * v0.x - m[1] * v0.y + m[2] * v1.x - m[3] * v1.y;
+    o0.y = m[0] * v0.y + m[1] * v0.x + m[2] * v1.y + m[3] * v1.x;
+    o1.x = m[4] * v0.x - m[5] * v0.y + m[6] * v1.x - m[7] * v1.y;
+    o1.y = m[4] * v0.y + m[5] * v0.x + m[6] * v1.y + m[7] * v1.x;
+    v0 = o0;
+    v1 = o1;
+}
+
+template <typename R, int S, typename T, int NA>
+__device__ __forceinline__ void op_d1(T (&a)[NA], const R* m, uint32_t jbits) {
+    constexpr uint32_t ALL = (S == 0 ? 0x5555u : S == 1 ? 0x3333u : S == 2 ? 0x0f0fu : 0x00ffu) & ((1u << NA) - 1u);
+    if (jbits == ALL) {
+#pragma unroll
+        for (int j = 0; j < NA; ++j)
+            if (!(j & (1 << S))) pair2<R>(m, a[j], a[j | (1 << S)]);
+    } else {
+#pragma unroll
+        for (int j = 0; j < NA; ++j)
+            if (!(j & (1 << S)) && ((jbits >> j) & 1)) pair2<R>(m, a[j], a[j | (1 << S)]);
+    }
+}
+
+// Dense gate on K of the slots (slot mask SM); mv: 2^K x 2^K complex.
+template <typename R, int K, int SM, typename T, int NA>
+__device__ __forceinline__ void op_dk(T (&a)[NA], const R* __restrict__ mv, uint32_t jbits) {
+    constexpr int D = 1 << K;
+#pragma unroll
+    for (int j = 0; j < NA; ++j) {
+        if (j & SM) continue;
+        if (!((jbits >> j) & 1)) continue;
+        T o[D];
+#pragma unroll
+        for (int i = 0; i < D; ++i) {
+            R re = 0, im = 0;
+            int sub = 0;                                       // register offset of column c
+#pragma unroll
+            for (int c = 0; c < D; ++c) {
+                const R mr = mv[2 * (i * D + c)], mi = mv[2 * (i * D + c) + 1];
+                const T v = a[j | sub];
+                re += mr * v.x - mi * v.y;
+                im += mr * v.y + mi * v.x;
+                sub = (sub - SM) & SM;
+            }
+            o[i].x = re;
+            o[i].y = im;
+        }
+        int sub = 0;
+#pragma unroll
+        for (int i = 0; i < D; ++i) {
+            a[j | sub] = o[i];
+            sub = (sub - SM) & SM;
+        }
+    }
+}
+
+template <int X, typename T, int NA>
+__device__ __forceinline__ void op_move(T (&a)[NA], uint32_t jbits) {
+#pragma unroll
+    for (int j = 0; j < NA; ++j) {
+        if (j & (X & -X)) continue;                            // the lowest moved bit is 0 in the first of a pair
+        if ((jbits >> j) & 1) {
+            const T t = a[j];
+            a[j] = a[j ^ X];
+            a[j ^ X] = t;
+        }
+    }
+}
+
+// A record's head and its first 8 values, in scalar registers: the next
+// record is loaded while the current one is applied (a wave otherwise waits
+// for two dependent scalar loads per gate, 1,500 cycles of a 2,000-cycle
+// gate where one workgroup holds the whole state).
+template <typename R> struct Rec {
+    static constexpr int NW = 8 + 8 * (int)sizeof(R) / 4;      // 16 or 24 words (a round's head is 16)
+    uint32_t w[NW];
+    __device__ __forceinline__ void load(const uint32_t* __restrict__ p) {
+        typedef uint32_t U8 __attribute__((ext_vector_type(8), aligned(4)));
+#pragma unroll
+        for (int i = 0; i < NW; i += 8) {
+            const U8 x = *(const U8*)(p + i);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) w[i + k] = x[k];
+        }
+    }
+    __device__ __forceinline__ R val(int i) const {
+        if constexpr (sizeof(R) == 4) return __uint_as_float(w[8 + i]);
+        else return __longlong_as_double((long long)((uint64_t)w[8 + 2 * i] | (uint64_t)w[9 + 2 * i] << 32));
+    }
+};
+
+template <typename R, typename T, int NA>
+__device__ __forceinline__ void apply_op(T (&a)[NA], const OpHead& h, const Rec<R>& rec,
+                                         const R* __restrict__ mv, uint32_t le, uint32_t w) {
+    const uint32_t code = h.code & 0xffu;
+    const uint32_t jb = h.jbits & 0xffffu;
+    if (code < GP_D2) {                                        // the most common ops first, by two branches
+        R m[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) m[i] = rec.val(i);
+        if (code < GP_D1 + 2) {
+            if (code == GP_D1) op_d1<R, 0>(a, m, jb);
+            else op_d1<R, 1>(a, m, jb);
+        } else {
+            if (NA == 8 || code == GP_D1 + 2) op_d1<R, 2>(a, m, jb);
+            else if constexpr (NA == 16) op_d1<R, 3>(a, m, jb);
+        }
+        return;
+    }
+    switch (code) {
+        case GP_D2 + 0: op_dk<R, 2, 3>(a, mv, jb); break;
+        case GP_D2 + 1: op_dk<R, 2, 5>(a, mv, jb); break;
+        case GP_D2 + 3: op_dk<R, 2, 6>(a, mv, jb); break;
+        case GP_D3 + 3: op_dk<R, 3, 7>(a, mv, jb); break;
+#define QVM_GP_4(C, K, SM) case C: if constexpr (NA == 16) op_dk<R, K, SM>(a, mv, jb); break;
+        QVM_GP_4(GP_D2 + 2, 2, 9) QVM_GP_4(GP_D2 + 4, 2, 10) QVM_GP_4(GP_D2 + 5, 2, 12)
+        QVM_GP_4(GP_D3 + 0, 3, 14) QVM_GP_4(GP_D3 + 1, 3, 13) QVM_GP_4(GP_D3 + 2, 3, 11)
+#undef QVM_GP_4
+        case GP_PHASE: {
+            const R pr = rec.val(0), pi = rec.val(1);
+#pragma unroll
+            for (int j = 0; j < NA; ++j)
+                if ((jb >> j) & 1) {
+                    const T v = a[j];
+                    a[j].x = pr * v.x - pi * v.y;
+                    a[j].y = pr * v.y + pi * v.x;
+                }
+        } break;
+        case GP_SIGN:
+#pragma unroll
+            for (int j = 0; j < NA; ++j) {                  // a sign-bit flip, without a branch per register
+                const uint32_t f = (jb << (31 - j)) & 0x80000000u;
+                a[j].x = flip_sign(a[j].x, f);
+                a[j].y = flip_sign(a[j].y, f);
+            }
+            break;
+        case GP_DIAG: {
+            const bool odd = ((__popc(le & h.pt) + __popc(w & h.po)) & 1) != 0;
+            const R er = odd ? rec.val(2) : rec.val(0), ei = odd ? rec.val(3) : rec.val(1);     // registers of even slot parity
+            const R qr = odd ? rec.val(0) : rec.val(2), qi = odd ? rec.val(1) : rec.val(3);
+#pragma unroll
+            for (int j = 0; j < NA; ++j)
+                if ((jb >> j) & 1) {
+                    const bool o = (h.jbits >> (16 + j)) & 1;
+                    const R pr = o ? qr : er, pi = o ? qi : ei;
+                    const T v = a[j];
+                    a[j].x = pr * v.x - pi * v.y;
+                    a[j].y = pr * v.y + pi * v.x;
+                }
+        } break;
+#define QVM_GP_MV(X) case GP_MOVE + X: if constexpr (X < NA) op_move<X>(a, jb); break;
+        QVM_GP_MV(1) QVM_GP_MV(2) QVM_GP_MV(3) QVM_GP_MV(4) QVM_GP_MV(5) QVM_GP_MV(6) QVM_GP_MV(7) QVM_GP_MV(8)
+        QVM_GP_MV(9) QVM_GP_MV(10) QVM_GP_MV(11) QVM_GP_MV(12) QVM_GP_MV(13) QVM_GP_MV(14) QVM_GP_MV(15)
+#undef QVM_GP_MV
+        default: break;
+    }
+}
+
+// ------------------------------------------------------------------ kernel
+// 2^(L-RS) threads work (at least a wave is launched); thread t's item in a
+// round is the tile element with t spread around the RS slots.  LDS addresses
+// use the tile kernel's swizzle: linear over GF(2), so register j's address
+// is the thread's XOR a uniform word, and four lane bits rarely collide.
+template <typename R, int RS>
+__global__ __launch_bounds__(RS == 4 && sizeof(R) == 8 ? 256 : 512, RS == 4 && sizeof(R) == 8 ? 2 : 4) void k_gate_pass(
+    typename GT<R>::T* __restrict__ psi, PassArgs A, const uint32_t* __restrict__ table) {
+    using T = typename GT<R>::T;
+    using V16 = typename GT<R>::V16;
+    using V2 = typename Vec2<R>::V;
+    constexpr int EP = GT<R>::EP;
+    constexpr int kAmps = 1 << RS;                             // amplitudes per thread
+    constexpr int NIT = kAmps / EP;                            // 16-byte pieces per thread
+    constexpr uint32_t ES = sizeof(T);
+    const uint32_t nt = 1u << (A.L - RS);                  // working threads
+    const uint32_t tid = threadIdx.x, w = blockIdx.x;
+    const bool live = tid < nt;
+    const uint64_t base = place(w, ~A.qmask);
+    T a[kAmps];
+    // stream in: pieces tid + nt i of the tile, all in flight, then to LDS.
+    // The index's high bits i are the tile's highest bits: a piece's offset
+    // and LDS slot are the thread's plus (XOR) those of the bits set in i.
+    constexpr int PB = EP == 2 ? RS - 1 : RS;                        // bits of i
+    uint64_t gtop[PB];
+    uint32_t stop[PB];
+#pragma unroll
+    for (int k = 0; k < PB; ++k) {
+        gtop[k] = 1ull << A.top[kSlots - PB + k];
+        stop[k] = tile_swizzle(1u << (A.L - PB + k));
+    }
+    if (!(A.direct & 1)) {
+        if (live) {
+            const uint64_t g0 = base + place(EP * tid, A.qmask);
+            const uint32_t s0 = tile_swizzle(EP * tid);
+            V16 v[NIT];
+#pragma unroll
+            for (int i = 0; i < NIT; ++i)
+                v[i] = __builtin_nontemporal_load((const V16*)(psi + g0 + subset<PB>(gtop, i)));
+#pragma unroll
+            for (int i = 0; i < NIT; ++i) {
+                const uint32_t s = s0 ^ (uint32_t)subset<PB>(stop, i);
+                if constexpr (EP == 2) {
+                    const V16 x = (s & 1) ? V16{v[i][2], v[i][3], v[i][0], v[i][1]} : v[i];
+                    gst<V16>((s & ~1u) * ES, x);
+                } else {
+                    gst<V16>(s * ES, v[i]);
+                }
+            }
+        }
+        __syncthreads();
+    }
+    const uint32_t* __restrict__ p = table + A.words;
+    Rec<R> cur, nxt;
+    cur.load(p);
+    for (uint32_t r = 0; r < A.nrounds; ++r) {
+        uint32_t hd[RND_WORDS];
+#pragma unroll
+        for (int i = 0; i < (int)RND_WORDS; ++i) hd[i] = cur.w[i];
+        const uint32_t nops = hd[8];
+        p += RND_WORDS;
+        nxt.load(p);
+        uint32_t le = tid;                                     // a zero inserted at every slot
+#pragma unroll
+        for (int k = 0; k < RS; ++k) le = ((le & ~(hd[k] - 1)) << 1) | (le & (hd[k] - 1));
+        uint32_t sl = tile_swizzle(le) * ES;
+        uint32_t so[RS];
+#pragma unroll
+        for (int k = 0; k < RS; ++k) so[k] = hd[4 + k];
+        uint64_t go[RS];
+#pragma unroll
+        for (int k = 0; k < RS; ++k) go[k] = 1ull << hd[9 + k];
+        if (live) {
+            if (r == 0 && (A.direct & 1)) {
+                const uint64_t gb = base + place(le, A.qmask);
+#pragma unroll
+                for (int j = 0; j < kAmps; ++j) {
+                    const V2 x = __builtin_nontemporal_load((const V2*)(psi + gb + subset<RS>(go, j)));
+                    a[j].x = x[0];
+                    a[j].y = x[1];
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < kAmps; ++j) {
+                    const V2 x = gld<V2>(sl ^ subset<RS>(so, j));
+                    a[j].x = x[0];
+                    a[j].y = x[1];
+                }
+            }
+        }
+        cur = nxt;
+        for (uint32_t q = 0; q < nops; ++q) {
+            const OpHead h{cur.w[0], cur.w[1], cur.w[2], cur.w[3], cur.w[4], cur.w[5], cur.w[6], cur.w[7]};
+            const R* mv = (const R*)(p + sizeof(OpHead) / 4);
+            p += h.code >> 8;
+            nxt.load(p);
+            if ((w & h.om) == h.ov && (le & h.tm) == h.tv) apply_op<R>(a, h, cur, mv, le, w);
+            cur = nxt;
+        }
+        const bool last = r + 1 == A.nrounds;
+        if (live) {
+            if (last && (A.direct & 2)) {
+                const uint64_t gb = base + place(le, A.qmask);
+#pragma unroll
+                for (int j = 0; j < kAmps; ++j)
+                    __builtin_nontemporal_store(V2{a[j].x, a[j].y}, (V2*)(psi + gb + subset<RS>(go, j)));
+            } else {
+#pragma unroll
+                for (int j = 0; j < kAmps; ++j) gst<V2>(sl ^ subset<RS>(so, j), V2{a[j].x, a[j].y});
+            }
+        }
+        if (!(last && (A.direct & 2))) __syncthreads();
+    }
+    if (!(A.direct & 2) && live) {
+        const uint64_t g0 = base + place(EP * tid, A.qmask);
+        const uint32_t s0 = tile_swizzle(EP * tid);
+#pragma unroll
+        for (int i = 0; i < NIT; ++i) {
+            const uint32_t s = s0 ^ subset<PB>(stop, i);
+            V16 x;
+            if constexpr (EP == 2) {
+                x = gld<V16>((s & ~1u) * ES);
+                if (s & 1) x = V16{x[2], x[3], x[0], x[1]};
+            } else {
+                x = gld<V16>(s * ES);
+            }
+            __builtin_nontemporal_store(x, (V16*)(psi + g0 + subset<PB>(gtop, i)));
+        }
+    }
+}
+
+// =============================================================== scheduling
+inline int pc(uint64_t v) { return __builtin_popcountll(v); }
+
+// A gate (or a merged run of uncontrolled one-target gates on one qubit) on
+// physical bits.
+struct GGate {
+    LOp op;
+    uint64_t xq;            // bits it does not act diagonally on (dense targets, moved bits)
+    uint64_t zq;            // bits it acts diagonally on (controls, diagonal targets)
+    double frac;            // share of the amplitudes its own kernel would touch
+};
+
+struct Sched {
+    uint64_t bx = 0, bz = 0;                     // bits held by gates passed over
+    bool free(const GGate& g) const { return !(g.xq & (bx | bz)) && !(g.zq & bx); }
+    void hold(const GGate& g) {
+        bx |= g.xq;
+        bz |= g.zq;
+    }
+};
+
+uint32_t local_bits(uint64_t phys, uint64_t qmask) {            // phys bits (all in qmask) as tile-local bits
+    uint32_t r = 0;
+    for (uint64_t m = phys; m; m &= m - 1)
+        r |= 1u << pc(qmask & ((m & (~m + 1)) - 1));
+    return r;
+}
+uint32_t tile_index_bits(uint64_t phys, uint64_t qmask) {       // phys bits outside qmask as bits of the tile index
+    uint32_t r = 0;
+    for (uint64_t m = phys & ~qmask; m; m &= m - 1) r |= 1u << pc(~qmask & ((m & (~m + 1)) - 1));
+    return r;
+}
+
+template <typename R>
+struct Emit {
+    std::vector<uint32_t>& tab;
+    uint64_t qmask;
+    uint64_t slots_phys;
+    int rs;                                      // slots
+    uint64_t slot_phys[kSlots];                  // ascending
+
+    uint32_t slot_bits(uint64_t phys) const {
+        uint32_t r = 0;
+        for (int s = 0; s < rs; ++s)
+            if (phys & slot_phys[s]) r |= 1u << s;
+        return r;
+    }
+    // registers j whose slot bits match (mask, val) and with no bit of `zero`
+    uint32_t regs(uint32_t mask, uint32_t val, uint32_t zero) const {
+        uint32_t b = 0;
+        for (uint32_t j = 0; j < 1u << rs; ++j)
+            if ((j & mask) == val && !(j & zero)) b |= 1u << j;
+        return b;
+    }
+    void record(OpHead h, const double* v, int nv) {
+        const int words = (int)(sizeof(OpHead) / 4) + (int)(nv * sizeof(R) / 4);
+        h.code |= (uint32_t)words << 8;
+        const size_t at = tab.size();
+        tab.resize(at + words);
+        memcpy(&tab[at], &h, sizeof(h));
+        for (int i = 0; i < nv; ++i) {
+            const R x = (R)v[i];
+            memcpy((char*)&tab[at + sizeof(OpHead) / 4] + i * sizeof(R), &x, sizeof(R));
+        }
+    }
+    OpHead head(uint32_t code, uint64_t cmask, uint64_t cval, uint32_t zero) const {
+        OpHead h{};
+        h.code = code;
+        h.jbits = regs(slot_bits(cmask), slot_bits(cval), zero);
+        const uint64_t in = cmask & qmask & ~slots_phys;
+        h.tm = local_bits(in, qmask);
+        h.tv = local_bits(in & cval, qmask);
+        h.om = tile_index_bits(cmask, qmask);
+        h.ov = tile_index_bits(cval, qmask);
+        return h;
+    }
+    // records it writes for one gate
+    int gate(const GGate& g) {
+        const LOp& o = g.op;
+        double v[128];
+        switch (o.cls) {
+            case OP_PHASE: {
+                const bool neg = o.phase == cd(-1.0, 0.0);
+                v[0] = o.phase.real();
+                v[1] = o.phase.imag();
+                record(head(neg ? GP_SIGN : GP_PHASE, o.cond_mask, o.cond_val, 0), v, neg ? 0 : 2);
+                return 1;
+            }
+            case OP_DIAG: {
+                const int D = 1 << o.k;
+                auto bits = [&](int j) {
+                    uint64_t b = 0;
+                    for (int r = 0; r < o.k; ++r)
+                        if ((j >> r) & 1) b |= 1ull << o.t[r];
+                    return b;
+                };
+                bool par = true;
+                for (int j = 0; j < D; ++j)
+                    if (o.m[j] != o.m[pc((uint64_t)j) & 1]) par = false;
+                if (par) {
+                    const uint64_t tm = bits(D - 1);
+                    OpHead h = head(GP_DIAG, o.cmask, o.cmask, 0);
+                    const uint32_t ps = slot_bits(tm);
+                    for (uint32_t j = 0; j < 1u << rs; ++j)
+                        if (__builtin_popcount(j & ps) & 1) h.jbits |= 1u << (16 + j);
+                    h.pt = local_bits(tm & qmask & ~slots_phys, qmask);
+                    h.po = tile_index_bits(tm, qmask);
+                    for (int i = 0; i < 2; ++i) {
+                        v[2 * i] = o.m[i].real();
+                        v[2 * i + 1] = o.m[i].imag();
+                    }
+                    record(h, v, 4);
+                    return 1;
+                }
+                for (int j = 0; j < D; ++j) {                   // one factor per entry, each on its own amplitudes
+                    v[0] = o.m[j].real();
+                    v[1] = o.m[j].imag();
+                    record(head(GP_PHASE, o.cmask | bits(D - 1), o.cmask | bits(j), 0), v, 2);
+                }
+                return D;
+            }
+            case OP_SWAPPAIR: {
+                // the condition on the amplitude of a pair whose lowest
+                // moved bit is 0 (the lowered op names the one with hbit 0)
+                const uint64_t cm = o.cond_mask | o.hbit;
+                uint64_t cv = o.cond_val & ~o.hbit;
+                if (cm & cv & o.xmask & (~o.xmask + 1)) cv ^= cm & o.xmask;
+                record(head(GP_MOVE + slot_bits(o.xmask), cm, cv, 0), v, 0);
+                return 1;
+            }
+            default: break;
+        }
+        // dense: matrix rows and columns reordered to ascending slots
+        const int D = 1 << o.k;
+        uint64_t tm = 0;
+        for (int r = 0; r < o.k; ++r) tm |= 1ull << o.t[r];
+        int at[3] = {0, 0, 0};                                  // matrix bit of the s-th lowest target
+        {
+            int s = 0;
+            for (uint64_t m = tm; m; m &= m - 1, ++s)
+                for (int r = 0; r < o.k; ++r)
+                    if (o.t[r] == __builtin_ctzll(m)) at[s] = r;
+        }
+        auto src = [&](int j) {
+            int q = 0;
+            for (int s = 0; s < o.k; ++s)
+                if ((j >> s) & 1) q |= 1 << at[s];
+            return q;
+        };
+        for (int i = 0; i < D; ++i)
+            for (int j = 0; j < D; ++j) {
+                const cd x = o.m[(size_t)src(i) * D + src(j)];
+                v[2 * (i * D + j)] = x.real();
+                v[2 * (i * D + j) + 1] = x.imag();
+            }
+        const uint32_t sm = slot_bits(tm);
+        uint32_t code;
+        if (o.k == 1) code = GP_D1 + __builtin_ctz(sm);
+        else if (o.k == 3) code = GP_D3 + __builtin_ctz(~sm);      // (three slots: the code without slot 3)
+        else code = GP_D2 + (sm == 3 ? 0 : sm == 5 ? 1 : sm == 9 ? 2 : sm == 6 ? 3 : sm == 10 ? 4 : 5);
+        record(head(code, o.cmask, o.cmask, sm), v, 2 * D * D);
+        return 1;
+    }
+};
+
+// Bits of the tile for the next pass and the gates it takes: gates in list
+// order, a gate passed over when a gate before it that was passed over
+// holds one of its bits (two gates that both act diagonally on the bits
+// they share commute) or when its bits do not fit in the tile.
+uint64_t take_pass(const std::vector<GGate>& G, const std::vector<char>& done, size_t first, int n, int L, int c,
+                   std::vector<int>& ops) {
+    const uint64_t all = n >= 64 ? ~0ull : (1ull << n) - 1;
+    uint64_t T = (1ull << std::min(c, n)) - 1;
+    if (L >= n) T = all;
+    Sched s;
+    ops.clear();
+    for (size_t i = first; i < G.size() && (s.bx & all) != all; ++i) {
+        if (done[i]) continue;
+        const GGate& g = G[i];
+        if (s.free(g) && pc(T | g.xq) <= L) {
+            T |= g.xq;
+            ops.push_back((int)i);
+        } else {
+            s.hold(g);
+        }
+    }
+    for (int q = 0; q < n && pc(T) < L; ++q) T |= 1ull << q;     // long runs: the lowest bits left
+    return T;
+}
+
+template <typename R>
+qvm_status run_segment(qvm_sv* sv, const std::vector<GGate>& G) {
+    using T = typename GT<R>::T;
+    const int n = sv->n, c = GT<R>::C;
+    const double S = (double)(1ull << n) * sizeof(T);
+    // Below 21 qubits a pass has few tiles, and the time of one wave through
+    // its gates counts: 8 amplitudes a thread instead of 16, and tiles that
+    // give 16 to 128 workgroups, as far as the passes that smaller tiles
+    // need (each two launches) pay (measured, microseconds: 12-qubit layered
+    // circuit of 175 gates, complex128, in one 12-qubit tile 102 against 109
+    // with 16 amplitudes; 17 qubits, 200 mixed gates, complex64, tiles of
+    // 2^10 / 2^11 / 2^12 172 / 168 / 171, 2^13 with 16 amplitudes 216; 20
+    // qubits 2^12 with 8 amplitudes 180, 2^13 with 16 225).  From 21 qubits
+    // on the chip is full and the fewest passes win (23 qubits: 572 against
+    // 630).
+    const int Lmax = n <= 12 ? 12 : n <= 16 ? 10 : n <= 19 ? 11 : n <= 20 ? 12 : GT<R>::LMAX;
+    const int rs = n <= 20 ? 3 : 4;
+    std::vector<char> done(G.size(), 0);
+    std::vector<int> ops, left, next;
+    std::vector<uint32_t> tab;
+    size_t remaining = G.size(), first = 0;
+    uint32_t* dtab = (uint32_t*)(sv->work + sv->lay.plan_off);
+    const size_t cap = sv->lay.plan_bytes / 4;
+    size_t used = 0;
+    while (remaining) {
+        while (done[first]) ++first;
+        const int L = std::min(n, Lmax);
+        const uint64_t qmask = take_pass(G, done, first, n, L, c, ops);
+        // one gate's kernel costs a launch (3 us) and its share of the
+        // state's traffic (5.5 TB/s), a pass two launches and all of the
+        // traffic (5 TB/s): a few phases or moves on large states, and one
+        // or two gates on small ones, stay one kernel each
+        double each = 0;
+        for (int i : ops) each += 3e-6 + 2.0 * S * G[i].frac / 5.5e12;
+        const bool pass = ops.size() > 1 && each > 8e-6 + 2.0 * S / 5.0e12;
+        for (int i : ops) done[i] = 1;
+        remaining -= ops.size();
+        if (!pass) {
+            for (int i : ops) {
+                qvm_status st = launch_op(sv, G[i].op);
+                if (st) return st;
+            }
+            continue;
+        }
+        // rounds
+        PassArgs A{};
+        A.qmask = qmask;
+        A.L = (uint32_t)L;
+        {
+            int k = kSlots;
+            for (int b = n - 1; k > 0; --b)
+                if ((qmask >> b) & 1) A.top[--k] = (uint32_t)b;
+        }
+        tab.clear();
+        left = ops;
+        double flops = 0;
+        std::vector<uint64_t> round_slots;
+        while (!left.empty()) {
+            Sched s;
+            uint64_t sm = 0;
+            next.clear();
+            std::vector<int> now;
+            for (size_t q = 0; q < left.size(); ++q) {
+                const GGate& g = G[left[q]];
+                if ((s.bx & qmask) != qmask && s.free(g) && pc(sm | g.xq) <= rs) {
+                    sm |= g.xq;
+                    now.push_back(left[q]);
+                } else {
+                    s.hold(g);
+                    next.push_back(left[q]);
+                }
+            }
+            for (int b = n - 1; b >= 0 && pc(sm) < rs; --b)     // free slots: the highest tile bits
+                if ((qmask >> b) & 1) sm |= 1ull << b;
+            const size_t at = tab.size();
+            tab.resize(at + RND_WORDS);
+            Emit<R> E{tab, qmask, sm, rs, {}};
+            {
+                int k = 0;
+                for (uint64_t m = sm; m; m &= m - 1) E.slot_phys[k++] = m & (~m + 1);
+            }
+            uint32_t nops = 0;
+            for (int i : now) {
+                nops += (uint32_t)E.gate(G[i]);
+                const LOp& o = G[i].op;
+                const double touched = G[i].frac * (double)(1ull << n);
+                flops += o.cls == OP_DENSE ? touched * 8.0 * (1 << o.k) : o.cls == OP_SWAPPAIR ? 0.0 : 6.0 * touched;
+            }
+            RoundHead rh{};
+            for (int k = 0; k < rs; ++k) {
+                rh.bit[k] = local_bits(E.slot_phys[k], qmask);
+                rh.lds[k] = tile_swizzle(rh.bit[k]) * (uint32_t)sizeof(T);
+                rh.phys[k] = (uint32_t)__builtin_ctzll(E.slot_phys[k]);
+            }
+            rh.nops = nops;
+            memcpy(&tab[at], &rh, sizeof(rh));
+            round_slots.push_back(sm);
+            ++A.nrounds;
+            left.swap(next);
+        }
+        const uint64_t low = (1ull << std::min(c, n)) - 1;
+        if (!(round_slots.front() & low)) A.direct |= 1;
+        if (!(round_slots.back() & low)) A.direct |= 2;
+        tab.resize((tab.size() + 31) & ~size_t(31));
+        if (used + tab.size() + 64 > cap) used = 0;             // in stream order: the passes before have run
+        if (tab.size() + 64 > cap) return fail(QVM_ENOMEM, "gate pass records exceed the workspace plan area");
+        A.words = (uint32_t)used;
+        PutArgs pa;
+        for (size_t o = 0; o < tab.size(); o += kPutWords) {
+            pa.dst = dtab + used + o;
+            pa.n = (uint32_t)std::min<size_t>(kPutWords, tab.size() - o);
+            pa.pad = 0;
+            memcpy(pa.w, tab.data() + o, pa.n * 4);
+            hipLaunchKernelGGL(k_put, dim3(1), dim3(256), 0, sv->stream, pa);
+            QVM_LAUNCH_CHECK(sv);
+        }
+        used += tab.size();
+        const unsigned threads = std::max(64u, 1u << (L - rs));
+        const size_t lds = A.direct == 3 && A.nrounds == 1 ? 0 : sizeof(T) << L;
+        const int tok = prof_begin(sv);
+        if (rs == 3)
+            hipLaunchKernelGGL((k_gate_pass<R, 3>), dim3(1u << (n - L)), dim3(threads), lds, sv->stream, (T*)sv->amps,
+                               A, dtab);
+        else
+            hipLaunchKernelGGL((k_gate_pass<R, 4>), dim3(1u << (n - L)), dim3(threads), lds, sv->stream, (T*)sv->amps,
+                               A, dtab);
+        QVM_LAUNCH_CHECK(sv);
+        prof_end(sv, tok, PK_GATES, 2.0 * S, flops);
+    }
+    return QVM_OK;
+}
+
+}  // namespace
+
+// The gate list in segments: bounds the host's work lists and the scans of
+// the scheduler.
+constexpr size_t kSegment = 4096;
+
+qvm_status run_gates(qvm_sv* sv, const qvm_gate* gates, size_t n_gates) {
+    std::vector<cd> u;
+    std::vector<GGate> G;
+    auto push = [&](const LOp& op) {
+        GGate g{op, 0, 0, 0};
+        uint64_t tm = 0;
+        for (int r = 0; r < op.k; ++r) tm |= 1ull << op.t[r];
+        switch (op.cls) {
+            case OP_PHASE:
+                g.zq = op.cond_mask;
+                g.frac = std::ldexp(1.0, -pc(op.cond_mask));
+                break;
+            case OP_DIAG:
+                g.zq = op.cmask | tm;
+                g.frac = std::ldexp(1.0, -pc(op.cmask));
+                break;
+            case OP_SWAPPAIR:
+                g.xq = op.xmask;
+                g.zq = op.cond_mask & ~op.xmask;
+                g.frac = std::ldexp(2.0, -pc(op.cond_mask | op.hbit));
+                break;
+            default:
+                g.xq = tm;
+                g.zq = op.cmask;
+                g.frac = std::ldexp(1.0, -pc(op.cmask));
+        }
+        G.push_back(std::move(g));
+    };
+    for (size_t s0 = 0; s0 < n_gates; s0 += kSegment) {
+        const size_t s1 = std::min(n_gates, s0 + kSegment);
+        G.clear();
+        // runs of uncontrolled one-target gates on a qubit become one gate
+        // (their product, in double precision)
+        struct Run { cd m[4]; };
+        std::vector<Run> runs;
+        std::vector<int> run_of;                 // per entry of order: run index, or -1 - gate index
+        int open[QVM_MAX_QUBITS];
+        std::fill(open, open + QVM_MAX_QUBITS, -1);
+        std::vector<int> run_t;
+        for (size_t i = s0; i < s1; ++i) {
+            const qvm_gate& g = gates[i];
+            if (g.k == 1 && g.ctrl_mask == 0) {
+                qvm_status st = gate_matrix(g, u);
+                if (st) return st;
+                const int t = sv->perm[g.targets[0]];
+                if (open[t] >= 0) {
+                    Run& r = runs[open[t]];
+                    cd p[4];
+                    for (int a = 0; a < 2; ++a)
+                        for (int b = 0; b < 2; ++b) {
+                            const cd x = u[2 * a], y = r.m[b], z = u[2 * a + 1], v = r.m[2 + b];
+                            p[2 * a + b] = cd(x.real() * y.real() - x.imag() * y.imag() + z.real() * v.real() - z.imag() * v.imag(),
+                                              x.real() * y.imag() + x.imag() * y.real() + z.real() * v.imag() + z.imag() * v.real());
+                        }
+                    std::copy(p, p + 4, r.m);
+                } else {
+                    open[t] = (int)runs.size();
+                    run_of.push_back((int)runs.size());
+                    run_t.push_back(t);
+                    Run r;
+                    std::copy(u.begin(), u.begin() + 4, r.m);
+                    runs.push_back(r);
+                }
+            } else {
+                run_of.push_back(-1 - (int)(i - s0));
+                for (uint64_t m = g.ctrl_mask; m; m &= m - 1) open[sv->perm[__builtin_ctzll(m)]] = -1;
+                for (int r = 0; r < g.k; ++r) open[sv->perm[g.targets[r]]] = -1;
+            }
+        }
+        G.reserve(run_of.size());
+        for (int e : run_of) {
+            LOp op;
+            if (e >= 0) {
+                u.assign(runs[e].m, runs[e].m + 4);
+                op = classify(1, &run_t[e], 0, u);
+            } else {
+                const qvm_gate& g = gates[s0 + (size_t)(-1 - e)];
+                qvm_status st = gate_matrix(g, u);
+                if (st) return st;
+                op = lower(sv, g, u);
+            }
+            if (op.cls == OP_PHASE && op.phase == cd(1.0, 0.0)) continue;      // identity
+            push(op);
+        }
+        qvm_status st;
+        if (sv->n < kSlots || G.size() < 2) {
+            st = QVM_OK;
+            for (const GGate& g : G)
+                if ((st = launch_op(sv, g.op))) break;
+        } else {
+            st = sv->dt == QVM_C64 ? run_segment<float>(sv, G) : run_segment<double>(sv, G);
+        }
+        if (st) return st;
+    }
+    return QVM_OK;
+}
+
+}  // namespace qvm

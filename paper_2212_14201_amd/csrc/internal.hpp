@@ -35,7 +35,7 @@ constexpr int kRedSlots = 64;         // doubles per block in the partials table
 
 // Per-launch timing with HIP events (enabled by qvm_profile_begin).
 enum ProfKind { PK_DENSE1 = 0, PK_DENSE2, PK_DENSE3, PK_DIAG, PK_PHASE, PK_SWAP, PK_TILE,
-                PK_BASIS, PK_RDM1, PK_COUNT };
+                PK_BASIS, PK_RDM1, PK_GATES, PK_COUNT };
 struct ProfRec {
     int kind;
     int ev;                           // index of the start event; end = ev + 1
@@ -111,6 +111,8 @@ LOp classify(int k, const int* phys_t, uint64_t phys_cmask, const std::vector<cd
 
 // ----------------------------------------------------- plain-path launchers
 qvm_status launch_op(qvm_sv* sv, const LOp& op);
+// A validated gate list, many gates per pass over the state (gatepass.hip).
+qvm_status run_gates(qvm_sv* sv, const qvm_gate* gates, size_t n_gates);
 qvm_status launch_init_basis(qvm_sv* sv, uint64_t phys_index);
 qvm_status launch_swap_bits(qvm_sv* sv, int a, int b);   // physical bit swap
 

@@ -81,11 +81,14 @@ def sweep_gates(ns, dtypes=("c128", "c64"), count=32, seed=7):
         for n in ns:
             sv = qvm.StateVector(n, dtype, init=0)
             for kind in GATE_KINDS:
-                ga = qvm.GateArray(gate_list(kind, n, count, seed + n))
-                sv.run(ga)                                  # warm-up
+                # one kernel per gate (a list given to run() shares passes)
+                gates = gate_list(kind, n, count, seed + n)
+                for g in gates:
+                    sv.apply(g)                             # warm-up
                 e0, e1 = _events()
                 e0.record()
-                sv.run(ga)
+                for g in gates:
+                    sv.apply(g)
                 e1.record()
                 torch.cuda.synchronize()
                 ms = e0.elapsed_time(e1) / count
