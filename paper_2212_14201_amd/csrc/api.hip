@@ -514,25 +514,14 @@ qvm_status qvm_expect_pauli(qvm_sv* sv, size_t nt, const uint64_t* x, const uint
     for (size_t t = 0; t < nt; ++t)
         if ((x[t] & ~lim) || (z[t] & ~lim)) return fail(QVM_ERANGE, "Pauli mask names a qubit >= n");
     std::vector<double> vals(nt, 0.0);
-    std::vector<bool> done(nt, false);
-    for (size_t t = 0; t < nt; ++t) {
-        if (done[t]) continue;
-        // group all terms with this x mask
-        std::vector<size_t> grp;
-        for (size_t u = t; u < nt; ++u)
-            if (!done[u] && x[u] == x[t]) grp.push_back(u);
-        uint64_t xp = phys_mask(sv, x[t]);
-        for (size_t s = 0; s < grp.size(); s += 32) {
-            int cnt = (int)std::min<size_t>(32, grp.size() - s);
-            uint64_t zp[32];
-            double res[32];
-            for (int i = 0; i < cnt; ++i) zp[i] = phys_mask(sv, z[grp[s + i]]);
-            qvm_status st = rd_pauli_group(sv, xp, cnt, zp, res);
-            if (st) return st;
-            for (int i = 0; i < cnt; ++i) vals[grp[s + i]] = res[i];
-        }
-        for (size_t u : grp) done[u] = true;
-    }
+    std::vector<PauliTerm> terms(nt);
+    for (size_t t = 0; t < nt; ++t) terms[t] = PauliTerm{phys_mask(sv, x[t]), phys_mask(sv, z[t]), t};
+    auto odd = [](const PauliTerm& p) { return __builtin_popcountll(p.x & p.z) & 1; };
+    std::stable_sort(terms.begin(), terms.end(), [&](const PauliTerm& p, const PauliTerm& q) {
+        return p.x != q.x ? p.x < q.x : odd(p) < odd(q);
+    });
+    qvm_status st = rd_pauli(sv, terms, vals.data());
+    if (st) return st;
     if (out_terms)
         for (size_t t = 0; t < nt; ++t) out_terms[t] = vals[t];
     if (out_sum) {

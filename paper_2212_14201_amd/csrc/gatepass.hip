@@ -754,15 +754,8 @@ qvm_status run_segment(qvm_sv* sv, const std::vector<GGate>& G) {
         if (used + tab.size() + 64 > cap) used = 0;             // in stream order: the passes before have run
         if (tab.size() + 64 > cap) return fail(QVM_ENOMEM, "gate pass records exceed the workspace plan area");
         A.words = (uint32_t)used;
-        PutArgs pa;
-        for (size_t o = 0; o < tab.size(); o += kPutWords) {
-            pa.dst = dtab + used + o;
-            pa.n = (uint32_t)std::min<size_t>(kPutWords, tab.size() - o);
-            pa.pad = 0;
-            memcpy(pa.w, tab.data() + o, pa.n * 4);
-            hipLaunchKernelGGL(k_put, dim3(1), dim3(256), 0, sv->stream, pa);
-            QVM_LAUNCH_CHECK(sv);
-        }
+        qvm_status st = put_words(sv, dtab + used, tab.data(), tab.size());
+        if (st) return st;
         used += tab.size();
         const unsigned threads = std::max(64u, 1u << (L - rs));
         const size_t lds = A.direct == 3 && A.nrounds == 1 ? 0 : sizeof(T) << L;
@@ -780,6 +773,19 @@ qvm_status run_segment(qvm_sv* sv, const std::vector<GGate>& G) {
 }
 
 }  // namespace
+
+qvm_status put_words(qvm_sv* sv, uint32_t* dst, const uint32_t* src, size_t n) {
+    PutArgs pa;
+    pa.pad = 0;
+    for (size_t o = 0; o < n; o += kPutWords) {
+        pa.dst = dst + o;
+        pa.n = (uint32_t)std::min<size_t>(kPutWords, n - o);
+        memcpy(pa.w, src + o, pa.n * 4);
+        hipLaunchKernelGGL(k_put, dim3(1), dim3(256), 0, sv->stream, pa);
+        QVM_LAUNCH_CHECK(sv);
+    }
+    return QVM_OK;
+}
 
 // The gate list in segments: bounds the host's work lists and the scans of
 // the scheduler.

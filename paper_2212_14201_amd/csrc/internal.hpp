@@ -113,6 +113,9 @@ LOp classify(int k, const int* phys_t, uint64_t phys_cmask, const std::vector<cd
 qvm_status launch_op(qvm_sv* sv, const LOp& op);
 // A validated gate list, many gates per pass over the state (gatepass.hip).
 qvm_status run_gates(qvm_sv* sv, const qvm_gate* gates, size_t n_gates);
+// Write words to device memory on the state's stream, carried as kernel
+// arguments (nothing on the host has to outlive the call).
+qvm_status put_words(qvm_sv* sv, uint32_t* dst, const uint32_t* src, size_t n);
 qvm_status launch_init_basis(qvm_sv* sv, uint64_t phys_index);
 qvm_status launch_swap_bits(qvm_sv* sv, int a, int b);   // physical bit swap
 
@@ -123,8 +126,12 @@ qvm_status rd_z_all(qvm_sv* sv, double* out_phys_total, double* out_phys_bit);
 // out = {sum |psi_i|^2 over physical bit pbit = 0, the same over bit = 1,
 //        Re and Im of sum psi_i conj(psi_{i | 2^pbit})}, FP64; synchronizes
 qvm_status rd_rdm1(qvm_sv* sv, int pbit, double* out);
-qvm_status rd_pauli_group(qvm_sv* sv, uint64_t x_phys, int nt, const uint64_t* z_phys,
-                          double* out);
+// Pauli strings on physical bits, sorted by (x, |x & z| odd); out[term.index]
+struct PauliTerm {
+    uint64_t x, z;
+    size_t index;
+};
+qvm_status rd_pauli(qvm_sv* sv, const std::vector<PauliTerm>& terms, double* out);
 qvm_status rd_probs_full(qvm_sv* sv, double* out_host);
 qvm_status rd_marginal(qvm_sv* sv, int m, const int* phys_q, double* out_host);
 qvm_status rd_sample(qvm_sv* sv, size_t ns, const double* u, uint64_t* out_logical);
