@@ -348,9 +348,9 @@ def noise_measure(torch, reps=3):
     """Kraus trajectories: 26 qubits, complex64, 4 layers of RY + RZ on every
     qubit, a CNOT / CZ brick and an H (262 gates), with depolarizing noise
     after every RY, amplitude damping on both qubits of every CNOT, phase
-    damping after every RZ and bit flips after every H.  Each branching is
-    one FP64 pass for the qubit's reduced density matrix plus the chosen
-    operator's plain-kernel pass."""
+    damping after every RZ and bit flips after every H.  Branchings on up to
+    four qubits share a pass, which applies the gates and operators before
+    and measures their joint density matrix in FP64."""
     import numpy as np
     from paper_2212_14201_amd import noise, profiling, qvm
     from workloads import noisy_layers, uniform_stream

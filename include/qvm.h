@@ -168,6 +168,24 @@ qvm_status qvm_kraus_ops(qvm_channel kind, double p, double t1, double t2, doubl
 qvm_status qvm_apply_kraus(qvm_sv* sv, int32_t qubit, int32_t n_ops, const double* ops, double u,
                            int32_t* chosen, double* probs);
 
+/* One noisy run from the state as it is: the gates in order as in qvm_run,
+ * gate i followed by the branchings first[i] .. first[i + 1] - 1 (first has
+ * n_gates + 1 entries, first[0] = 0).  Branching q is qvm_apply_kraus on
+ * qubit[q] with channel[q]'s operators and uniforms[q]; branches[q] receives
+ * its branch.  Channel c has n_ops[c] operators; ops holds the channels'
+ * operators one channel after the other, each as in qvm_apply_kraus.  The
+ * weights of up to four qubits' branchings come from one measurement of
+ * their joint density matrix (FP64), on which the gates and chosen operators
+ * between are then played on the host.  Everything is validated before
+ * anything is enqueued; errors as in qvm_run and qvm_apply_kraus (a branching
+ * whose weights are all zero ends the run there, the gates and branchings
+ * since the last measurement not applied).  Synchronizes the stream.  Uses
+ * the workspace's staging and plan areas. */
+qvm_status qvm_run_trajectory(qvm_sv* sv, const qvm_gate* gates, size_t n_gates, const size_t* first,
+                              const int32_t* qubit, const int32_t* channel, size_t n_channels,
+                              const int32_t* n_ops, const double* ops, const double* uniforms,
+                              int32_t* branches);
+
 /* Apply a gate list in order with the plain per-gate path, in one call (the
  * per-gate call overhead the paper measures at small n is paid once).  Each
  * gate is applied with its own matrix (consecutive uncontrolled one-target

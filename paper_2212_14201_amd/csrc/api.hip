@@ -248,6 +248,31 @@ LOp classify(int k, const int* t, uint64_t cmask, const std::vector<cd>& u) {
     return op;
 }
 
+qvm_status choose_branch(const double* r, int n_ops, const double* ops, double u, int* branch, cd* m, double* probs) {
+    const cd r01(r[2], r[3]);
+    // p_i = ||K_i psi||^2 = Tr(K_i^dag K_i rho)
+    double w[QVM_MAX_KRAUS], total = 0;
+    for (int i = 0; i < n_ops; ++i) {
+        const double* k = ops + 8 * i;
+        const cd a(k[0], k[1]), b(k[2], k[3]), c(k[4], k[5]), d(k[6], k[7]);
+        const double m00 = std::norm(a) + std::norm(c), m11 = std::norm(b) + std::norm(d);
+        const cd m01 = std::conj(a) * b + std::conj(c) * d;          // (K^dag K)_{01}
+        // Tr(M rho) = m00 r00 + m11 r11 + 2 Re(m01 conj(r01))
+        w[i] = std::max(0.0, m00 * r[0] + m11 * r[1] + 2.0 * (m01 * std::conj(r01)).real());
+        total += w[i];
+    }
+    if (!(total > 0.0)) return fail(QVM_EARG, "every Kraus branch has zero weight");
+    int j = 0;
+    for (double acc = w[0]; j < n_ops - 1 && !(acc > u * total); acc += w[++j]) {}
+    while (w[j] == 0.0 && j > 0) --j;                 // rounding at the top end
+    const double f = std::sqrt(total / w[j]);        // keeps the state's norm
+    for (int e = 0; e < 4; ++e) m[e] = f * cd(ops[8 * j + 2 * e], ops[8 * j + 2 * e + 1]);
+    *branch = j;
+    if (probs)
+        for (int i = 0; i < n_ops; ++i) probs[i] = w[i] / total;
+    return QVM_OK;
+}
+
 LOp lower(const qvm_sv* sv, const qvm_gate& g, const std::vector<cd>& u) {
     int pt[QVM_MAX_K];
     for (int r = 0; r < g.k; ++r) pt[r] = sv->perm[g.targets[r]];
@@ -411,25 +436,10 @@ qvm_status qvm_apply_kraus(qvm_sv* sv, int32_t qubit, int32_t n_ops, const doubl
     double r[4];
     qvm_status st = rd_rdm1(sv, sv->perm[qubit], r);
     if (st) return st;
-    const cd r01(r[2], r[3]);
-    // p_i = ||K_i psi||^2 = Tr(K_i^dag K_i rho)
-    double w[QVM_MAX_KRAUS], total = 0;
-    for (int i = 0; i < n_ops; ++i) {
-        const double* k = ops + 8 * i;
-        const cd a(k[0], k[1]), b(k[2], k[3]), c(k[4], k[5]), d(k[6], k[7]);
-        const double m00 = std::norm(a) + std::norm(c), m11 = std::norm(b) + std::norm(d);
-        const cd m01 = std::conj(a) * b + std::conj(c) * d;          // (K^dag K)_{01}
-        // Tr(M rho) = m00 r00 + m11 r11 + 2 Re(m01 conj(r01))
-        w[i] = std::max(0.0, m00 * r[0] + m11 * r[1] + 2.0 * (m01 * std::conj(r01)).real());
-        total += w[i];
-    }
-    if (!(total > 0.0)) return fail(QVM_EARG, "every Kraus branch has zero weight");
     int j = 0;
-    for (double acc = w[0]; j < n_ops - 1 && !(acc > u * total); acc += w[++j]) {}
-    while (w[j] == 0.0 && j > 0) --j;                 // rounding at the top end
-    const double f = std::sqrt(total / w[j]);        // keeps the state's norm
     std::vector<cd> m(4);
-    for (int e = 0; e < 4; ++e) m[e] = f * cd(ops[8 * j + 2 * e], ops[8 * j + 2 * e + 1]);
+    st = choose_branch(r, n_ops, ops, u, &j, m.data(), probs);
+    if (st) return st;
     qvm_gate g{};
     g.kind = QVM_G_MATRIX;
     g.k = 1;
@@ -437,9 +447,42 @@ qvm_status qvm_apply_kraus(qvm_sv* sv, int32_t qubit, int32_t n_ops, const doubl
     st = launch_op(sv, lower(sv, g, m));
     if (st) return st;
     if (chosen) *chosen = j;
-    if (probs)
-        for (int i = 0; i < n_ops; ++i) probs[i] = w[i] / total;
     return QVM_OK;
+}
+
+qvm_status qvm_run_trajectory(qvm_sv* sv, const qvm_gate* gates, size_t n_gates, const size_t* first,
+                              const int32_t* qubit, const int32_t* channel, size_t n_channels,
+                              const int32_t* n_ops, const double* ops, const double* uniforms,
+                              int32_t* branches) {
+    QVM_CHECK_SV(sv);
+    if (n_gates && (!gates || !first)) return fail(QVM_EARG, "NULL gate list");
+    for (size_t i = 0; i < n_gates; ++i) {
+        qvm_status st = validate_gate(gates[i], sv->n, false);
+        if (st) return fail(st, "gate " + std::to_string(i) + ": " + g_err);
+        if (first[i] > first[i + 1]) return fail(QVM_EARG, "branching ranges out of order");
+    }
+    const size_t nb = n_gates ? first[n_gates] : 0;
+    if (n_gates && first[0] != 0) return fail(QVM_EARG, "branching ranges start above 0");
+    if (nb && (!qubit || !channel || !n_ops || !ops || !uniforms || !branches))
+        return fail(QVM_EARG, "NULL argument");
+    try {
+        std::vector<Channel> chans;
+        for (size_t c = 0; c < n_channels && nb; ++c) {
+            if (n_ops[c] < 1 || n_ops[c] > QVM_MAX_KRAUS) return fail(QVM_EARG, "n_ops outside 1..16");
+            chans.push_back(Channel{n_ops[c], ops});
+            ops += 8 * (size_t)n_ops[c];
+        }
+        std::vector<Branching> br(nb);
+        for (size_t q = 0; q < nb; ++q) {
+            if (qubit[q] < 0 || qubit[q] >= sv->n) return fail(QVM_ERANGE, "qubit >= n");
+            if (channel[q] < 0 || (size_t)channel[q] >= n_channels) return fail(QVM_EARG, "channel index out of range");
+            if (!(uniforms[q] >= 0.0 && uniforms[q] < 1.0)) return fail(QVM_EARG, "u outside [0, 1)");
+            br[q] = Branching{qubit[q], channel[q]};
+        }
+        return run_trajectory(sv, gates, n_gates, br.data(), first, chans, uniforms, branches);
+    } catch (const std::bad_alloc&) {
+        return fail(QVM_ENOMEM, "host allocation failed");
+    }
 }
 
 qvm_status qvm_run(qvm_sv* sv, const qvm_gate* gates, size_t n_gates) {

@@ -109,6 +109,16 @@ struct PassArgs {
     uint32_t top[kSlots];   // positions of the four highest tile bits (a thread's pieces), ascending
 };
 
+// A pass that also measures: the reduced density matrix of four tile bits
+// (k_gate_pass with RDM), after the pass's gates.
+struct RdmArgs {
+    uint32_t ntiles;        // the workgroups loop over the tiles: one partial each
+    uint32_t store;         // 0: no gates ran, the tile is as it was
+    uint32_t slot[kSlots];  // LDS byte addresses of the measured bits, ascending
+    uint32_t col[9];        // LDS byte addresses of the other tile bits, ascending
+    uint32_t pad;
+};
+
 constexpr uint32_t kPutWords = 4000;              // 16,000 bytes of records per k_put launch
 struct PutArgs {
     uint32_t* dst;
@@ -331,9 +341,45 @@ __device__ __forceinline__ void apply_op(T (&a)[NA], const OpHead& h, const Rec<
 // round is the tile element with t spread around the RS slots.  LDS addresses
 // use the tile kernel's swizzle: linear over GF(2), so register j's address
 // is the thread's XOR a uniform word, and four lane bits rarely collide.
-template <typename R, int RS>
+typedef double D4 __attribute__((ext_vector_type(4)));
+constexpr uint32_t kRdmVals = 512;               // values of a partial: 8 per lane
+constexpr uint32_t kRdmBlocks = 512;             // workgroups of a measuring pass, at most: two per CU (2,048: 15.2 against 14.2 ms a run below)
+
+// rho_ij = sum over the tile's columns of psi_i conj(psi_j), i and j over the
+// 16 values of the measured bits: a product of the 16 x 2^(L-4) matrix of
+// the tile's amplitudes with its adjoint, on FP64 MFMA 16x16x4.  Lane l reads
+// amplitude l % 16 of column l / 16 of four; the same registers are both
+// operands: re re + im im is rho's real part, im re minus its transpose the
+// imaginary part (the host subtracts).  Three instructions per 64
+// amplitudes: about half the time their traffic takes.
+template <typename R>
+__device__ __forceinline__ void rdm_tile(D4& rr, D4& ri, const RdmArgs& M, uint32_t L) {
+    using V2 = typename Vec2<R>::V;
+    const uint32_t lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t ncol = 1u << (L - kSlots);
+    uint32_t at = 0;                                           // the lane's amplitude and column of four
+#pragma unroll
+    for (int b = 0; b < kSlots; ++b) at ^= ((lane >> b) & 1) ? M.slot[b] : 0u;
+    at ^= ((lane >> 4) & 1) ? M.col[0] : 0u;
+    at ^= ((lane >> 5) & 1) ? M.col[1] : 0u;
+    for (uint32_t c = 4 * wv; c < ncol; c += 4 * nw) {
+        uint32_t u = 0;
+#pragma unroll
+        for (int b = 2; b < 9; ++b) u ^= ((c >> b) & 1) ? M.col[b] : 0u;
+        V2 v = {0, 0};
+        if (c + (lane >> 4) < ncol) v = gld<V2>(at ^ u);
+        const double x = v[0], y = v[1];
+        rr = __builtin_amdgcn_mfma_f64_16x16x4f64(x, x, rr, 0, 0, 0);
+        rr = __builtin_amdgcn_mfma_f64_16x16x4f64(y, y, rr, 0, 0, 0);
+        ri = __builtin_amdgcn_mfma_f64_16x16x4f64(y, x, ri, 0, 0, 0);
+    }
+}
+
+template <typename R, int RS, bool RDM>
 __global__ __launch_bounds__(RS == 4 && sizeof(R) == 8 ? 256 : 512, RS == 4 && sizeof(R) == 8 ? 2 : 4) void k_gate_pass(
-    typename GT<R>::T* __restrict__ psi, PassArgs A, const uint32_t* __restrict__ table) {
+    typename GT<R>::T* __restrict__ psi, PassArgs A, const uint32_t* __restrict__ table, RdmArgs M,
+    double* __restrict__ part) {
     using T = typename GT<R>::T;
     using V16 = typename GT<R>::V16;
     using V2 = typename Vec2<R>::V;
@@ -342,10 +388,12 @@ __global__ __launch_bounds__(RS == 4 && sizeof(R) == 8 ? 256 : 512, RS == 4 && s
     constexpr int NIT = kAmps / EP;                            // 16-byte pieces per thread
     constexpr uint32_t ES = sizeof(T);
     const uint32_t nt = 1u << (A.L - RS);                  // working threads
-    const uint32_t tid = threadIdx.x, w = blockIdx.x;
+    const uint32_t tid = threadIdx.x;
     const bool live = tid < nt;
-    const uint64_t base = place(w, ~A.qmask);
     T a[kAmps];
+    D4 rr = {0, 0, 0, 0}, ri = {0, 0, 0, 0};                   // RDM: sums of the workgroup's tiles
+    for (uint32_t w = blockIdx.x;;) {
+    const uint64_t base = place(w, ~A.qmask);
     // stream in: pieces tid + nt i of the tile, all in flight, then to LDS.
     // The index's high bits i are the tile's highest bits: a piece's offset
     // and LDS slot are the thread's plus (XOR) those of the bits set in i.
@@ -439,7 +487,8 @@ __global__ __launch_bounds__(RS == 4 && sizeof(R) == 8 ? 256 : 512, RS == 4 && s
         }
         if (!(last && (A.direct & 2))) __syncthreads();
     }
-    if (!(A.direct & 2) && live) {
+    if constexpr (RDM) rdm_tile<R>(rr, ri, M, A.L);
+    if (!(A.direct & 2) && live && (!RDM || M.store)) {
         const uint64_t g0 = base + place(EP * tid, A.qmask);
         const uint32_t s0 = tile_swizzle(EP * tid);
 #pragma unroll
@@ -454,6 +503,43 @@ __global__ __launch_bounds__(RS == 4 && sizeof(R) == 8 ? 256 : 512, RS == 4 && s
             }
             __builtin_nontemporal_store(x, (V16*)(psi + g0 + subset<PB>(gtop, i)));
         }
+    }
+    if constexpr (!RDM) break;
+    w += gridDim.x;
+    if (w >= M.ntiles) break;
+    __syncthreads();                                           // the tile has been read: the next may come in
+    }
+    if constexpr (RDM) {
+        // the waves' sums through LDS, in order
+        __syncthreads();
+        const uint32_t lane = tid & 63, wv = tid >> 6;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            gst<double>(8 * (512 * wv + 64 * q + lane), rr[q]);
+            gst<double>(8 * (512 * wv + 64 * (q + 4) + lane), ri[q]);
+        }
+        __syncthreads();
+        for (uint32_t e = tid; e < kRdmVals; e += blockDim.x) {
+            double s = 0;
+            for (uint32_t v = 0; v < blockDim.x / 64; ++v) s += gld<double>(8 * (512 * v + e));
+            part[(size_t)blockIdx.x * kRdmVals + e] = s;
+        }
+    }
+}
+
+// The partials of nb workgroups, in order: 16 values per block.
+__global__ __launch_bounds__(256) void k_rdm_final(const double* __restrict__ part, uint32_t nb,
+                                                   double* __restrict__ out) {
+    __shared__ double sh[16][17];
+    const uint32_t v = threadIdx.x & 15, g = threadIdx.x >> 4;
+    double s = 0;
+    for (uint32_t b = g; b < nb; b += 16) s += part[(size_t)b * kRdmVals + 16 * blockIdx.x + v];
+    sh[g][v] = s;
+    __syncthreads();
+    if (g == 0) {
+        double r = 0;
+        for (int i = 0; i < 16; ++i) r += sh[i][v];
+        out[16 * blockIdx.x + v] = r;
     }
 }
 
@@ -627,9 +713,9 @@ struct Emit {
 // holds one of its bits (two gates that both act diagonally on the bits
 // they share commute) or when its bits do not fit in the tile.
 uint64_t take_pass(const std::vector<GGate>& G, const std::vector<char>& done, size_t first, int n, int L, int c,
-                   std::vector<int>& ops) {
+                   uint64_t need, std::vector<int>& ops) {
     const uint64_t all = n >= 64 ? ~0ull : (1ull << n) - 1;
-    uint64_t T = (1ull << std::min(c, n)) - 1;
+    uint64_t T = ((1ull << std::min(c, n)) - 1) | need;
     if (L >= n) T = all;
     Sched s;
     ops.clear();
@@ -647,34 +733,172 @@ uint64_t take_pass(const std::vector<GGate>& G, const std::vector<char>& done, s
     return T;
 }
 
+// Records of the passes of one call: in the workspace's plan area, in stream
+// order (when it is full, the next pass's records go to its start: the passes
+// before have run by then).
+struct PassBuf {
+    uint32_t* dev;
+    size_t cap, used = 0;
+    explicit PassBuf(qvm_sv* sv)
+        : dev((uint32_t*)(sv->work + sv->lay.plan_off)), cap(sv->lay.plan_bytes / 4) {}
+};
+
+// One pass over tiles of the bits in qmask: the gates ops of G in order, then,
+// if asked, the reduced density matrix of the bits in measure (to rho_part:
+// its workgroups' partials; *blocks: how many).
 template <typename R>
-qvm_status run_segment(qvm_sv* sv, const std::vector<GGate>& G) {
+qvm_status launch_pass(qvm_sv* sv, PassBuf& buf, const std::vector<GGate>& G, const std::vector<int>& ops,
+                       uint64_t qmask, int rs, uint64_t measure = 0, double* rho_part = nullptr,
+                       uint32_t* blocks = nullptr) {
     using T = typename GT<R>::T;
-    const int n = sv->n, c = GT<R>::C;
-    const double S = (double)(1ull << n) * sizeof(T);
-    // Below 21 qubits a pass has few tiles, and the time of one wave through
-    // its gates counts: 8 amplitudes a thread instead of 16, and tiles that
-    // give 16 to 128 workgroups, as far as the passes that smaller tiles
-    // need (each two launches) pay (measured, microseconds: 12-qubit layered
-    // circuit of 175 gates, complex128, in one 12-qubit tile 102 against 109
-    // with 16 amplitudes; 17 qubits, 200 mixed gates, complex64, tiles of
-    // 2^10 / 2^11 / 2^12 172 / 168 / 171, 2^13 with 16 amplitudes 216; 20
-    // qubits 2^12 with 8 amplitudes 180, 2^13 with 16 225).  From 21 qubits
-    // on the chip is full and the fewest passes win (23 qubits: 572 against
-    // 630).
-    const int Lmax = n <= 12 ? 12 : n <= 16 ? 10 : n <= 19 ? 11 : n <= 20 ? 12 : GT<R>::LMAX;
-    const int rs = n <= 20 ? 3 : 4;
-    std::vector<char> done(G.size(), 0);
-    std::vector<int> ops, left, next;
+    const int n = sv->n, L = pc(qmask);
+    PassArgs A{};
+    A.qmask = qmask;
+    A.L = (uint32_t)L;
+    {
+        int k = kSlots;
+        for (int b = n - 1; k > 0; --b)
+            if ((qmask >> b) & 1) A.top[--k] = (uint32_t)b;
+    }
     std::vector<uint32_t> tab;
+    std::vector<int> left = ops, next, now;
+    double flops = 0;
+    std::vector<uint64_t> round_slots;
+    while (!left.empty()) {
+        Sched s;
+        uint64_t sm = 0;
+        next.clear();
+        now.clear();
+        for (size_t q = 0; q < left.size(); ++q) {
+            const GGate& g = G[left[q]];
+            if ((s.bx & qmask) != qmask && s.free(g) && pc(sm | g.xq) <= rs) {
+                sm |= g.xq;
+                now.push_back(left[q]);
+            } else {
+                s.hold(g);
+                next.push_back(left[q]);
+            }
+        }
+        for (int b = n - 1; b >= 0 && pc(sm) < rs; --b)         // free slots: the highest tile bits
+            if ((qmask >> b) & 1) sm |= 1ull << b;
+        const size_t at = tab.size();
+        tab.resize(at + RND_WORDS);
+        Emit<R> E{tab, qmask, sm, rs, {}};
+        {
+            int k = 0;
+            for (uint64_t m = sm; m; m &= m - 1) E.slot_phys[k++] = m & (~m + 1);
+        }
+        uint32_t nops = 0;
+        for (int i : now) {
+            nops += (uint32_t)E.gate(G[i]);
+            const LOp& o = G[i].op;
+            const double touched = G[i].frac * (double)(1ull << n);
+            flops += o.cls == OP_DENSE ? touched * 8.0 * (1 << o.k) : o.cls == OP_SWAPPAIR ? 0.0 : 6.0 * touched;
+        }
+        RoundHead rh{};
+        for (int k = 0; k < rs; ++k) {
+            rh.bit[k] = local_bits(E.slot_phys[k], qmask);
+            rh.lds[k] = tile_swizzle(rh.bit[k]) * (uint32_t)sizeof(T);
+            rh.phys[k] = (uint32_t)__builtin_ctzll(E.slot_phys[k]);
+        }
+        rh.nops = nops;
+        memcpy(&tab[at], &rh, sizeof(rh));
+        round_slots.push_back(sm);
+        ++A.nrounds;
+        left.swap(next);
+    }
+    const uint64_t low = (1ull << std::min<int>(GT<R>::C, n)) - 1;
+    if (A.nrounds) {
+        if (!(round_slots.front() & low)) A.direct |= 1;
+        if (!measure && !(round_slots.back() & low)) A.direct |= 2;
+    }
+    tab.resize((tab.size() + 31) & ~size_t(31));
+    if (buf.used + tab.size() + 64 > buf.cap) buf.used = 0;
+    if (tab.size() + 64 > buf.cap) return fail(QVM_ENOMEM, "gate pass records exceed the workspace plan area");
+    A.words = (uint32_t)buf.used;
+    qvm_status st = put_words(sv, buf.dev + buf.used, tab.data(), tab.size());
+    if (st) return st;
+    buf.used += tab.size();
+    const unsigned threads = std::max(64u, 1u << (L - rs));
+    size_t lds = A.direct == 3 && A.nrounds == 1 ? 0 : sizeof(T) << L;
+    unsigned grid = 1u << (n - L);
+    RdmArgs M{};
+    if (measure) {
+        M.ntiles = grid;
+        M.store = A.nrounds ? 1 : 0;
+        int ks = 0, kc = 0;
+        for (int b = 0; b < L; ++b) {
+            uint64_t m = qmask;                                 // the b-th lowest tile bit
+            for (int i = 0; i < b; ++i) m &= m - 1;
+            const uint32_t at = tile_swizzle(1u << b) * (uint32_t)sizeof(T);
+            if (measure & m & (~m + 1)) M.slot[ks++] = at;
+            else M.col[kc++] = at;
+        }
+        grid = std::min(grid, kRdmBlocks);
+        *blocks = grid;
+        lds = std::max(lds, (size_t)(threads / 64) * kRdmVals * sizeof(double));
+    }
+    const int tok = prof_begin(sv);
+    T* amps = (T*)sv->amps;
+    if (measure) {
+        if (rs == 3)
+            hipLaunchKernelGGL((k_gate_pass<R, 3, true>), dim3(grid), dim3(threads), lds, sv->stream, amps, A, buf.dev,
+                               M, rho_part);
+        else
+            hipLaunchKernelGGL((k_gate_pass<R, 4, true>), dim3(grid), dim3(threads), lds, sv->stream, amps, A, buf.dev,
+                               M, rho_part);
+    } else {
+        if (rs == 3)
+            hipLaunchKernelGGL((k_gate_pass<R, 3, false>), dim3(grid), dim3(threads), lds, sv->stream, amps, A,
+                               buf.dev, M, rho_part);
+        else
+            hipLaunchKernelGGL((k_gate_pass<R, 4, false>), dim3(grid), dim3(threads), lds, sv->stream, amps, A,
+                               buf.dev, M, rho_part);
+    }
+    QVM_LAUNCH_CHECK(sv);
+    const double S = (double)(1ull << n) * sizeof(T);
+    prof_end(sv, tok, measure ? PK_RDM1 : PK_GATES, M.store || !measure ? 2.0 * S : S, flops);
+    return QVM_OK;
+}
+
+// Amplitudes per thread (as a power of two) and widest tile of a pass.
+//
+// Below 21 qubits a pass has few tiles, and the time of one wave through its
+// gates counts: 8 amplitudes a thread instead of 16, and tiles that give 16
+// to 128 workgroups, as far as the passes that smaller tiles need (each two
+// launches) pay (measured, microseconds: 12-qubit layered circuit of 175
+// gates, complex128, in one 12-qubit tile 102 against 109 with 16
+// amplitudes; 17 qubits, 200 mixed gates, complex64, tiles of 2^10 / 2^11 /
+// 2^12 172 / 168 / 171, 2^13 with 16 amplitudes 216; 20 qubits 2^12 with 8
+// amplitudes 180, 2^13 with 16 225).  From 21 qubits on the chip is full and
+// the fewest passes win (23 qubits: 572 against 630).
+int pass_slots(int n) { return n <= 20 ? 3 : 4; }
+template <typename R> int pass_width(int n) {
+    return std::min(n, n <= 12 ? 12 : n <= 16 ? 10 : n <= 19 ? 11 : n <= 20 ? 12 : GT<R>::LMAX);
+}
+
+// Passes over the gates of G in order until none is left, or, with bits to
+// measure, until one pass whose tile holds those bits takes all that are
+// left and measures.
+template <typename R>
+qvm_status run_segment(qvm_sv* sv, const std::vector<GGate>& G, uint64_t measure = 0, double* rho_part = nullptr,
+                       uint32_t* blocks = nullptr) {
+    using T = typename GT<R>::T;
+    const int n = sv->n, c = GT<R>::C, rs = pass_slots(n);
+    const double S = (double)(1ull << n) * sizeof(T);
+    PassBuf buf(sv);
+    std::vector<char> done(G.size(), 0);
+    std::vector<int> ops;
     size_t remaining = G.size(), first = 0;
-    uint32_t* dtab = (uint32_t*)(sv->work + sv->lay.plan_off);
-    const size_t cap = sv->lay.plan_bytes / 4;
-    size_t used = 0;
-    while (remaining) {
-        while (done[first]) ++first;
-        const int L = std::min(n, Lmax);
-        const uint64_t qmask = take_pass(G, done, first, n, L, c, ops);
+    while (remaining || measure) {
+        while (first < G.size() && done[first]) ++first;
+        if (measure) {
+            // (the tile holds the low bits, the measured ones and four more)
+            const int L = std::min(n, n <= 20 ? 12 : GT<R>::LMAX);
+            const uint64_t qmask = take_pass(G, done, first, n, L, c, measure, ops);
+            if (ops.size() == remaining) return launch_pass<R>(sv, buf, G, ops, qmask, rs, measure, rho_part, blocks);
+        }
+        const uint64_t qmask = take_pass(G, done, first, n, pass_width<R>(n), c, 0, ops);
         // one gate's kernel costs a launch (3 us) and its share of the
         // state's traffic (5.5 TB/s), a pass two launches and all of the
         // traffic (5 TB/s): a few phases or moves on large states, and one
@@ -684,92 +908,126 @@ qvm_status run_segment(qvm_sv* sv, const std::vector<GGate>& G) {
         const bool pass = ops.size() > 1 && each > 8e-6 + 2.0 * S / 5.0e12;
         for (int i : ops) done[i] = 1;
         remaining -= ops.size();
-        if (!pass) {
-            for (int i : ops) {
-                qvm_status st = launch_op(sv, G[i].op);
-                if (st) return st;
-            }
+        if (pass) {
+            qvm_status st = launch_pass<R>(sv, buf, G, ops, qmask, rs);
+            if (st) return st;
             continue;
         }
-        // rounds
-        PassArgs A{};
-        A.qmask = qmask;
-        A.L = (uint32_t)L;
-        {
-            int k = kSlots;
-            for (int b = n - 1; k > 0; --b)
-                if ((qmask >> b) & 1) A.top[--k] = (uint32_t)b;
+        for (int i : ops) {
+            qvm_status st = launch_op(sv, G[i].op);
+            if (st) return st;
         }
-        tab.clear();
-        left = ops;
-        double flops = 0;
-        std::vector<uint64_t> round_slots;
-        while (!left.empty()) {
-            Sched s;
-            uint64_t sm = 0;
-            next.clear();
-            std::vector<int> now;
-            for (size_t q = 0; q < left.size(); ++q) {
-                const GGate& g = G[left[q]];
-                if ((s.bx & qmask) != qmask && s.free(g) && pc(sm | g.xq) <= rs) {
-                    sm |= g.xq;
-                    now.push_back(left[q]);
-                } else {
-                    s.hold(g);
-                    next.push_back(left[q]);
-                }
-            }
-            for (int b = n - 1; b >= 0 && pc(sm) < rs; --b)     // free slots: the highest tile bits
-                if ((qmask >> b) & 1) sm |= 1ull << b;
-            const size_t at = tab.size();
-            tab.resize(at + RND_WORDS);
-            Emit<R> E{tab, qmask, sm, rs, {}};
-            {
-                int k = 0;
-                for (uint64_t m = sm; m; m &= m - 1) E.slot_phys[k++] = m & (~m + 1);
-            }
-            uint32_t nops = 0;
-            for (int i : now) {
-                nops += (uint32_t)E.gate(G[i]);
-                const LOp& o = G[i].op;
-                const double touched = G[i].frac * (double)(1ull << n);
-                flops += o.cls == OP_DENSE ? touched * 8.0 * (1 << o.k) : o.cls == OP_SWAPPAIR ? 0.0 : 6.0 * touched;
-            }
-            RoundHead rh{};
-            for (int k = 0; k < rs; ++k) {
-                rh.bit[k] = local_bits(E.slot_phys[k], qmask);
-                rh.lds[k] = tile_swizzle(rh.bit[k]) * (uint32_t)sizeof(T);
-                rh.phys[k] = (uint32_t)__builtin_ctzll(E.slot_phys[k]);
-            }
-            rh.nops = nops;
-            memcpy(&tab[at], &rh, sizeof(rh));
-            round_slots.push_back(sm);
-            ++A.nrounds;
-            left.swap(next);
-        }
-        const uint64_t low = (1ull << std::min(c, n)) - 1;
-        if (!(round_slots.front() & low)) A.direct |= 1;
-        if (!(round_slots.back() & low)) A.direct |= 2;
-        tab.resize((tab.size() + 31) & ~size_t(31));
-        if (used + tab.size() + 64 > cap) used = 0;             // in stream order: the passes before have run
-        if (tab.size() + 64 > cap) return fail(QVM_ENOMEM, "gate pass records exceed the workspace plan area");
-        A.words = (uint32_t)used;
-        qvm_status st = put_words(sv, dtab + used, tab.data(), tab.size());
-        if (st) return st;
-        used += tab.size();
-        const unsigned threads = std::max(64u, 1u << (L - rs));
-        const size_t lds = A.direct == 3 && A.nrounds == 1 ? 0 : sizeof(T) << L;
-        const int tok = prof_begin(sv);
-        if (rs == 3)
-            hipLaunchKernelGGL((k_gate_pass<R, 3>), dim3(1u << (n - L)), dim3(threads), lds, sv->stream, (T*)sv->amps,
-                               A, dtab);
-        else
-            hipLaunchKernelGGL((k_gate_pass<R, 4>), dim3(1u << (n - L)), dim3(threads), lds, sv->stream, (T*)sv->amps,
-                               A, dtab);
-        QVM_LAUNCH_CHECK(sv);
-        prof_end(sv, tok, PK_GATES, 2.0 * S, flops);
     }
     return QVM_OK;
+}
+
+// A gate list under construction: runs of uncontrolled one-target gates on a
+// bit become one gate (their product, in double precision).
+class ListBuilder {
+  public:
+    ListBuilder() { std::fill(open_, open_ + QVM_MAX_QUBITS, -1); }
+    void one(int bit, const cd* m) {
+        if (open_[bit] < 0) {
+            open_[bit] = (int)items_.size();
+            Item it{};
+            it.bit = bit;
+            std::copy(m, m + 4, it.m);
+            items_.push_back(std::move(it));
+            return;
+        }
+        cd* r = items_[open_[bit]].m;
+        cd p[4];
+        for (int a = 0; a < 2; ++a)
+            for (int b = 0; b < 2; ++b) {
+                const cd x = m[2 * a], y = r[b], z = m[2 * a + 1], v = r[2 + b];
+                p[2 * a + b] =
+                    cd(x.real() * y.real() - x.imag() * y.imag() + z.real() * v.real() - z.imag() * v.imag(),
+                       x.real() * y.imag() + x.imag() * y.real() + z.real() * v.imag() + z.imag() * v.real());
+            }
+        std::copy(p, p + 4, r);
+    }
+    void any(LOp op, uint64_t bits) {
+        for (uint64_t m = bits; m; m &= m - 1) open_[__builtin_ctzll(m)] = -1;
+        Item it{};
+        it.bit = -1;
+        it.op = std::move(op);
+        items_.push_back(std::move(it));
+    }
+    size_t size() const { return items_.size(); }
+    std::vector<GGate> finish() {
+        std::vector<GGate> G;
+        G.reserve(items_.size());
+        std::vector<cd> u;
+        for (Item& it : items_) {
+            if (it.bit >= 0) {
+                u.assign(it.m, it.m + 4);
+                it.op = classify(1, &it.bit, 0, u);
+            }
+            if (it.op.cls == OP_PHASE && it.op.phase == cd(1.0, 0.0)) continue;      // identity
+            G.push_back(placed(std::move(it.op)));
+        }
+        return G;
+    }
+
+  private:
+    struct Item {
+        int bit;                                 // >= 0: a run of one-target gates with product m
+        cd m[4];
+        LOp op;
+    };
+    static GGate placed(LOp op) {
+        GGate g{std::move(op), 0, 0, 0};
+        const LOp& o = g.op;
+        uint64_t tm = 0;
+        for (int r = 0; r < o.k; ++r) tm |= 1ull << o.t[r];
+        switch (o.cls) {
+            case OP_PHASE:
+                g.zq = o.cond_mask;
+                g.frac = std::ldexp(1.0, -pc(o.cond_mask));
+                break;
+            case OP_DIAG:
+                g.zq = o.cmask | tm;
+                g.frac = std::ldexp(1.0, -pc(o.cmask));
+                break;
+            case OP_SWAPPAIR:
+                g.xq = o.xmask;
+                g.zq = o.cond_mask & ~o.xmask;
+                g.frac = std::ldexp(2.0, -pc(o.cond_mask | o.hbit));
+                break;
+            default:
+                g.xq = tm;
+                g.zq = o.cmask;
+                g.frac = std::ldexp(1.0, -pc(o.cmask));
+        }
+        return g;
+    }
+    std::vector<Item> items_;
+    int open_[QVM_MAX_QUBITS];
+};
+
+// Lowers one validated gate into the list; returns the physical bits it touches.
+qvm_status add_gate(qvm_sv* sv, ListBuilder& B, const qvm_gate& g, std::vector<cd>& u) {
+    qvm_status st = gate_matrix(g, u);
+    if (st) return st;
+    if (g.k == 1 && g.ctrl_mask == 0) {
+        B.one(sv->perm[g.targets[0]], u.data());
+        return QVM_OK;
+    }
+    uint64_t bits = phys_mask(sv, g.ctrl_mask);
+    for (int r = 0; r < g.k; ++r) bits |= 1ull << sv->perm[g.targets[r]];
+    B.any(lower(sv, g, u), bits);
+    return QVM_OK;
+}
+
+qvm_status run_list(qvm_sv* sv, const std::vector<GGate>& G) {
+    if (sv->n < kSlots || G.size() < 2) {
+        for (const GGate& g : G) {
+            const qvm_status st = launch_op(sv, g.op);
+            if (st) return st;
+        }
+        return QVM_OK;
+    }
+    return sv->dt == QVM_C64 ? run_segment<float>(sv, G) : run_segment<double>(sv, G);
 }
 
 }  // namespace
@@ -793,99 +1051,235 @@ constexpr size_t kSegment = 4096;
 
 qvm_status run_gates(qvm_sv* sv, const qvm_gate* gates, size_t n_gates) {
     std::vector<cd> u;
-    std::vector<GGate> G;
-    auto push = [&](const LOp& op) {
-        GGate g{op, 0, 0, 0};
-        uint64_t tm = 0;
-        for (int r = 0; r < op.k; ++r) tm |= 1ull << op.t[r];
-        switch (op.cls) {
-            case OP_PHASE:
-                g.zq = op.cond_mask;
-                g.frac = std::ldexp(1.0, -pc(op.cond_mask));
-                break;
-            case OP_DIAG:
-                g.zq = op.cmask | tm;
-                g.frac = std::ldexp(1.0, -pc(op.cmask));
-                break;
-            case OP_SWAPPAIR:
-                g.xq = op.xmask;
-                g.zq = op.cond_mask & ~op.xmask;
-                g.frac = std::ldexp(2.0, -pc(op.cond_mask | op.hbit));
-                break;
-            default:
-                g.xq = tm;
-                g.zq = op.cmask;
-                g.frac = std::ldexp(1.0, -pc(op.cmask));
-        }
-        G.push_back(std::move(g));
-    };
     for (size_t s0 = 0; s0 < n_gates; s0 += kSegment) {
-        const size_t s1 = std::min(n_gates, s0 + kSegment);
-        G.clear();
-        // runs of uncontrolled one-target gates on a qubit become one gate
-        // (their product, in double precision)
-        struct Run { cd m[4]; };
-        std::vector<Run> runs;
-        std::vector<int> run_of;                 // per entry of order: run index, or -1 - gate index
-        int open[QVM_MAX_QUBITS];
-        std::fill(open, open + QVM_MAX_QUBITS, -1);
-        std::vector<int> run_t;
-        for (size_t i = s0; i < s1; ++i) {
-            const qvm_gate& g = gates[i];
-            if (g.k == 1 && g.ctrl_mask == 0) {
-                qvm_status st = gate_matrix(g, u);
-                if (st) return st;
-                const int t = sv->perm[g.targets[0]];
-                if (open[t] >= 0) {
-                    Run& r = runs[open[t]];
-                    cd p[4];
-                    for (int a = 0; a < 2; ++a)
-                        for (int b = 0; b < 2; ++b) {
-                            const cd x = u[2 * a], y = r.m[b], z = u[2 * a + 1], v = r.m[2 + b];
-                            p[2 * a + b] = cd(x.real() * y.real() - x.imag() * y.imag() + z.real() * v.real() - z.imag() * v.imag(),
-                                              x.real() * y.imag() + x.imag() * y.real() + z.real() * v.imag() + z.imag() * v.real());
-                        }
-                    std::copy(p, p + 4, r.m);
-                } else {
-                    open[t] = (int)runs.size();
-                    run_of.push_back((int)runs.size());
-                    run_t.push_back(t);
-                    Run r;
-                    std::copy(u.begin(), u.begin() + 4, r.m);
-                    runs.push_back(r);
-                }
-            } else {
-                run_of.push_back(-1 - (int)(i - s0));
-                for (uint64_t m = g.ctrl_mask; m; m &= m - 1) open[sv->perm[__builtin_ctzll(m)]] = -1;
-                for (int r = 0; r < g.k; ++r) open[sv->perm[g.targets[r]]] = -1;
-            }
+        ListBuilder B;
+        for (size_t i = s0; i < std::min(n_gates, s0 + kSegment); ++i) {
+            const qvm_status st = add_gate(sv, B, gates[i], u);
+            if (st) return st;
         }
-        G.reserve(run_of.size());
-        for (int e : run_of) {
-            LOp op;
-            if (e >= 0) {
-                u.assign(runs[e].m, runs[e].m + 4);
-                op = classify(1, &run_t[e], 0, u);
-            } else {
-                const qvm_gate& g = gates[s0 + (size_t)(-1 - e)];
-                qvm_status st = gate_matrix(g, u);
-                if (st) return st;
-                op = lower(sv, g, u);
-            }
-            if (op.cls == OP_PHASE && op.phase == cd(1.0, 0.0)) continue;      // identity
-            push(op);
-        }
-        qvm_status st;
-        if (sv->n < kSlots || G.size() < 2) {
-            st = QVM_OK;
-            for (const GGate& g : G)
-                if ((st = launch_op(sv, g.op))) break;
-        } else {
-            st = sv->dt == QVM_C64 ? run_segment<float>(sv, G) : run_segment<double>(sv, G);
-        }
+        const qvm_status st = run_list(sv, B.finish());
         if (st) return st;
     }
     return QVM_OK;
+}
+
+// ============================================================ trajectories
+// A noisy run (qvm_run_trajectory).  Every branching needs its qubit's
+// density matrix at that point of the program, so one pass per branching
+// reads the whole state, a host round trip chooses, and one more pass
+// applies the chosen operator (0.42 ms per branching at 26 qubits, complex64).  But
+// the reduced density matrix of up to four qubits determines everything that
+// happens on those four until another qubit joins in: gates and chosen
+// operators act on it as on the state.  So the program is cut into groups of
+// steps that stay within four qubits; a group costs one pass, which applies
+// the previous group's gates and chosen operators and measures this group's
+// 16 x 16 matrix, and the host plays the group's branchings on that.
+//
+// 26 qubits, complex64, 262 gates, 264 branchings: 110 -> 14.2 ms in 40
+// groups, 355 us each: the pass 285 (its traffic alone 167), the partials'
+// sum 15, the copy and the host's part 50.
+//
+// Branchings keep their program order (each one's weights depend on the
+// choices before it).  Gates without a branching that share no qubit with
+// the open group do not change its matrix when they are unitary (every named
+// gate): they wait until the group ends.
+namespace {
+
+// rho <- op rho op^H for an op on the 16-dimensional register.
+struct Rho {
+    double re[16][16], im[16][16];
+    // rows: v_i <- sum_j m_ij v_j over the register positions pos (with controls cm)
+    void rows(const cd* m, int k, const int* pos, uint32_t cm) {
+        uint32_t tm = 0;
+        for (int r = 0; r < k; ++r) tm |= 1u << pos[r];
+        const int D = 1 << k;
+        for (uint32_t b = 0; b < 16; ++b) {
+            if ((b & tm) || (b & cm) != cm) continue;
+            uint32_t ix[8];
+            for (int j = 0; j < D; ++j) {
+                ix[j] = b;
+                for (int r = 0; r < k; ++r)
+                    if ((j >> r) & 1) ix[j] |= 1u << pos[r];
+            }
+            for (int c = 0; c < 16; ++c) {
+                double xr[8], xi[8];
+                for (int j = 0; j < D; ++j) {
+                    xr[j] = re[ix[j]][c];
+                    xi[j] = im[ix[j]][c];
+                }
+                for (int i = 0; i < D; ++i) {
+                    double sr = 0, si = 0;
+                    for (int j = 0; j < D; ++j) {
+                        const double a = m[i * D + j].real(), d = m[i * D + j].imag();
+                        sr += a * xr[j] - d * xi[j];
+                        si += a * xi[j] + d * xr[j];
+                    }
+                    re[ix[i]][c] = sr;
+                    im[ix[i]][c] = si;
+                }
+            }
+        }
+    }
+    void adjoint() {
+        for (int i = 0; i < 16; ++i) {
+            im[i][i] = -im[i][i];
+            for (int j = 0; j < i; ++j) {
+                std::swap(re[i][j], re[j][i]);
+                const double t = im[i][j];
+                im[i][j] = -im[j][i];
+                im[j][i] = -t;
+            }
+        }
+    }
+    void apply(const cd* m, int k, const int* pos, uint32_t cm) {
+        rows(m, k, pos, cm);
+        adjoint();
+        rows(m, k, pos, cm);
+        adjoint();
+    }
+    // one position's 2 x 2 matrix: {rho_00, rho_11, Re rho_01, Im rho_01}
+    void one(int pos, double* r) const {
+        r[0] = r[1] = r[2] = r[3] = 0;
+        for (uint32_t b = 0; b < 16; ++b) {
+            if ((b >> pos) & 1) {
+                r[1] += re[b][b];
+            } else {
+                const uint32_t d = b | 1u << pos;
+                r[0] += re[b][b];
+                r[2] += re[b][d];
+                r[3] += im[b][d];
+            }
+        }
+    }
+};
+
+template <typename R>
+qvm_status measure_t(qvm_sv* sv, const std::vector<GGate>& G, uint64_t bits, Rho& rho) {
+    // (partials and the result: the staging area)
+    double* part = (double*)(sv->work + sv->lay.io_off);
+    double* res = part + (size_t)kRdmBlocks * kRdmVals;
+    uint32_t blocks = 0;
+    qvm_status st = run_segment<R>(sv, G, bits, part, &blocks);
+    if (st) return st;
+    hipLaunchKernelGGL(k_rdm_final, dim3(kRdmVals / 16), dim3(256), 0, sv->stream, part, blocks, res);
+    QVM_LAUNCH_CHECK(sv);
+    double v[kRdmVals];
+    QVM_HIP(sv, hipMemcpyAsync(v, res, sizeof(v), hipMemcpyDeviceToHost, sv->stream));
+    QVM_HIP(sv, hipStreamSynchronize(sv->stream));
+    // register q of lane l: row l / 16 + 4 q, column l % 16
+    for (int i = 0; i < 16; ++i)
+        for (int j = 0; j < 16; ++j) {
+            auto at = [&](int row, int col) { return 64 * (row >> 2) + 16 * (row & 3) + col; };
+            rho.re[i][j] = v[at(i, j)];
+            rho.im[i][j] = v[256 + at(i, j)] - v[256 + at(j, i)];
+        }
+    return QVM_OK;
+}
+
+}  // namespace
+
+// One branching on its own: the qubit's density matrix, then the chosen
+// operator's kernel.
+static qvm_status branch_alone(qvm_sv* sv, int bit, const Channel& ch, double uniform, int32_t* branch) {
+    double r[4];
+    qvm_status st = rd_rdm1(sv, bit, r);
+    if (st) return st;
+    int j = 0;
+    std::vector<cd> m(4);
+    st = choose_branch(r, ch.n_ops, ch.ops, uniform, &j, m.data(), nullptr);
+    if (st) return st;
+    *branch = j;
+    return launch_op(sv, classify(1, &bit, 0, m));
+}
+
+qvm_status run_trajectory(qvm_sv* sv, const qvm_gate* gates, size_t n_gates, const Branching* br,
+                          const size_t* first, const std::vector<Channel>& chans, const double* uniforms,
+                          int32_t* branches) {
+    std::vector<cd> u;
+    auto bits_of = [&](size_t i) {
+        const qvm_gate& g = gates[i];
+        uint64_t b = phys_mask(sv, g.ctrl_mask);
+        for (int r = 0; r < g.k; ++r) b |= 1ull << sv->perm[g.targets[r]];
+        for (size_t q = first[i]; q < first[i + 1]; ++q) b |= 1ull << sv->perm[br[q].qubit];
+        return b;
+    };
+    std::vector<size_t> body, later;             // the group's gates, and those passed over
+    ListBuilder B;                               // what the next pass applies
+    size_t pos = 0;
+    qvm_status st = QVM_OK;
+    while (pos < n_gates) {
+        // the next group: gates without noise up to the first branching, then
+        // what stays within four qubits
+        body.clear();
+        later.clear();
+        uint64_t grp = 0, held = 0;
+        size_t i = pos;
+        for (; i < n_gates; ++i) {
+            const uint64_t b = bits_of(i);
+            const bool noisy = first[i + 1] > first[i];
+            if (!grp && !noisy) {
+                if ((st = add_gate(sv, B, gates[i], u))) return st;
+                if (B.size() >= kSegment) {
+                    if ((st = run_list(sv, B.finish()))) return st;
+                    B = ListBuilder();
+                }
+                continue;
+            }
+            if (!noisy && !(b & grp) && gates[i].kind != QVM_G_MATRIX) {
+                later.push_back(i);
+                held |= b;
+                continue;
+            }
+            if ((b & held) || pc(grp | b) > kSlots || sv->n < kSlots) break;
+            grp |= b;
+            body.push_back(i);
+        }
+        pos = i;
+        if (body.empty()) {
+            if (pos == n_gates) break;
+            // a noisy gate on more than four qubits, or fewer than four in all
+            if ((st = add_gate(sv, B, gates[pos], u)) || (st = run_list(sv, B.finish()))) return st;
+            B = ListBuilder();
+            for (size_t q = first[pos]; q < first[pos + 1]; ++q)
+                if ((st = branch_alone(sv, sv->perm[br[q].qubit], chans[br[q].channel], uniforms[q], branches + q)))
+                    return st;
+            ++pos;
+            continue;
+        }
+        uint64_t m = grp;
+        for (int q = sv->n - 1; q >= 0 && pc(m) < kSlots; --q) m |= 1ull << q;
+        Rho rho;
+        const std::vector<GGate> G = B.finish();
+        st = sv->dt == QVM_C64 ? measure_t<float>(sv, G, m, rho) : measure_t<double>(sv, G, m, rho);
+        if (st) return st;
+        B = ListBuilder();
+        auto reg = [&](int bit) { return pc(m & ((1ull << bit) - 1)); };
+        for (size_t gi : body) {
+            const qvm_gate& g = gates[gi];
+            if ((st = gate_matrix(g, u))) return st;
+            int p[3];
+            uint32_t cm = 0;
+            for (int r = 0; r < g.k; ++r) p[r] = reg(sv->perm[g.targets[r]]);
+            for (uint64_t c = phys_mask(sv, g.ctrl_mask); c; c &= c - 1) cm |= 1u << reg(__builtin_ctzll(c));
+            rho.apply(u.data(), g.k, p, cm);
+            if ((st = add_gate(sv, B, g, u))) return st;
+            for (size_t q = first[gi]; q < first[gi + 1]; ++q) {
+                const int bit = sv->perm[br[q].qubit], rp = reg(bit);
+                const Channel& ch = chans[br[q].channel];
+                double r[4];
+                rho.one(rp, r);
+                int j = 0;
+                cd k[4];
+                if ((st = choose_branch(r, ch.n_ops, ch.ops, uniforms[q], &j, k, nullptr))) return st;
+                branches[q] = j;
+                rho.apply(k, 1, &rp, 0);
+                B.one(bit, k);
+            }
+        }
+        for (size_t gi : later)
+            if ((st = add_gate(sv, B, gates[gi], u))) return st;
+    }
+    return run_list(sv, B.finish());
 }
 
 }  // namespace qvm

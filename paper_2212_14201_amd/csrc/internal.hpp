@@ -113,6 +113,22 @@ LOp classify(int k, const int* phys_t, uint64_t phys_cmask, const std::vector<cd
 qvm_status launch_op(qvm_sv* sv, const LOp& op);
 // A validated gate list, many gates per pass over the state (gatepass.hip).
 qvm_status run_gates(qvm_sv* sv, const qvm_gate* gates, size_t n_gates);
+// A noisy run by trajectories (gatepass.hip): gate i's branchings are br[first[i]
+// .. first[i + 1]), branching q draws with uniforms[q] and reports branches[q].
+struct Channel {
+    int n_ops;
+    const double* ops;                // n_ops 2x2 matrices as (re, im) doubles, row-major
+};
+struct Branching {
+    int qubit;                        // logical
+    int channel;
+};
+qvm_status run_trajectory(qvm_sv* sv, const qvm_gate* gates, size_t n_gates, const Branching* br,
+                          const size_t* first, const std::vector<Channel>& chans, const double* uniforms,
+                          int32_t* branches);
+// The branch a uniform draws from a qubit's density matrix r = {rho_00,
+// rho_11, Re rho_01, Im rho_01}, and its operator scaled to keep the norm.
+qvm_status choose_branch(const double* r, int n_ops, const double* ops, double u, int* branch, cd* m, double* probs);
 // Write words to device memory on the state's stream, carried as kernel
 // arguments (nothing on the host has to outlive the call).
 qvm_status put_words(qvm_sv* sv, uint32_t* dst, const uint32_t* src, size_t n);

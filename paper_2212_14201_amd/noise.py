@@ -2,11 +2,11 @@
 
 The paper's noise models are single-qubit Kraus operator sets with an
 adjustable error rate, attached to gate types.  One noisy run here is one
-trajectory: after every gate whose type carries a model, each qubit the gate
-touches (targets, then controls) goes through one branching of the channel
-(``StateVector.apply_kraus``: branch weights from the qubit's reduced
+trajectory (``StateVector.run_trajectory``): after every gate whose type
+carries a model, each qubit the gate touches (targets, then controls) goes
+through one branching of the channel (branch weights from the reduced
 density matrix in FP64, the branch drawn with the caller's next uniform, the
-chosen operator applied by the plain gate kernels).  Averaged over many
+chosen operator applied).  Averaged over many
 trajectories the states reproduce the channel's density matrix.
 
 Channels (the paper's equations):
@@ -88,29 +88,24 @@ class NoiseModel:
 
 
 def run_trajectory(sv, gates, model: NoiseModel, uniforms, init: int = 0):
-    """One noisy run from |init>: gates without noise go to the plain path
-    in batches; each noisy gate is followed by its branchings.  Returns the
-    chosen branch of every branching, in order."""
+    """One noisy run from |init>, in one library call: each noisy gate is
+    followed by its branchings.  Returns the chosen branch of every
+    branching, in order."""
     need = model.branchings(gates)
     u = np.asarray(uniforms, dtype=np.float64)
     if u.size < need:
         raise ValueError(f"{need} uniforms needed, {u.size} given")
     sv.init_basis(init)
-    branches = []
-    k = 0
-    batch = []
+    gates = list(gates)
+    chans, ids, first, qubit, channel = [], {}, [0], [], []
     for g in gates:
-        batch.append(g)
-        chans = model.channels_for(g)
-        if not chans:
-            continue
-        sv.run(batch)
-        batch = []
-        for ops in chans:
-            for q in tuple(g.targets) + tuple(g.controls):
-                j, _ = sv.apply_kraus(q, ops, u[k])
-                k += 1
-                branches.append(j)
-    if batch:
-        sv.run(batch)
-    return branches
+        for ops in model.channels_for(g):
+            c = ids.get(id(ops))
+            if c is None:                        # (chans keeps every ops alive while its id is used)
+                c = ids[id(ops)] = len(chans)
+                chans.append(ops)
+            qs = tuple(g.targets) + tuple(g.controls)
+            qubit += qs
+            channel += [c] * len(qs)
+        first.append(len(qubit))
+    return sv.run_trajectory(gates, first, qubit, channel, chans, u[:need])

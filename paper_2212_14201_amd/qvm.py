@@ -65,6 +65,8 @@ def _declare(L):
         "qvm_run": (st, [_vp, _gp, ctypes.c_size_t]),
         "qvm_apply_kraus": (st, [_vp, ctypes.c_int32, ctypes.c_int32, _dp, ctypes.c_double,
                                  _i32p, _dp]),
+        "qvm_run_trajectory": (st, [_vp, _gp, ctypes.c_size_t, ctypes.POINTER(ctypes.c_size_t), _i32p, _i32p,
+                                    ctypes.c_size_t, _i32p, _dp, _dp, _i32p]),
         "qvm_get_layout": (st, [_vp, _i32p]),
         "qvm_reset_layout": (st, [_vp]),
         "qvm_probabilities": (st, [_vp, ctypes.c_int, _i32p, _dp]),
@@ -335,6 +337,29 @@ class StateVector:
         check(lib().qvm_apply_kraus(self._h, int(qubit), k.shape[0], buf.ctypes.data_as(_dp),
                                     float(u), ctypes.byref(j), probs.ctypes.data_as(_dp)))
         return int(j.value), probs
+
+    def run_trajectory(self, gates, first, qubits, channels, kraus, uniforms):
+        """One noisy run (qvm_run_trajectory): gate i is followed by the
+        branchings first[i] .. first[i + 1] - 1, branching q on qubits[q] with
+        the operators kraus[channels[q]] and uniforms[q].  Returns the branch
+        of every branching."""
+        ga = gates if isinstance(gates, GateArray) else GateArray(gates)
+        ks = [np.asarray(k, dtype=np.complex128).reshape(-1, 2, 2) for k in kraus]
+        ops = np.ascontiguousarray(np.concatenate(ks) if ks else np.zeros((0, 2, 2), np.complex128))
+        n_ops = np.array([k.shape[0] for k in ks], dtype=np.int32)
+        f = np.ascontiguousarray(first, dtype=np.uintp)
+        q = np.ascontiguousarray(qubits, dtype=np.int32)
+        c = np.ascontiguousarray(channels, dtype=np.int32)
+        u = np.ascontiguousarray(uniforms, dtype=np.float64)
+        if f.size != ga.n + 1 or not q.size == c.size == u.size == int(f[-1]):
+            raise ValueError("run_trajectory: first has one entry more than the gates, and ends with the number of "
+                             "qubits, channels and uniforms")
+        out = np.zeros(q.size, dtype=np.int32)
+        check(lib().qvm_run_trajectory(self._h, ga.ptr(), ga.n, f.ctypes.data_as(ctypes.POINTER(ctypes.c_size_t)),
+                                       q.ctypes.data_as(_i32p), c.ctypes.data_as(_i32p), len(ks),
+                                       n_ops.ctypes.data_as(_i32p), ops.view(np.float64).ctypes.data_as(_dp),
+                                       u.ctypes.data_as(_dp), out.ctypes.data_as(_i32p)))
+        return out.tolist()
 
     def layout(self):
         out = np.zeros(self.n, dtype=np.int32)

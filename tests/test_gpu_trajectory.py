@@ -1,0 +1,123 @@
+"""Noisy runs in one call: groups of up to four qubits measured together,
+against the FP64 oracle's trajectories, where the grouping can go wrong: states of fewer than four
+qubits and of one tile, on both sides of the tile widths, gates passed over
+between branchings, gates that are not unitary, noise on gates of more than
+four qubits, controls named in any order, and a permuted layout."""
+import functools
+
+import numpy as np
+import pytest
+
+import oracle
+from oracle import noise as onoise
+from tests.util import C128_TOL, c64_bound, gate_ks
+from workloads import Gate, layered_u3_cz, noisy_layers, random_mixed_circuit, uniform_stream
+
+pytestmark = pytest.mark.gpu
+
+qvm = pytest.importorskip("paper_2212_14201_amd.qvm")
+noise = pytest.importorskip("paper_2212_14201_amd.noise")
+
+MODEL = [("ry", "depolarizing", {"p": 0.08}), ("cnot", "damping", {"p": 0.2}), ("cnot", "dephasing", {"p": 0.1}),
+         ("rz", "phase_damping", {"p": 0.15}), ("h", "bit_flip", {"p": 0.3}), ("toffoli", "bit_phase_flip", {"p": 0.2}),
+         ("x+5c", "damping", {"p": 0.2}), ("rzz", "depolarizing", {"p": 0.1}), ("swap", "damping", {"p": 0.1})]
+
+
+@pytest.fixture(autouse=True)
+def _gpu(require_gpu):
+    pass
+
+
+@functools.lru_cache(maxsize=None)
+def oracle_run(n):
+    """The oracle's trajectory with uniforms in the middle of the branch they
+    draw, so that no decision lies near a boundary: (uniforms, branches,
+    state, the smallest distance to a boundary)."""
+    gates = circuits(n, 500 + n)
+    model = noise.NoiseModel(MODEL)
+    rng = np.random.default_rng(900 + n)
+    psi = oracle.basis_state(n, 0)
+    us, branches, gaps = [], [], []
+    for g in gates:
+        oracle.apply_matrix(psi, n, oracle.gate_matrix(g), g.targets, g.controls)
+        for ops in model.channels_for(g):
+            for q in tuple(g.targets) + tuple(g.controls):
+                w = onoise.branch_weights(psi, n, q, ops)
+                cum = np.concatenate([[0.0], np.cumsum(w / w.sum())])
+                j = min(int(np.searchsorted(cum, rng.random(), side="right")) - 1, len(w) - 1)
+                u = 0.5 * (cum[j] + cum[j + 1])
+                psi, jj, _ = onoise.trajectory_step(psi, n, q, ops, u)
+                assert jj == j
+                us.append(u)
+                branches.append(j)
+                gaps.append(0.5 * (cum[j + 1] - cum[j]))
+    return np.array(us), branches, psi, min(gaps)
+
+
+def circuits(n, seed):
+    g = noisy_layers(n, 2 if n < 20 else 1, seed)
+    rng = np.random.default_rng(seed)
+    if n >= 3:
+        g += random_mixed_circuit(n, 30, seed, kmax=min(3, n), max_ctrl=min(2, n - 3))
+        a, b, c = (int(q) for q in rng.permutation(n)[:3])
+        g += [Gate("x", (a,), (c, b)), Gate("x", (b,), (a,)), Gate("x", (a,), (b,)),
+              # not unitary: must not be passed over
+              Gate("unitary", (c,), (), (), -1, np.array([[1.0, 0.2], [0.1, 0.7]]) + 0j), Gate("h", (a,)),
+              Gate("swap", (c, a)), Gate("ry", (c,), (), (0.4,))]
+    if n >= 8:
+        g += [Gate("x", (2,), (7, 0, 5, 1, 6)), Gate("h", (3,)), Gate("rzz", (7, 0), (), (0.3,))]
+    return g
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("n", [2, 3, 4, 5, 8, 12, 13, 21])
+def test_groups_match_the_oracle(n, dtype):
+    gates = circuits(n, 500 + n)
+    u, want_br, want, gap = oracle_run(n)
+    assert gap > 1e-3
+    sv = qvm.StateVector(n, dtype)
+    br = noise.run_trajectory(sv, gates, noise.NoiseModel(MODEL), u)
+    err = float(np.max(np.abs(sv.amplitudes() - want)))
+    tol = C128_TOL if dtype == "c128" else 2 * c64_bound(gate_ks(gates) + [1] * len(want_br))
+    print(f"n={n} {dtype} branchings={len(br)} smallest gap {gap:.1e} err {err:.1e} tol {tol:.1e}")
+    assert br == want_br
+    assert err <= tol
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+def test_trajectory_on_a_permuted_layout(dtype):
+    """The library call from a state that a fused plan left permuted, against
+    the oracle's trajectory of the whole program."""
+    n = 10
+    first, then = layered_u3_cz(n, 4, 3), noisy_layers(n, 2, 8)
+    model = [e for e in MODEL if e[0] in ("ry", "rz", "h")]
+    m = noise.NoiseModel(model)
+    u = uniform_stream(12, m.branchings(then))
+    want, wbr, margins = onoise.noisy_run(n, first + then, model, u)
+    sv = qvm.StateVector(n, dtype)
+    qvm.Plan(first, n, dtype, k_max=3, tile_qubits=7).run(sv)
+    assert np.any(sv.layout() != np.arange(n))
+    rng_first, qubit, chan, chans = [0], [], [], [e[3] for e in m.entries]
+    for g in then:
+        for c, e in enumerate(m.entries):
+            if e[0] == noise.gate_type(g):
+                qubit.append(g.targets[0])
+                chan.append(c)
+        rng_first.append(len(qubit))
+    assert min(margins) > 1e-4
+    br = sv.run_trajectory(then, rng_first, qubit, chan, chans, u)
+    assert br == wbr
+    tol = C128_TOL if dtype == "c128" else 2 * c64_bound(gate_ks(first + then) + [1] * len(br))
+    assert np.max(np.abs(sv.amplitudes() - want)) <= tol
+
+
+def test_argument_errors():
+    sv = qvm.StateVector(5, "c128")
+    g = [Gate("h", (0,))]
+    k = noise.kraus_ops("damping", p=0.5)
+    for q, c, ks, u in (([5], [0], [k], [0.5]), ([0], [1], [k], [0.5]), ([0], [0], [k], [1.0]),
+                        ([0], [0], [np.zeros((17, 2, 2))], [0.5]), ([0], [0], [np.zeros((1, 2, 2))], [0.5])):
+        with pytest.raises(qvm.QvmError):
+            sv.run_trajectory(g, [0, 1], q, c, ks, u)
+    assert sv.run_trajectory([], [0], [], [], [], []) == []
+    assert abs(sv.norm() - 1) < 1e-12
