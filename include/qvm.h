@@ -405,13 +405,19 @@ qvm_status qvm_simplify(const qvm_gate* in, size_t n_in, int n_qubits, qvm_gate*
 
 /* ------------------------------------------------------------- gradients */
 
-/* Number of gate groups qvm_adjoint_expect_grad splits a circuit into (each
- * group is one pass over the batch forward and one in reverse; up to 4
- * target qubits per group for complex64, 3 for complex128), for callers
- * that account for the passes the sweep executes.  Same gate, parameter
- * index and error rules as qvm_adjoint_expect_grad.  Host-only. */
+/* Number of gate groups of a circuit: gates applied to amplitudes a thread
+ * holds in registers (up to 4 target qubits per group for complex64, 3 for
+ * complex128).  Same gate, parameter index and error rules as
+ * qvm_adjoint_expect_grad.  Host-only. */
 qvm_status qvm_adjoint_group_count(int n_qubits, qvm_dtype dt, const qvm_gate* gates, size_t n_gates,
                                    const int32_t* param_index, int n_params, int32_t* n_groups);
+
+/* Number of passes over psi the forward sweep takes (consecutive groups share
+ * a pass while their qubits fit a tile), for callers that account for its
+ * traffic.  The reverse sweep passes over psi and lambda as often in
+ * complex128, and once per group in complex64.  Rules as above.  Host-only. */
+qvm_status qvm_adjoint_pass_count(int n_qubits, qvm_dtype dt, const qvm_gate* gates, size_t n_gates,
+                                  const int32_t* param_index, int n_params, int32_t* n_passes);
 
 /* Bytes of device workspace qvm_adjoint_expect_grad needs. */
 size_t qvm_adjoint_workspace_bytes(int n_qubits, int batch, size_t n_gates);
@@ -429,12 +435,10 @@ size_t qvm_adjoint_workspace_bytes(int n_qubits, int batch, size_t n_gates);
  * psi_dev and lam_dev each hold batch x 2^n amplitudes of dt (caller-owned,
  * distinct); work_dev at least qvm_adjoint_workspace_bytes.  Outputs on the
  * host: f_out[batch]; grad_out[batch][n_params] (NULL: expectation only).
- * All batch elements run together: the gates are split into groups that
- * target at most 4 (complex64) / 3 (complex128) qubits, and each group is
- * one launch that keeps those amplitudes of psi and lambda in registers
- * while it applies (and, in the reverse sweep, differentiates) every gate
- * of the group, so a group costs one pass over the states.  Sums in double
- * precision.  Synchronous on hip_stream. */
+ * All batch elements run together: a pass keeps tiles of the states on the
+ * chip and applies (and, in the reverse sweep, differentiates) every gate that
+ * can run on the tile's qubits.  Sums in double precision.  Synchronous on
+ * hip_stream. */
 qvm_status qvm_adjoint_expect_grad(int n_qubits, qvm_dtype dt, int batch,
                                    const qvm_gate* gates, size_t n_gates,
                                    const int32_t* param_index, int n_params,

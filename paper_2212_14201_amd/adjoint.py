@@ -26,6 +26,8 @@ def _declare():
     L.qvm_adjoint_group_count.argtypes = [ctypes.c_int, ctypes.c_int, _gp, ctypes.c_size_t, _i32p,
                                           ctypes.c_int, _i32p]
     L.qvm_adjoint_group_count.restype = ctypes.c_int
+    L.qvm_adjoint_pass_count.argtypes = L.qvm_adjoint_group_count.argtypes
+    L.qvm_adjoint_pass_count.restype = ctypes.c_int
     return L
 
 
@@ -59,12 +61,18 @@ class AdjointProblem:
                                     dtype=torch.uint8, device=self.device)
 
     def group_count(self):
-        """Gate groups of the sweep: one pass over the batch each, forward
-        and in reverse."""
+        """Gate groups of the sweep (gates applied in registers together)."""
+        return self._count(_declare().qvm_adjoint_group_count)
+
+    def pass_count(self):
+        """Passes over the batch of the forward sweep (in reverse: as many in
+        complex128, one per group in complex64)."""
+        return self._count(_declare().qvm_adjoint_pass_count)
+
+    def _count(self, fn):
         out = ctypes.c_int32()
-        check(_declare().qvm_adjoint_group_count(self.n, _dt(self.dtype), self.gates.ptr(), self.gates.n,
-                                                 self.pidx.ctypes.data_as(_i32p), self.n_params,
-                                                 ctypes.byref(out)))
+        check(fn(self.n, _dt(self.dtype), self.gates.ptr(), self.gates.n, self.pidx.ctypes.data_as(_i32p),
+                 self.n_params, ctypes.byref(out)))
         return int(out.value)
 
     def run(self, params, want_grad=True):

@@ -46,26 +46,11 @@
 #include <cstring>
 #include <vector>
 
-#include "internal.hpp"
-#include "tile.hpp"
+#include "gatepass.hpp"
 
 namespace qvm {
 
 namespace {
-
-constexpr int kSlots = 4;                        // slots of a round, at most
-
-template <typename R> struct GT;
-template <> struct GT<float> {
-    using T = float2;
-    using V16 = float __attribute__((ext_vector_type(4)));
-    static constexpr int EP = 2, C = 4, LMAX = 13;
-};
-template <> struct GT<double> {
-    using T = double2;
-    using V16 = double __attribute__((ext_vector_type(2)));
-    static constexpr int EP = 1, C = 3, LMAX = 12;
-};
 
 // Op codes.  D1 + s: dense gate on slot s; D2 + pair: on the slot pair (0,1),
 // (0,2), (0,3), (1,2), (1,3), (2,3); D3 + s: on the three slots other than s;
@@ -134,74 +119,6 @@ __global__ __launch_bounds__(256) void k_put(PutArgs a) {
     for (uint32_t i = threadIdx.x; i < a.n; i += 256) dst[i] = arg[4 + i];
 }
 
-// Bits of x placed on the set bits of mask, ascending, a run at a time.
-__device__ __forceinline__ uint64_t place(uint64_t x, uint64_t mask) {
-    uint64_t r = 0;
-    while (mask) {
-        const uint64_t low = mask & (~mask + 1);
-        const uint64_t run = ((mask + low) & ~mask) - low;       // the lowest run of ones
-        const int len = __builtin_popcountll(run);
-        r |= (x * low) & run;
-        x = len < 64 ? x >> len : 0;
-        mask &= ~run;
-    }
-    return r;
-}
-
-// XOR (for disjoint bits: OR) of the entries at the bits set in j.
-template <int N, typename U>
-__device__ __forceinline__ U subset(const U (&v)[N], int j) {
-    U r = 0;
-#pragma unroll
-    for (int k = 0; k < N; ++k)
-        if ((j >> k) & 1) r ^= v[k];
-    return r;
-}
-
-template <typename T>
-__device__ __forceinline__ T gld(uint32_t off) {
-    return *(const __attribute__((address_space(3))) T*)(size_t)off;
-}
-template <typename T>
-__device__ __forceinline__ void gst(uint32_t off, T v) {
-    *(__attribute__((address_space(3))) T*)(size_t)off = v;
-}
-template <typename R> struct Vec2;
-template <> struct Vec2<float> { using V = float __attribute__((ext_vector_type(2))); };
-template <> struct Vec2<double> { using V = double __attribute__((ext_vector_type(2))); };
-
-// ------------------------------------------------- ops on the 16 registers
-__device__ __forceinline__ float flip_sign(float x, uint32_t f) { return __uint_as_float(__float_as_uint(x) ^ f); }
-__device__ __forceinline__ double flip_sign(double x, uint32_t f) {
-    return __hiloint2double(__double2hiint(x) ^ (int)f, __double2loint(x));
-}
-
-template <typename R, typename T>
-__device__ __forceinline__ void pair2(const R* m, T& v0, T& v1) {
-    T o0, o1;
-    o0.x = m[0] * v0.x - m[1] * v0.y + m[2] * v1.x - m[3] * v1.y;
-    o0.y = m[0] * v0.y + m[1] * v0.x + m[2] * v1.y + m[3] * v1.x;
-    o1.x = m[4] * v0.x - m[5] * v0.y + m[6] * v1.x - m[7] * v1.y;
-    o1.y = m[4] * v0.y + m[5] * v0.x + m[6] * v1.y + m[7] * v1.x;
-    v0 = o0;
-    v1 = o1;
-}
-
-template <typename R, int S, typename T, int NA>
-__device__ __forceinline__ void op_d1(T (&a)[NA], const R* m, uint32_t jbits) {
-    constexpr uint32_t ALL = (S == 0 ? 0x5555u : S == 1 ? 0x3333u : S == 2 ? 0x0f0fu : 0x00ffu) & ((1u << NA) - 1u);
-    if (jbits == ALL) {
-#pragma unroll
-        for (int j = 0; j < NA; ++j)
-            if (!(j & (1 << S))) pair2<R>(m, a[j], a[j | (1 << S)]);
-    } else {
-#pragma unroll
-        for (int j = 0; j < NA; ++j)
-            if (!(j & (1 << S)) && ((jbits >> j) & 1)) pair2<R>(m, a[j], a[j | (1 << S)]);
-    }
-}
-
-// Dense gate on K of the slots (slot mask SM); mv: 2^K x 2^K complex.
 template <typename R, int K, int SM, typename T, int NA>
 __device__ __forceinline__ void op_dk(T (&a)[NA], const R* __restrict__ mv, uint32_t jbits) {
     constexpr int D = 1 << K;
@@ -230,19 +147,6 @@ __device__ __forceinline__ void op_dk(T (&a)[NA], const R* __restrict__ mv, uint
         for (int i = 0; i < D; ++i) {
             a[j | sub] = o[i];
             sub = (sub - SM) & SM;
-        }
-    }
-}
-
-template <int X, typename T, int NA>
-__device__ __forceinline__ void op_move(T (&a)[NA], uint32_t jbits) {
-#pragma unroll
-    for (int j = 0; j < NA; ++j) {
-        if (j & (X & -X)) continue;                            // the lowest moved bit is 0 in the first of a pair
-        if ((jbits >> j) & 1) {
-            const T t = a[j];
-            a[j] = a[j ^ X];
-            a[j ^ X] = t;
         }
     }
 }
@@ -544,8 +448,6 @@ __global__ __launch_bounds__(256) void k_rdm_final(const double* __restrict__ pa
 }
 
 // =============================================================== scheduling
-inline int pc(uint64_t v) { return __builtin_popcountll(v); }
-
 // A gate (or a merged run of uncontrolled one-target gates on one qubit) on
 // physical bits.
 struct GGate {
@@ -554,27 +456,6 @@ struct GGate {
     uint64_t zq;            // bits it acts diagonally on (controls, diagonal targets)
     double frac;            // share of the amplitudes its own kernel would touch
 };
-
-struct Sched {
-    uint64_t bx = 0, bz = 0;                     // bits held by gates passed over
-    bool free(const GGate& g) const { return !(g.xq & (bx | bz)) && !(g.zq & bx); }
-    void hold(const GGate& g) {
-        bx |= g.xq;
-        bz |= g.zq;
-    }
-};
-
-uint32_t local_bits(uint64_t phys, uint64_t qmask) {            // phys bits (all in qmask) as tile-local bits
-    uint32_t r = 0;
-    for (uint64_t m = phys; m; m &= m - 1)
-        r |= 1u << pc(qmask & ((m & (~m + 1)) - 1));
-    return r;
-}
-uint32_t tile_index_bits(uint64_t phys, uint64_t qmask) {       // phys bits outside qmask as bits of the tile index
-    uint32_t r = 0;
-    for (uint64_t m = phys & ~qmask; m; m &= m - 1) r |= 1u << pc(~qmask & ((m & (~m + 1)) - 1));
-    return r;
-}
 
 template <typename R>
 struct Emit {
@@ -707,31 +588,6 @@ struct Emit {
         return 1;
     }
 };
-
-// Bits of the tile for the next pass and the gates it takes: gates in list
-// order, a gate passed over when a gate before it that was passed over
-// holds one of its bits (two gates that both act diagonally on the bits
-// they share commute) or when its bits do not fit in the tile.
-uint64_t take_pass(const std::vector<GGate>& G, const std::vector<char>& done, size_t first, int n, int L, int c,
-                   uint64_t need, std::vector<int>& ops) {
-    const uint64_t all = n >= 64 ? ~0ull : (1ull << n) - 1;
-    uint64_t T = ((1ull << std::min(c, n)) - 1) | need;
-    if (L >= n) T = all;
-    Sched s;
-    ops.clear();
-    for (size_t i = first; i < G.size() && (s.bx & all) != all; ++i) {
-        if (done[i]) continue;
-        const GGate& g = G[i];
-        if (s.free(g) && pc(T | g.xq) <= L) {
-            T |= g.xq;
-            ops.push_back((int)i);
-        } else {
-            s.hold(g);
-        }
-    }
-    for (int q = 0; q < n && pc(T) < L; ++q) T |= 1ull << q;     // long runs: the lowest bits left
-    return T;
-}
 
 // Records of the passes of one call: in the workspace's plan area, in stream
 // order (when it is full, the next pass's records go to its start: the passes
