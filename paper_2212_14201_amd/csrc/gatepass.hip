@@ -6,9 +6,8 @@
 // per 30-qubit complex128 gate) and, below about 20 qubits, by its launch
 // (2.7-4 us).  A gate pass keeps tiles of up to 2^13 (complex64) / 2^12
 // (complex128) amplitudes in LDS and applies every gate of the list that can
-// run on the tile's qubits, each gate with its own matrix and the arithmetic
-// of the one-gate kernels (gates.hip): unlike a fused plan no matrices of
-// different qubits are multiplied together.
+// run on the tile's qubits, each gate by itself: unlike a fused plan no
+// matrices of different qubits are multiplied together.
 //
 //   pass   one workgroup per tile: the 2^L amplitudes that share all
 //          non-tile physical bits; the tile always holds the c lowest bits
@@ -19,19 +18,22 @@
 //          and applies, in order, the gates whose targets are slots; then the
 //          amplitudes go back to LDS and the next round takes other slots.
 //          16 amplitudes (32 or 64 VGPRs) keep four waves per SIMD in
-//          complex64 and two in complex128; a round's LDS traffic (1,024
-//          cycles per 64 KiB tile and CU) costs about one dense gate's
-//          arithmetic.
+//          complex64 and two in complex128 (of 64 KiB tiles).
+//   record what a round applies at once: one gate, the signs that are due, or
+//          a LAYER, the factors and rotations that are due (pass_gates).
 //
-// What bounds it: the vector unit (a dense gate takes 16 multiply-adds per
-// pair and, for the register moves of the in-place update, about 20% more
-// instructions).  28 qubits, complex128, 8 layers of U3 + CZ (332 gates):
-// 361 ms with one kernel per gate, 31.5 ms in 6 passes, of which the
-// multiply-adds alone take 12 ms and the passes' traffic 8 ms; the first
-// pass (72 dense gates) issues vector instructions in 74% of its cycles.
-// 25 qubits, complex64, 4 layers of rotations + CNOTs (400 gates): 35.3 ->
-// 1.9 ms.  12 qubits, complex128, 20 layers (350 gates, one workgroup): 1.38
-// -> 0.19 ms.
+// What bounds it: 28 qubits, complex128, 8 layers of U3 + CZ (332 gates):
+// 361 ms with one kernel per gate; 31.6 ms in 6 passes with a dense 2 x 2
+// product per U3, of which the passes' traffic takes 8 ms; 27.7 ms with
+// rotations and phases (a third of the multiply-adds) in a record each, and
+// no faster when these worked in place (a quarter fewer vector instructions):
+// then branches bound it, a dozen per record; 21.5 ms with LAYER and SIGNS
+// records.  Now the first pass (72 U3) issues vector instructions in 64% of
+// its cycles, and the last two are bound by HBM.
+// 25 qubits, complex64, 4 layers of rotations + CNOTs (400 gates): 35.3 ms
+// with one kernel per gate, 1.92 with dense products, now 1.75 (11 passes,
+// whose traffic takes 0.92).  12 qubits, complex128, 20 layers (350 gates, one
+// workgroup): 1.38 ms, 0.187, now 0.126.
 //
 // The list's records are written to the workspace by k_put kernels, which
 // carry them as kernel arguments: no copy from host memory that the caller
@@ -44,6 +46,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <deque>
 #include <vector>
 
 #include "gatepass.hpp"
@@ -56,8 +59,10 @@ namespace {
 // (0,2), (0,3), (1,2), (1,3), (2,3); D3 + s: on the three slots other than s;
 // PHASE: one factor; SIGN: a factor of -1; DIAG: two factors chosen by the
 // parity of some index bits (RZ, RZZ); MOVE + x: amplitudes j and j ^ x
-// exchanged (x = 1..15 over the slots).
-enum : uint32_t { GP_D1 = 0, GP_D2 = 4, GP_D3 = 10, GP_PHASE = 14, GP_SIGN = 15, GP_DIAG = 16, GP_MOVE = 16 };
+// exchanged (x = 1..15 over the slots); SIGNS: factors of -1, each on its own
+// condition; LAYER: a factor of its own for every register, then a real
+// rotation on each of some slots.
+enum : uint32_t { GP_D1 = 0, GP_D2 = 4, GP_D3 = 10, GP_PHASE = 14, GP_DIAG = 15, GP_MOVE = 16, GP_SIGNS = 32, GP_LAYER = 33 };
 
 // One op: 8 words, then its values (R).  A record applies to register j of
 // thread (local index) t in tile w when bit j of jbits is set, (t & tm) ==
@@ -65,12 +70,19 @@ enum : uint32_t { GP_D1 = 0, GP_D2 = 4, GP_D3 = 10, GP_PHASE = 14, GP_SIGN = 15,
 struct OpHead {
     uint32_t code;          // op code | words to the next record << 8
     uint32_t jbits;         // registers it applies to (D1..D3: by the first of each group) |
-                            // DIAG: registers with odd slot parity << 16
+                            // DIAG: registers with odd slot parity << 16 |
+                            // LAYER: the slots rotated, and kTable if there are factors |
+                            // SIGNS: how many conditions follow (SignCond)
     uint32_t tm, tv;
     uint32_t om, ov;
     uint32_t pt, po;        // DIAG: parity masks over t and w
 };
 static_assert(sizeof(OpHead) == 32, "eight words");
+constexpr uint32_t kTable = 16;
+struct SignCond {
+    uint32_t jbits, tm, tv, om, ov, pad[3];
+};
+static_assert(sizeof(SignCond) == 32, "eight words");
 
 // A round: 16 words.  The slots' addresses are worked out on the host: the
 // same uniform arithmetic in every wave cost more scalar instructions per
@@ -119,6 +131,7 @@ __global__ __launch_bounds__(256) void k_put(PutArgs a) {
     for (uint32_t i = threadIdx.x; i < a.n; i += 256) dst[i] = arg[4 + i];
 }
 
+// Dense gate on K of the slots (slot mask SM); mv: 2^K x 2^K complex.
 template <typename R, int K, int SM, typename T, int NA>
 __device__ __forceinline__ void op_dk(T (&a)[NA], const R* __restrict__ mv, uint32_t jbits) {
     constexpr int D = 1 << K;
@@ -142,12 +155,36 @@ __device__ __forceinline__ void op_dk(T (&a)[NA], const R* __restrict__ mv, uint
             o[i].x = re;
             o[i].y = im;
         }
+        // all of the results, then back (move_to)
+#pragma unroll
+        for (int i = 0; i < D; i += 4)
+            asm volatile("" : "+v"(o[i].x), "+v"(o[i].y), "+v"(o[i + 1].x), "+v"(o[i + 1].y), "+v"(o[i + 2].x),
+                         "+v"(o[i + 2].y), "+v"(o[i + 3].x), "+v"(o[i + 3].y));
         int sub = 0;
 #pragma unroll
         for (int i = 0; i < D; ++i) {
-            a[j | sub] = o[i];
+            a[j | sub] = T{move_to(o[i].x), move_to(o[i].y)};
             sub = (sub - SM) & SM;
         }
+    }
+}
+
+// The rotation [c -s; s c] on slot S as three shears: v0 += a v1, v1 += b v0,
+// v0 += a v1 with a = -tan(angle / 2) and b = s, angle in [0, pi/2].  Six
+// multiply-adds per pair, all in place, where a dense gate takes sixteen and
+// three register moves.
+template <typename R, int S, typename T, int NA>
+__device__ __forceinline__ void op_turn(T (&a)[NA], R ta, R tb) {
+#pragma unroll
+    for (int j = 0; j < NA; ++j) {
+        if (j & (1 << S)) continue;
+        T &v0 = a[j], &v1 = a[j | (1 << S)];
+        v0.x += ta * v1.x;
+        v0.y += ta * v1.y;
+        v1.x += tb * v0.x;
+        v1.y += tb * v0.y;
+        v0.x += ta * v1.x;
+        v0.y += ta * v1.y;
     }
 }
 
@@ -178,47 +215,54 @@ __device__ __forceinline__ void apply_op(T (&a)[NA], const OpHead& h, const Rec<
                                          const R* __restrict__ mv, uint32_t le, uint32_t w) {
     const uint32_t code = h.code & 0xffu;
     const uint32_t jb = h.jbits & 0xffffu;
-    if (code < GP_D2) {                                        // the most common ops first, by two branches
-        R m[8];
+    if (!below(code, GP_SIGNS)) {
+        if (is(code, GP_LAYER)) {
+            if (jb & kTable) {
+                const R* __restrict__ f = mv + 2 * kSlots;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) m[i] = rec.val(i);
-        if (code < GP_D1 + 2) {
-            if (code == GP_D1) op_d1<R, 0>(a, m, jb);
-            else op_d1<R, 1>(a, m, jb);
-        } else {
-            if (NA == 8 || code == GP_D1 + 2) op_d1<R, 2>(a, m, jb);
-            else if constexpr (NA == 16) op_d1<R, 3>(a, m, jb);
+                for (int j = 0; j < NA; ++j) phase1<R>(f[2 * j], f[2 * j + 1], a[j]);
+            }
+            if (jb & 1) op_turn<R, 0>(a, rec.val(0), rec.val(1));
+            if (jb & 2) op_turn<R, 1>(a, rec.val(2), rec.val(3));
+            if (jb & 4) op_turn<R, 2>(a, rec.val(4), rec.val(5));
+            if constexpr (NA == 16)
+                if (jb & 8) op_turn<R, 3>(a, rec.val(6), rec.val(7));
         }
-        return;
-    }
-    switch (code) {
-        case GP_D2 + 0: op_dk<R, 2, 3>(a, mv, jb); break;
-        case GP_D2 + 1: op_dk<R, 2, 5>(a, mv, jb); break;
-        case GP_D2 + 3: op_dk<R, 2, 6>(a, mv, jb); break;
-        case GP_D3 + 3: op_dk<R, 3, 7>(a, mv, jb); break;
-#define QVM_GP_4(C, K, SM) case C: if constexpr (NA == 16) op_dk<R, K, SM>(a, mv, jb); break;
-        QVM_GP_4(GP_D2 + 2, 2, 9) QVM_GP_4(GP_D2 + 4, 2, 10) QVM_GP_4(GP_D2 + 5, 2, 12)
-        QVM_GP_4(GP_D3 + 0, 3, 14) QVM_GP_4(GP_D3 + 1, 3, 13) QVM_GP_4(GP_D3 + 2, 3, 11)
-#undef QVM_GP_4
-        case GP_PHASE: {
-            const R pr = rec.val(0), pi = rec.val(1);
+        if (is(code, GP_SIGNS)) {
+            // each register's sign: the parity of the conditions the thread meets
+            uint32_t odd = 0;
+            typedef uint32_t U8 __attribute__((ext_vector_type(8), aligned(4)));
+            const U8* __restrict__ c = (const U8*)mv;
+            for (uint32_t i = 0; i < jb; ++i) {
+                const U8 x = c[i];
+                odd ^= (((w & x[3]) ^ x[4]) | ((le & x[1]) ^ x[2])) == 0 ? x[0] : 0u;
+            }
 #pragma unroll
-            for (int j = 0; j < NA; ++j)
-                if ((jb >> j) & 1) {
-                    const T v = a[j];
-                    a[j].x = pr * v.x - pi * v.y;
-                    a[j].y = pr * v.y + pi * v.x;
-                }
-        } break;
-        case GP_SIGN:
-#pragma unroll
-            for (int j = 0; j < NA; ++j) {                  // a sign-bit flip, without a branch per register
-                const uint32_t f = (jb << (31 - j)) & 0x80000000u;
+            for (int j = 0; j < NA; ++j) {
+                const uint32_t f = (odd << (31 - j)) & 0x80000000u;
                 a[j].x = flip_sign(a[j].x, f);
                 a[j].y = flip_sign(a[j].y, f);
             }
-            break;
-        case GP_DIAG: {
+        }
+    }
+    if (below(code, GP_D2)) {
+        R m[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) m[i] = rec.val(i);
+        if (is(code, GP_D1)) op_d1<R, 0>(a, m, jb);
+        if (is(code, GP_D1 + 1)) op_d1<R, 1>(a, m, jb);
+        if (is(code, GP_D1 + 2)) op_d1<R, 2>(a, m, jb);
+        if constexpr (NA == 16)
+            if (is(code, GP_D1 + 3)) op_d1<R, 3>(a, m, jb);
+    }
+    if (below(code - GP_PHASE, GP_SIGNS - GP_PHASE)) {
+        if (is(code, GP_PHASE)) {
+            const R pr = rec.val(0), pi = rec.val(1);
+#pragma unroll
+            for (int j = 0; j < NA; ++j)
+                if ((jb >> j) & 1) phase1(pr, pi, a[j]);
+        }
+        if (is(code, GP_DIAG)) {
             const bool odd = ((__popc(le & h.pt) + __popc(w & h.po)) & 1) != 0;
             const R er = odd ? rec.val(2) : rec.val(0), ei = odd ? rec.val(3) : rec.val(1);     // registers of even slot parity
             const R qr = odd ? rec.val(0) : rec.val(2), qi = odd ? rec.val(1) : rec.val(3);
@@ -226,17 +270,23 @@ __device__ __forceinline__ void apply_op(T (&a)[NA], const OpHead& h, const Rec<
             for (int j = 0; j < NA; ++j)
                 if ((jb >> j) & 1) {
                     const bool o = (h.jbits >> (16 + j)) & 1;
-                    const R pr = o ? qr : er, pi = o ? qi : ei;
-                    const T v = a[j];
-                    a[j].x = pr * v.x - pi * v.y;
-                    a[j].y = pr * v.y + pi * v.x;
+                    phase1<R>(o ? qr : er, o ? qi : ei, a[j]);
                 }
-        } break;
-#define QVM_GP_MV(X) case GP_MOVE + X: if constexpr (X < NA) op_move<X>(a, jb); break;
-        QVM_GP_MV(1) QVM_GP_MV(2) QVM_GP_MV(3) QVM_GP_MV(4) QVM_GP_MV(5) QVM_GP_MV(6) QVM_GP_MV(7) QVM_GP_MV(8)
-        QVM_GP_MV(9) QVM_GP_MV(10) QVM_GP_MV(11) QVM_GP_MV(12) QVM_GP_MV(13) QVM_GP_MV(14) QVM_GP_MV(15)
+        }
+#define QVM_GP_MV(X) if constexpr (X < NA) if (is(code, GP_MOVE + X)) op_move<X>(a, jb);
+        QVM_GP_MV(1) QVM_GP_MV(2) QVM_GP_MV(4) QVM_GP_MV(8)
+        if (!below(code, GP_MOVE + 3) && __popc(code - GP_MOVE) > 1) {
+            QVM_GP_MV(3) QVM_GP_MV(5) QVM_GP_MV(6) QVM_GP_MV(7) QVM_GP_MV(9) QVM_GP_MV(10) QVM_GP_MV(11) QVM_GP_MV(12)
+            QVM_GP_MV(13) QVM_GP_MV(14) QVM_GP_MV(15)
+        }
 #undef QVM_GP_MV
-        default: break;
+    }
+    if (below(code - GP_D2, GP_PHASE - GP_D2)) {
+#define QVM_GP_DK(C, K, SM) if constexpr (SM < NA) if (is(code, C)) op_dk<R, K, SM>(a, mv, jb);
+        QVM_GP_DK(GP_D2 + 0, 2, 3) QVM_GP_DK(GP_D2 + 1, 2, 5) QVM_GP_DK(GP_D2 + 2, 2, 9) QVM_GP_DK(GP_D2 + 3, 2, 6)
+        QVM_GP_DK(GP_D2 + 4, 2, 10) QVM_GP_DK(GP_D2 + 5, 2, 12) QVM_GP_DK(GP_D3 + 0, 3, 14) QVM_GP_DK(GP_D3 + 1, 3, 13)
+        QVM_GP_DK(GP_D3 + 2, 3, 11) QVM_GP_DK(GP_D3 + 3, 3, 7)
+#undef QVM_GP_DK
     }
 }
 
@@ -500,16 +550,64 @@ struct Emit {
         h.ov = tile_index_bits(cval, qmask);
         return h;
     }
+    // A diagonal op on slots alone: its factors per register multiplied into
+    // f, or false.
+    bool slot_factors(const LOp& o, cd* f) const {
+        uint64_t bits = o.cls == OP_PHASE ? o.cond_mask : o.cmask;
+        if (o.cls == OP_DIAG)
+            for (int r = 0; r < o.k; ++r) bits |= 1ull << o.t[r];
+        if ((o.cls != OP_PHASE && o.cls != OP_DIAG) || (bits & ~slots_phys)) return false;
+        if (!f) return true;
+        for (uint32_t j = 0; j < 1u << rs; ++j) {
+            uint64_t at = 0;
+            for (int s = 0; s < rs; ++s)
+                if ((j >> s) & 1) at |= slot_phys[s];
+            if (o.cls == OP_PHASE) {
+                if ((at & o.cond_mask) == o.cond_val) f[j] *= o.phase;
+            } else if ((at & o.cmask) == o.cmask) {
+                int e = 0;
+                for (int r = 0; r < o.k; ++r) e |= (int)((at >> o.t[r]) & 1) << r;
+                f[j] *= o.m[e];
+            }
+        }
+        return true;
+    }
+    // factors f (or none) and rotations (a, b) of the slots in mask
+    void layer(const cd* f, uint32_t mask, const double (*ab)[2]) {
+        double v[2 * kSlots + (2 << kSlots)] = {};
+        for (int k = 0; k < kSlots; ++k)
+            if ((mask >> k) & 1) {
+                v[2 * k] = ab[k][0];
+                v[2 * k + 1] = ab[k][1];
+            }
+        if (f)
+            for (uint32_t j = 0; j < 1u << rs; ++j) {
+                v[2 * kSlots + 2 * j] = f[j].real();
+                v[2 * kSlots + 2 * j + 1] = f[j].imag();
+            }
+        OpHead h{};
+        h.code = GP_LAYER;
+        h.jbits = mask | (f ? kTable : 0);
+        record(h, v, 2 * kSlots + (f ? 2 << rs : 0));
+    }
+    void signs(const std::vector<SignCond>& c) {
+        OpHead h{};
+        const size_t words = sizeof(OpHead) / 4 + c.size() * sizeof(SignCond) / 4;
+        h.code = GP_SIGNS | (uint32_t)words << 8;
+        h.jbits = (uint32_t)c.size();
+        const size_t at = tab.size();
+        tab.resize(at + words);
+        memcpy(&tab[at], &h, sizeof(h));
+        memcpy(&tab[at + sizeof(h) / 4], c.data(), c.size() * sizeof(SignCond));
+    }
     // records it writes for one gate
-    int gate(const GGate& g) {
-        const LOp& o = g.op;
+    int gate(const LOp& o) {
         double v[128];
         switch (o.cls) {
             case OP_PHASE: {
-                const bool neg = o.phase == cd(-1.0, 0.0);
                 v[0] = o.phase.real();
                 v[1] = o.phase.imag();
-                record(head(neg ? GP_SIGN : GP_PHASE, o.cond_mask, o.cond_val, 0), v, neg ? 0 : 2);
+                record(head(GP_PHASE, o.cond_mask, o.cond_val, 0), v, 2);
                 return 1;
             }
             case OP_DIAG: {
@@ -589,6 +687,309 @@ struct Emit {
     }
 };
 
+// A pass's gates as its records take them.  A unitary one-target gate is
+// g diag(1, p) R diag(1, q), R a real rotation: R alone is a sequence of
+// shears (op_turn), and the phases join those of other gates.  A phase
+// waits on its bit (through gates that act diagonally on it, and through an
+// uncontrolled X as its conjugate) until a gate that acts otherwise on the
+// bit needs it applied (pre) or the pass ends; in a round the phases that
+// are due on the slots become one factor per register.  U3 layers with CZs between them so
+// take, per four gates, four rotations and one set of factors: 32 multiply-adds
+// per amplitude pair against the 64 (and 12 moves) of four dense gates.  Rounding:
+// against U3 gates exact in 80 bits (10 qubits, 12 layers, complex128) the
+// state is off by 0.9 to 0.95e-15, with dense products by 0.9 to 0.97e-15.
+struct PGate {
+    const LOp* op;
+    uint64_t xq, zq;
+    double frac;
+    bool turn;              // the rotation (a, b), after pre
+    double a, b;
+    int npre;
+    int bit[4];
+    cd pre[4];
+};
+
+bool unit(const cd& x) { return std::fabs(std::norm(x) - 1.0) < 4e-15; }
+cd mulc(const cd& a, const cd& b) {
+    return cd(a.real() * b.real() - a.imag() * b.imag(), a.real() * b.imag() + a.imag() * b.real());
+}
+
+// A phase that is carried along, in long double: rounded at every gate, the
+// factor of all amplitudes alone would be off by more than the gates' own
+// rounding (332 gates: 4e-15 of the state's norm against 2e-15).
+struct Phase {
+    long double re = 1.0L, im = 0.0L;
+    Phase() = default;
+    Phase(long double r, long double i) : re(r), im(i) {}
+    explicit Phase(const cd& x) : re(x.real()), im(x.imag()) {}
+    bool one() const { return re == 1.0L && im == 0.0L; }
+    Phase conj() const { return Phase(re, -im); }
+    void by(const Phase& o) {
+        const long double r = re * o.re - im * o.im;
+        im = re * o.im + im * o.re;
+        re = r;
+    }
+    cd value() const { return cd((double)re, (double)im); }
+};
+
+struct Euler { Phase g, p, q; double c, s; };
+
+// u = g diag(1, p) [c -s; s c] diag(1, q), for a unitary u with no zero entry.
+bool euler(const std::vector<cd>& u, Euler& e) {
+    Phase w[4];
+    long double r[4];
+    for (int i = 0; i < 4; ++i) {
+        const long double x = u[i].real(), y = u[i].imag();
+        r[i] = sqrtl(x * x + y * y);
+        if (!(r[i] > 0.0L) || !(r[i] < 2.0L)) return false;
+        w[i] = Phase(x / r[i], y / r[i]);
+    }
+    // (the mean of both columns: what the entries' rounding leaves of the
+    // matrix's norm stays in g)
+    const long double c2 = r[0] * r[3], s2 = r[1] * r[2], h = sqrtl(c2 + s2), tol = 4e-15L;
+    if (!(fabsl(h - 1.0L) < tol) || !(fabsl(r[0] - r[3]) < tol) || !(fabsl(r[1] - r[2]) < tol)) return false;
+    e.c = (double)(sqrtl(c2) / h);
+    e.s = (double)(sqrtl(s2) / h);
+    e.g = w[0];
+    e.p = w[2];
+    e.p.by(w[0].conj());
+    e.q = Phase(-w[1].re, -w[1].im);
+    e.q.by(w[0].conj());
+    Phase d = e.g;
+    d.by(e.p);
+    d.by(e.q);
+    if (!(fabsl(d.re - w[3].re) * r[3] < tol) || !(fabsl(d.im - w[3].im) * r[3] < tol)) return false;
+    e.g.re *= h;
+    e.g.im *= h;
+    return true;
+}
+
+// (own: ops that are not the list's)
+std::vector<PGate> pass_gates(const std::vector<GGate>& G, const std::vector<int>& ops, std::deque<LOp>& own) {
+    const cd one(1.0, 0.0), zero(0.0, 0.0);
+    std::vector<PGate> out;
+    out.reserve(ops.size() + 2);
+    Phase ph[QVM_MAX_QUBITS], all;               // of the amplitudes with the bit set; of every amplitude
+    for (int i : ops) {
+        const LOp& o = G[i].op;
+        if (o.cls == OP_PHASE && pc(o.cond_mask) == 1 && unit(o.phase)) {
+            Phase f(o.phase);
+            if (!o.cond_val) {
+                all.by(f);
+                f = f.conj();
+            }
+            ph[__builtin_ctzll(o.cond_mask)].by(f);
+            continue;
+        }
+        if (o.cls == OP_DIAG && o.k == 1 && o.cmask == 0 && unit(o.m[0]) && unit(o.m[1])) {
+            Phase f(o.m[1]);
+            f.by(Phase(o.m[0]).conj());
+            ph[o.t[0]].by(f);
+            all.by(Phase(o.m[0]));
+            continue;
+        }
+        PGate g{&o, G[i].xq, G[i].zq, G[i].frac, false, 0, 0, 0, {}, {}};
+        const bool lone = o.cls == OP_DENSE && o.k == 1 && o.cmask == 0;
+        Phase after;                             // what it leaves on its bit
+        Euler e;
+        if (lone && o.m[0] == zero && o.m[3] == zero && unit(o.m[1]) && unit(o.m[2])) {
+            // diag(m1, m2) X: all m1, then m2 / m1 on the bit
+            after = Phase(o.m[2]);
+            after.by(Phase(o.m[1]).conj());
+            all.by(Phase(o.m[1]));
+            own.push_back(classify(1, o.t, 0, {zero, one, one, zero}));
+            g.op = &own.back();
+        } else if (lone && euler(o.m, e)) {
+            g.turn = true;
+            g.a = -e.s / (1.0 + e.c);
+            g.b = e.s;
+            all.by(e.g);
+            ph[o.t[0]].by(e.q);
+            after = e.p;
+        }
+        for (uint64_t m = g.xq; m; m &= m - 1) {
+            const int b = __builtin_ctzll(m);
+            if (ph[b].one()) continue;
+            if (g.op->cls == OP_SWAPPAIR && g.xq == 1ull << b && !g.zq) {
+                all.by(ph[b]);
+                ph[b] = ph[b].conj();
+                continue;
+            }
+            g.bit[g.npre] = b;
+            g.pre[g.npre++] = ph[b].value();
+            ph[b] = Phase();
+        }
+        if (!after.one()) ph[__builtin_ctzll(g.xq)].by(after);
+        out.push_back(std::move(g));
+    }
+    auto phase = [&](uint64_t bits, const Phase& f) {
+        LOp o{};
+        o.cls = OP_PHASE;
+        o.cond_mask = o.cond_val = bits;
+        o.phase = f.value();
+        own.push_back(std::move(o));
+        return PGate{&own.back(), 0, bits, std::ldexp(1.0, -pc(bits)), false, 0, 0, 0, {}, {}};
+    };
+    for (int b = 0; b < QVM_MAX_QUBITS; ++b)
+        if (!ph[b].one()) out.push_back(phase(1ull << b, ph[b]));
+    if (!all.one()) out.insert(out.begin(), phase(0, all));
+    return out;
+}
+
+// The records of a round: gates `now` of P in order.  A diagonal gate waits
+// until a gate acts otherwise on one of its bits, and then all that wait are
+// applied: the ones on slots alone as factors, the signs together, others one
+// by one.  A rotation takes with it the rotations of the other slots that can
+// come as early.  Fewer records, because choosing an op takes a dozen
+// branches (the head of this file has the times with a record per gate).
+// Returns how many.
+constexpr size_t kMaxSigns = 64;                 // conditions of a record
+
+template <typename R>
+uint32_t round_records(Emit<R>& E, const std::vector<PGate>& P, const std::vector<int>& now, double amps,
+                       double& flops) {
+    const cd one(1.0, 0.0), neg(-1.0, 0.0);
+    const int NA = 1 << E.rs;
+    uint32_t nops = 0;
+    std::vector<char> used(now.size(), 0), pre_used(now.size(), 0);
+    std::vector<size_t> wait;                    // diagonal gates not applied yet
+    uint64_t wait_bits = 0;
+    cd f[1 << kSlots], fs[1 << kSlots];          // factors to be applied next; fs: the signs among them
+    std::vector<SignCond> signs;
+    int items = 0;                               // in f
+    const LOp* single = nullptr;
+    std::vector<LOp> hold;
+    hold.reserve(4);
+    auto clear = [&]() {
+        std::fill(f, f + NA, one);
+        std::fill(fs, fs + NA, one);
+        signs.clear();
+        hold.clear();
+        items = 0;
+        single = nullptr;
+    };
+    clear();
+    auto factor = [&](const LOp& o) {            // o on slots alone
+        const bool sign = o.cls == OP_PHASE && o.phase == neg;
+        E.slot_factors(o, sign ? fs : f);
+        if (sign) return;
+        ++items;
+        single = &o;
+    };
+    auto pres = [&](size_t k) {
+        const PGate& q = P[now[k]];
+        if (pre_used[k]) return;
+        pre_used[k] = 1;
+        for (int b = 0; b < q.npre; ++b) {
+            LOp o{};
+            o.cls = OP_PHASE;
+            o.cond_mask = o.cond_val = 1ull << q.bit[b];
+            o.phase = q.pre[b];
+            if (hold.size() < hold.capacity()) {
+                hold.push_back(o);
+                factor(hold.back());
+            } else {
+                factor(o);
+            }
+        }
+    };
+    auto release = [&]() {
+        for (size_t k : wait) {
+            const LOp& o = *P[now[k]].op;
+            if (E.slot_factors(o, nullptr)) {
+                factor(o);
+            } else if (o.cls == OP_PHASE && o.phase == neg) {
+                const OpHead h = E.head(GP_SIGNS, o.cond_mask, o.cond_val, 0);
+                signs.push_back(SignCond{h.jbits, h.tm, h.tv, h.om, h.ov, {0, 0, 0}});
+            } else {
+                nops += (uint32_t)E.gate(o);
+                flops += 6.0 * amps * P[now[k]].frac;
+            }
+        }
+        wait.clear();
+        wait_bits = 0;
+    };
+    // the factors and signs due, with the rotations of the slots in mask
+    auto apply = [&](uint32_t mask, const double (*ab)[2]) {
+        const bool lone = items == 1 && !mask;   // one gate's factors: on its own registers only
+        const bool tab = items && !lone;
+        uint32_t nb = 0;
+        for (int j = 0; j < NA; ++j) {
+            if (tab) f[j] = mulc(f[j], fs[j]);
+            else if (fs[j] == neg) nb |= 1u << j;
+        }
+        if (nb) signs.push_back(SignCond{nb, 0, 0, 0, 0, {0, 0, 0}});
+        for (size_t k = 0; k < signs.size(); k += kMaxSigns) {
+            E.signs(std::vector<SignCond>(signs.begin() + k, signs.begin() + std::min(signs.size(), k + kMaxSigns)));
+            ++nops;
+        }
+        if (lone) {
+            nops += (uint32_t)E.gate(*single);
+            flops += 3.0 * amps;
+        }
+        if (tab || mask) {
+            E.layer(tab ? f : nullptr, mask, ab);
+            ++nops;
+            flops += (tab ? 6.0 : 0.0) * amps + 6.0 * amps * __builtin_popcount(mask);
+        }
+        clear();
+    };
+    for (size_t i = 0; i < now.size(); ++i) {
+        if (used[i]) continue;
+        const PGate& g = P[now[i]];
+        if (!g.xq) {
+            wait.push_back(i);
+            wait_bits |= g.zq;
+            continue;
+        }
+        if (wait_bits & g.xq) release();
+        pres(i);
+        uint64_t bx = g.turn ? 0 : g.xq, bz = (g.turn ? 0 : g.zq) | wait_bits;   // bits of gates passed over
+        uint32_t mask = 0;
+        double ab[kSlots][2] = {};
+        auto rotate = [&](const PGate& q) {
+            const int k = __builtin_ctz(E.slot_bits(q.xq));
+            mask |= 1u << k;
+            ab[k][0] = q.a;
+            ab[k][1] = q.b;
+        };
+        uint64_t turned = 0;
+        if (g.turn) {
+            rotate(g);
+            turned = g.xq;
+        }
+        for (size_t k = i + 1; k < now.size(); ++k) {
+            if (used[k]) continue;
+            const PGate& q = P[now[k]];
+            if (g.turn && q.turn && !(q.xq & (bx | bz | turned))) {
+                pres(k);
+                rotate(q);
+                turned |= q.xq;
+                used[k] = 1;
+                continue;
+            }
+            // (factors due later that can be applied already)
+            if (items && q.npre && !(q.xq & (bx | turned))) pres(k);
+            if (items && !q.xq && !(q.zq & (bx | turned)) && E.slot_factors(*q.op, nullptr)) {
+                factor(*q.op);
+                used[k] = 1;
+                continue;
+            }
+            bx |= q.xq;
+            bz |= q.zq;
+        }
+        apply(mask, ab);
+        if (!g.turn) {
+            nops += (uint32_t)E.gate(*g.op);
+            const double touched = g.frac * amps;
+            flops += g.op->cls == OP_DENSE ? touched * 8.0 * (1 << g.op->k) : g.op->cls == OP_SWAPPAIR ? 0.0 : 6.0 * touched;
+        }
+    }
+    release();
+    apply(0, nullptr);
+    return nops;
+}
+
 // Records of the passes of one call: in the workspace's plan area, in stream
 // order (when it is full, the next pass's records go to its start: the passes
 // before have run by then).
@@ -617,7 +1018,11 @@ qvm_status launch_pass(qvm_sv* sv, PassBuf& buf, const std::vector<GGate>& G, co
             if ((qmask >> b) & 1) A.top[--k] = (uint32_t)b;
     }
     std::vector<uint32_t> tab;
-    std::vector<int> left = ops, next, now;
+    std::deque<LOp> own;
+    const std::vector<PGate> P = pass_gates(G, ops, own);
+    if (P.empty() && !measure) return QVM_OK;                   // (the gates undo each other)
+    std::vector<int> left(P.size()), next, now;
+    for (size_t i = 0; i < P.size(); ++i) left[i] = (int)i;
     double flops = 0;
     std::vector<uint64_t> round_slots;
     while (!left.empty()) {
@@ -626,7 +1031,7 @@ qvm_status launch_pass(qvm_sv* sv, PassBuf& buf, const std::vector<GGate>& G, co
         next.clear();
         now.clear();
         for (size_t q = 0; q < left.size(); ++q) {
-            const GGate& g = G[left[q]];
+            const PGate& g = P[left[q]];
             if ((s.bx & qmask) != qmask && s.free(g) && pc(sm | g.xq) <= rs) {
                 sm |= g.xq;
                 now.push_back(left[q]);
@@ -644,13 +1049,7 @@ qvm_status launch_pass(qvm_sv* sv, PassBuf& buf, const std::vector<GGate>& G, co
             int k = 0;
             for (uint64_t m = sm; m; m &= m - 1) E.slot_phys[k++] = m & (~m + 1);
         }
-        uint32_t nops = 0;
-        for (int i : now) {
-            nops += (uint32_t)E.gate(G[i]);
-            const LOp& o = G[i].op;
-            const double touched = G[i].frac * (double)(1ull << n);
-            flops += o.cls == OP_DENSE ? touched * 8.0 * (1 << o.k) : o.cls == OP_SWAPPAIR ? 0.0 : 6.0 * touched;
-        }
+        const uint32_t nops = round_records(E, P, now, (double)(1ull << n), flops);
         RoundHead rh{};
         for (int k = 0; k < rs; ++k) {
             rh.bit[k] = local_bits(E.slot_phys[k], qmask);
@@ -722,12 +1121,15 @@ qvm_status launch_pass(qvm_sv* sv, PassBuf& buf, const std::vector<GGate>& G, co
 // Below 21 qubits a pass has few tiles, and the time of one wave through its
 // gates counts: 8 amplitudes a thread instead of 16, and tiles that give 16
 // to 128 workgroups, as far as the passes that smaller tiles need (each two
-// launches) pay (measured, microseconds: 12-qubit layered circuit of 175
-// gates, complex128, in one 12-qubit tile 102 against 109 with 16
-// amplitudes; 17 qubits, 200 mixed gates, complex64, tiles of 2^10 / 2^11 /
-// 2^12 172 / 168 / 171, 2^13 with 16 amplitudes 216; 20 qubits 2^12 with 8
-// amplitudes 180, 2^13 with 16 225).  From 21 qubits on the chip is full and
-// the fewest passes win (23 qubits: 572 against 630).
+// launches) pay.  From 21 qubits on the chip is full and the fewest passes win.
+// Measured, microseconds a call with the host's part, 8 / 16 amplitudes:
+//   12 qubits, 350 gates, complex128, tiles of 2^12     211 / 234
+//   16 qubits, 188 gates, complex64, 2^10 / 2^13        122 / 129
+//   17 qubits, 200 mixed gates, complex64, 2^11 / 2^13  203 / 248
+//   20 qubits, 236 gates, complex128, 2^12              167 / 193
+//   23 qubits, 204 gates, complex64, 2^12 / 2^13        364 / 319
+//   25 qubits, 400 gates, complex64, 2^12 / 2^13        2137 / 1744
+//   28 qubits, 332 gates, complex128, 2^12              29.9 / 27.5 ms
 int pass_slots(int n) { return n <= 20 ? 3 : 4; }
 template <typename R> int pass_width(int n) {
     return std::min(n, n <= 12 ? 12 : n <= 16 ? 10 : n <= 19 ? 11 : n <= 20 ? 12 : GT<R>::LMAX);

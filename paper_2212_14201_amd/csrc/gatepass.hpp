@@ -71,6 +71,35 @@ __device__ __forceinline__ double flip_sign(double x, uint32_t f) {
     return __hiloint2double(__double2hiint(x) ^ (int)f, __double2loint(x));
 }
 
+// Ops in place.  A loop over ops keeps a thread's amplitudes where they are
+// only if every op can end in the registers it began in; one that cannot
+// makes each op, also the others, copy all amplitudes (32 moves after the 48
+// multiply-adds of a rotation of 16 complex128 amplitudes).  So
+// - an op that needs its inputs until its last result is done takes the
+//   results back by moves that the compiler does not see through (move_to);
+// - ops are chosen by one test after the other, each without an else, on
+//   copies of the code that the compiler cannot relate (is): control flow is
+//   structured into such tests anyway, and an op behind an else would keep the
+//   amplitudes of before the tested op alive through it.
+__device__ __forceinline__ bool is(uint32_t code, uint32_t c) {
+    asm volatile("" : "+s"(code));
+    return code == c;
+}
+__device__ __forceinline__ bool below(uint32_t code, uint32_t c) {
+    asm volatile("" : "+s"(code));
+    return code < c;
+}
+__device__ __forceinline__ float move_to(float x) {
+    float d;
+    asm volatile("v_mov_b32 %0, %1" : "=v"(d) : "v"(x));
+    return d;
+}
+__device__ __forceinline__ double move_to(double x) {
+    double d;
+    asm volatile("v_mov_b64 %0, %1" : "=v"(d) : "v"(x));
+    return d;
+}
+
 template <typename R, typename T>
 __device__ __forceinline__ void pair2(const R* m, T& v0, T& v1) {
     T o0, o1;
@@ -78,35 +107,55 @@ __device__ __forceinline__ void pair2(const R* m, T& v0, T& v1) {
     o0.y = m[0] * v0.y + m[1] * v0.x + m[2] * v1.y + m[3] * v1.x;
     o1.x = m[4] * v0.x - m[5] * v0.y + m[6] * v1.x - m[7] * v1.y;
     o1.y = m[4] * v0.y + m[5] * v0.x + m[6] * v1.y + m[7] * v1.x;
-    v0 = o0;
-    v1 = o1;
+    asm volatile("" : "+v"(o0.x), "+v"(o0.y), "+v"(o1.x), "+v"(o1.y));
+    v0 = {move_to(o0.x), move_to(o0.y)};
+    v1 = {move_to(o1.x), move_to(o1.y)};
+}
+
+// v times p, in place.
+template <typename R, typename T>
+__device__ __forceinline__ void phase1(R pr, R pi, T& v) {
+    const R t = pi * v.y, u = pr * v.y;
+    v.y = u + pi * v.x;
+    v.x = pr * v.x - t;
 }
 
 template <typename R, int S, typename T, int NA>
 __device__ __forceinline__ void op_d1(T (&a)[NA], const R* m, uint32_t jbits) {
     constexpr uint32_t ALL = (S == 0 ? 0x5555u : S == 1 ? 0x3333u : S == 2 ? 0x0f0fu : 0x00ffu) & ((1u << NA) - 1u);
-    if (jbits == ALL) {
+    if (is(jbits, ALL)) {
 #pragma unroll
         for (int j = 0; j < NA; ++j)
             if (!(j & (1 << S))) pair2<R>(m, a[j], a[j | (1 << S)]);
-    } else {
+        jbits = 0;
+    }
+    if (!is(jbits, 0)) {
 #pragma unroll
         for (int j = 0; j < NA; ++j)
             if (!(j & (1 << S)) && ((jbits >> j) & 1)) pair2<R>(m, a[j], a[j | (1 << S)]);
     }
 }
 
-// Dense gate on K of the slots (slot mask SM); mv: 2^K x 2^K complex.
+// Amplitudes j and j ^ X exchanged, in place (no select of both).
+__device__ __forceinline__ void exchange(float& x, float& y, uint32_t m) {
+    const uint32_t a = __float_as_uint(x), b = __float_as_uint(y), d = (a ^ b) & m;
+    x = __uint_as_float(a ^ d);
+    y = __uint_as_float(b ^ d);
+}
+__device__ __forceinline__ void exchange(double& x, double& y, uint32_t m) {
+    const uint32_t al = __double2loint(x), ah = __double2hiint(x), bl = __double2loint(y), bh = __double2hiint(y);
+    const uint32_t dl = (al ^ bl) & m, dh = (ah ^ bh) & m;
+    x = __hiloint2double(ah ^ dh, al ^ dl);
+    y = __hiloint2double(bh ^ dh, bl ^ dl);
+}
 template <int X, typename T, int NA>
 __device__ __forceinline__ void op_move(T (&a)[NA], uint32_t jbits) {
 #pragma unroll
     for (int j = 0; j < NA; ++j) {
         if (j & (X & -X)) continue;                            // the lowest moved bit is 0 in the first of a pair
-        if ((jbits >> j) & 1) {
-            const T t = a[j];
-            a[j] = a[j ^ X];
-            a[j ^ X] = t;
-        }
+        const uint32_t m = 0u - ((jbits >> j) & 1u);
+        exchange(a[j].x, a[j ^ X].x, m);
+        exchange(a[j].y, a[j ^ X].y, m);
     }
 }
 
