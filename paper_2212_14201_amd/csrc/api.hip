@@ -507,19 +507,7 @@ qvm_status qvm_get_layout(const qvm_sv* sv, int32_t* perm_out) {
 
 qvm_status qvm_reset_layout(qvm_sv* sv) {
     QVM_CHECK_SV(sv);
-    // selection-sort the layout with physical bit swaps
-    for (int q = 0; q < sv->n; ++q) {
-        if (sv->perm[q] == q) continue;
-        int other = -1;
-        for (int r = 0; r < sv->n; ++r)
-            if (sv->perm[r] == q) other = r;
-        int a = sv->perm[q], b = q;         // physical bits to exchange
-        qvm_status st = launch_swap_bits(sv, a, b);
-        if (st) return st;
-        sv->perm[other] = a;
-        sv->perm[q] = b;
-    }
-    return QVM_OK;
+    return reset_layout(sv);
 }
 
 qvm_status qvm_norm(qvm_sv* sv, double* out) {

@@ -134,6 +134,7 @@ qvm_status choose_branch(const double* r, int n_ops, const double* ops, double u
 qvm_status put_words(qvm_sv* sv, uint32_t* dst, const uint32_t* src, size_t n);
 qvm_status launch_init_basis(qvm_sv* sv, uint64_t phys_index);
 qvm_status launch_swap_bits(qvm_sv* sv, int a, int b);   // physical bit swap
+qvm_status reset_layout(qvm_sv* sv);
 
 // ------------------------------------------------------- readout launchers
 qvm_status rd_norm(qvm_sv* sv, double* out);
