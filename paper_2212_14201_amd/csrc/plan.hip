@@ -34,7 +34,8 @@
 
 namespace qvm {
 
-qvm_status launch_tile_pass(qvm_sv* sv, const PassDesc& pd, const char* blob_dev, double flops);
+qvm_status launch_tile_pass(qvm_sv* sv, const PassDesc& pd, const char* blob_dev, double flops, size_t first,
+                            size_t end);
 
 namespace {
 
@@ -1407,9 +1408,17 @@ qvm_status run_plan(qvm_sv* sv, const qvm_plan* P) {
     char* dblob = sv->work + sv->lay.plan_off;
     if (!P->blob.empty())
         QVM_HIP(sv, hipMemcpyAsync(dblob, P->blob.data(), P->blob.size(), hipMemcpyHostToDevice, sv->stream));
+    // a pass's data ends with its chunk and remap tables
+    auto pass_end = [](const PassDesc& pd) {
+        const uint64_t chunks = 1ull << (pd.L - pd.c);
+        return std::max<uint64_t>({pd.ldoff + 8 * chunks, pd.remap ? pd.rmhi + 4 * chunks : 0, pd.remap ? pd.rmlo + (4ull << pd.c) : 0});
+    };
+    size_t first = 0;
     for (size_t i = 0; i < P->passes.size(); ++i) {
-        qvm_status st = launch_tile_pass(sv, P->passes[i], dblob, P->pass_flops[i]);
+        const size_t end = std::min<size_t>(pass_end(P->passes[i]), P->blob.size());
+        qvm_status st = launch_tile_pass(sv, P->passes[i], dblob, P->pass_flops[i], std::min(first, end), end);
         if (st) return st;
+        first = end;
     }
     for (int q = 0; q < sv->n; ++q) sv->perm[q] = P->final_perm[q];
     return QVM_OK;
