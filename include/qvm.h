@@ -414,8 +414,8 @@ qvm_status qvm_adjoint_group_count(int n_qubits, qvm_dtype dt, const qvm_gate* g
 
 /* Number of passes over psi the forward sweep takes (consecutive groups share
  * a pass while their qubits fit a tile), for callers that account for its
- * traffic.  The reverse sweep passes over psi and lambda as often in
- * complex128, and once per group in complex64.  Rules as above.  Host-only. */
+ * traffic.  The reverse sweep passes over psi and lambda as often.  Rules as
+ * above.  Host-only. */
 qvm_status qvm_adjoint_pass_count(int n_qubits, qvm_dtype dt, const qvm_gate* gates, size_t n_gates,
                                   const int32_t* param_index, int n_params, int32_t* n_passes);
 

@@ -65,8 +65,7 @@ class AdjointProblem:
         return self._count(_declare().qvm_adjoint_group_count)
 
     def pass_count(self):
-        """Passes over the batch of the forward sweep (in reverse: as many in
-        complex128, one per group in complex64)."""
+        """Passes over the batch, forward and again in reverse."""
         return self._count(_declare().qvm_adjoint_pass_count)
 
     def _count(self, fn):

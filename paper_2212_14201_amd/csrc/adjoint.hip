@@ -22,17 +22,19 @@
 // Z: with V = U_m ... U_{l+1}, Im <lambda_l| G |psi_l> = Im <lambda| V G
 // V^dagger |psi> = sum_P R_PG S_P, R the rotation of V.
 //
-// complex64: gate by gate, in the order of the groups below, as merged or
-// reordered gates would round the states (and so the gradients) otherwise.
-// The forward sweep puts the groups into passes, the reverse sweep launches
-// one kernel per group (k_adj_group).
+// complex64: gate by gate, in the order of the groups below, each product
+// rounded in a fixed way (adj_apply), as merged or reordered gates would round
+// the states (and so the gradients) otherwise.
 //
-// Before, both sweeps in both types launched a kernel per group, and the host
-// computed every matrix.  20 qubits, complex64, 944 gates (640 trainable),
-// batch 64: forward 92 groups in 23.6 ms, now 41 passes in 14.5; reverse 58.4
-// ms, now 55.6; a call 86.4 ms, now 72.7.  11 qubits, complex128, batch
-// 8, a state one tile: a call 568 us, now 282 (the two sweeps 55 and 120 us on
-// 8 blocks: a chain of rounds, bound by latency).
+// Before, both sweeps in both types launched a kernel per group of four (three)
+// target qubits, and the host computed every matrix.  20 qubits, complex64, 944
+// gates (640 trainable), batch 64: 92 groups each way, forward 23.6 ms, reverse
+// 58.4, a call 85.9 ms; now 41 passes each way, 13.2 and 44 ms, a call 60.9.
+// The passes' traffic takes 7 and 14 ms; in the reverse sweep vector
+// instructions take 61% of the cycles (half of them the gradient terms, which
+// are formed and summed in double precision), with two waves per SIMD.  11
+// qubits, complex128, batch 8, a state one tile: a call 568 us, now 265 (8
+// blocks: a chain of rounds, bound by latency).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -74,7 +76,7 @@ __device__ double adj_block_sum(double v, double* sh) {
 // slot s: AD_MAT the matrix of run `mat`; AD_RE the same without its imaginary
 // part (RY, H: all zero), AD_DG without its off-diagonal entries (RZ); AD_MOVE
 // the pair's amplitudes exchanged; AD_SIGN a factor of -1.
-enum : uint32_t { AD_MAT = 0, AD_RE = 4, AD_DG = 8, AD_MOVE = 12, AD_SIGN = 16 };
+enum : uint32_t { AD_MAT = 0, AD_RE = 4, AD_DG = 8, AD_MOVE = 12, AD_SIGN = 16, AD_RX = 20 };
 struct AdjOp {
     uint32_t code, jbits;
     uint32_t tm, tv, om, ov;
@@ -99,120 +101,175 @@ struct AdjPass {
     uint32_t top[kAdjSlots]; // positions of the highest tile bits, ascending
 };
 
-// S_X, S_Y, S_Z of one pair (the qubit's 0 and 1 amplitudes), added to g.
-template <typename T>
-__device__ __forceinline__ void pauli_terms(double (&g)[3], uint32_t need, const T& a0, const T& a1, const T& l0,
-                                            const T& l1) {
-    const double p0r = a0.x, p0i = a0.y, p1r = a1.x, p1i = a1.y;
-    const double q0r = l0.x, q0i = l0.y, q1r = l1.x, q1i = l1.y;
-    if (need & 1) g[0] += (q0r * p1i - q0i * p1r) + (q1r * p0i - q1i * p0r);    // X: (p1, p0)
-    if (need & 2) g[1] += (q1r * p0r + q1i * p0i) - (q0r * p1r + q0i * p1i);    // Y: (-i p1, i p0)
-    if (need & 4) g[2] += (q0r * p0i - q0i * p0r) - (q1r * p1i - q1i * p1r);    // Z: (p0, -p1)
+// A value widened where it is used: left to itself the compiler widens all of
+// a thread's amplitudes ahead of the branches that use some (256 registers).
+__device__ __forceinline__ double widen(float x) {
+    double d;
+    asm volatile("v_cvt_f64_f32 %0, %1" : "=v"(d) : "v"(x));
+    return d;
+}
+__device__ __forceinline__ double widen(double x) { return x; }
+
+// S_X, S_Y or S_Z (V = 1, 2, 3) of one pair (the qubit's 0 and 1 amplitudes).
+template <int V, typename T>
+__device__ __forceinline__ double pauli_term(const T& a0, const T& a1, const T& l0, const T& l1) {
+    const double p0r = widen(a0.x), p0i = widen(a0.y), p1r = widen(a1.x), p1i = widen(a1.y);
+    const double q0r = widen(l0.x), q0i = widen(l0.y), q1r = widen(l1.x), q1i = widen(l1.y);
+    if (V == 1) return (q0r * p1i - q0i * p1r) + (q1r * p0i - q1i * p0r);        // X: (p1, p0)
+    if (V == 2) return (q1r * p0r + q1i * p0i) - (q0r * p1r + q0i * p1i);        // Y: (-i p1, i p0)
+    return (q0r * p0i - q0i * p0r) - (q1r * p1i - q1i * p1r);                    // Z: (p0, -p1)
 }
 
-template <int S, int NA, typename T>
-__device__ __forceinline__ void adj_grad(double (&g)[3], uint32_t need, const T (&a)[NA], const T (&l)[NA],
-                                         uint32_t jbits) {
-#pragma unroll
-    for (int j = 0; j < NA; ++j)
-        if (!(j & (1 << S)) && ((jbits >> j) & 1)) pauli_terms(g, need, a[j], a[j | (1 << S)], l[j], l[j | (1 << S)]);
+// The wave's sum, in lane 63: register-to-register moves, rows of 16 lanes
+// first (exchanges through LDS held the wave up for every gate).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v) {
+    const uint64_t u = __double_as_longlong(v);
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (uint32_t)u, CTRL, ROWS, 0xf, true);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (uint32_t)(u >> 32), CTRL, ROWS, 0xf, true);
+    return v + __longlong_as_double((uint64_t)hi << 32 | lo);
+}
+__device__ __forceinline__ double wave_total(double v) {
+    v = dpp_add<0x111, 0xf>(v);      // row_shr:1
+    v = dpp_add<0x112, 0xf>(v);
+    v = dpp_add<0x114, 0xf>(v);
+    v = dpp_add<0x118, 0xf>(v);
+    v = dpp_add<0x142, 0xa>(v);      // row_bcast:15 into rows 1 and 3
+    return dpp_add<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
 }
 
-// The wave's sums of three values: X in lanes 0-15, Y in 16-31, Z in 32-47
-// (seven exchanges where three separate sums take eighteen).
-__device__ __forceinline__ double wave_sum3(const double (&g)[3], uint32_t lane) {
-    const bool hi = (lane & 32) != 0, up = (lane & 16) != 0;
-    double a0 = hi ? g[2] : g[0], a1 = hi ? 0.0 : g[1];
-    a0 += __shfl_xor(hi ? g[0] : g[2], 32, 64);
-    a1 += __shfl_xor(hi ? g[1] : 0.0, 32, 64);
-    double b = up ? a1 : a0;
-    b += __shfl_xor(up ? a0 : a1, 16, 64);
+// The sum of one Pauli on slot S, added to the wave's in LDS at `at`.
+template <int V, int S, int NA, typename T>
+__device__ __forceinline__ void adj_sum(const T (&a)[NA], const T (&l)[NA], uint32_t jb, bool act, uint32_t at,
+                                        uint32_t lane) {
+    double g = 0;
+    constexpr uint32_t ALL = (S == 0 ? 0x5555u : S == 1 ? 0x3333u : S == 2 ? 0x0f0fu : 0x00ffu) & ((1u << NA) - 1u);
+    if (act && jb == ALL) {
 #pragma unroll
-    for (int o = 8; o > 0; o >>= 1) b += __shfl_xor(b, o, 64);
-    return b;
-}
-__device__ __forceinline__ double wave_sum(double v) {
+        for (int j = 0; j < NA; ++j)
+            if (!(j & (1 << S))) {
+                g += pauli_term<V>(a[j], a[j | (1 << S)], l[j], l[j | (1 << S)]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+    } else if (act) {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-// A step's gradient sums on slot S, added to the wave's in LDS at `at`.
-template <int S, int NA, typename T>
-__device__ __forceinline__ void adj_sums(const T (&a)[NA], const T (&l)[NA], uint32_t need, uint32_t jb, bool act,
-                                         uint32_t at, uint32_t lane) {
-    double g[3] = {0, 0, 0};
-    if (need == 7) {
-        if (act) adj_grad<S, NA>(g, 7, a, l, jb);
-        const double s = wave_sum3(g, lane);
-        if ((lane & 15) == 0 && lane < 48) gst<double>(at + lane / 2, gld<double>(at + lane / 2) + s);
-        return;
+        for (int j = 0; j < NA; ++j)
+            if (!(j & (1 << S)) && ((jb >> j) & 1)) {
+                g += pauli_term<V>(a[j], a[j | (1 << S)], l[j], l[j | (1 << S)]);
+                // (pairs one after the other: eight pairs' widened values
+                // at once would take 128 registers)
+                __builtin_amdgcn_sched_barrier(0);
+            }
     }
-    if (act) {
-        if (need == 1) adj_grad<S, NA>(g, 1, a, l, jb);
-        else if (need == 2) adj_grad<S, NA>(g, 2, a, l, jb);
-        else adj_grad<S, NA>(g, 4, a, l, jb);
-    }
-    const double s = wave_sum(g[0] + g[1] + g[2]);             // (two of them are 0)
-    if (lane == 0) gst<double>(at, gld<double>(at) + s);
+    g = wave_total(g);
+    if (lane == 63) gst<double>(at, gld<double>(at) + g);
 }
 
 // One product rounded, the other fused.
 __device__ __forceinline__ float mad(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double mad(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
-// A step on slot S of one state's registers.  The forms without the zero
-// entries round as the full product does (which rounds its first or, where
-// it subtracts, its second product and fuses the others in order).
-template <typename R, int S, int NA, typename T>
-__device__ __forceinline__ void adj_apply(T (&a)[NA], const R* u, uint32_t kind, uint32_t jb) {
+// A step on slot S of one state's registers, in place (gatepass.hpp).  Every
+// product is written as it rounds: the first of a row's four rounded, the
+// others fused in order; in the real part the second comes first.  SWAP: in
+// the imaginary part too, except in the first pair.  complex64 states are
+// rounded so, psi without and lambda with SWAP, as the sweep's first kernels
+// were compiled; other orders change the gradients by 1e-7 of their size.
+// The forms without the zero entries round alike.  (As dense products with an
+// else for every kind the reverse sweep took 55 ms, these forms with all
+// amplitudes copied for every gate 57, in place 47, without a branch for
+// every pair 44.)
+template <typename R, int S, bool ADJ, bool SWAP, int NA, typename T>
+__device__ __forceinline__ void adj_apply(T (&a)[NA], const R* m, uint32_t kind, uint32_t jb) {
+    // the matrix m or its adjoint, negated where it is used (a transposed copy
+    // made ahead of the branches costs all ops their place again)
+    struct {
+        const R* m;
+        __device__ __forceinline__ R operator[](int i) const {
+            if (!ADJ) return m[i];
+            const int j = i == 2 || i == 3 ? i + 2 : i == 4 || i == 5 ? i - 2 : i;
+            return (i & 1) ? -m[j] : m[j];
+        }
+    } const u{m};
     constexpr uint32_t ALL = (S == 0 ? 0x5555u : S == 1 ? 0x3333u : S == 2 ? 0x0f0fu : 0x00ffu) & ((1u << NA) - 1u);
-    if (kind == AD_MAT) {
-        op_d1<R, S>(a, u, jb);
-    } else if (kind == AD_MOVE) {
-        op_move<(1 << S)>(a, jb);
-    } else {
-        auto re = [&](int j) {
-            T &v0 = a[j], &v1 = a[j | (1 << S)];
-            T o0, o1;
-            o0.x = mad(u[2], v1.x, u[0] * v0.x);
-            o0.y = mad(u[2], v1.y, u[0] * v0.y);
-            o1.x = mad(u[6], v1.x, u[4] * v0.x);
-            o1.y = mad(u[6], v1.y, u[4] * v0.y);
-            v0 = o0;
-            v1 = o1;
-        };
-        auto dg = [&](int j) {
-            T &v0 = a[j], &v1 = a[j | (1 << S)];
-            T o0, o1;
-            o0.x = mad(u[0], v0.x, -(u[1] * v0.y));
-            o0.y = mad(u[1], v0.x, u[0] * v0.y);
-            o1.x = mad(-u[7], v1.y, u[6] * v1.x);
-            o1.y = mad(u[7], v1.x, u[6] * v1.y);
-            v0 = o0;
-            v1 = o1;
-        };
-        if (kind == AD_RE) {
-            if (jb == ALL) {
+    auto each = [&](auto f) {
 #pragma unroll
-                for (int j = 0; j < NA; ++j)
-                    if (!(j & (1 << S))) re(j);
-            } else {
+        for (int j = 0; j < NA; ++j)
+            if (!(j & (1 << S)) && ((jb >> j) & 1)) f(a[j], a[j | (1 << S)], SWAP && j != 0);
+    };
+    // (all pairs without a branch for each)
+    auto most = [&](auto f) {
+        if (is(jb, ALL)) {
 #pragma unroll
-                for (int j = 0; j < NA; ++j)
-                    if (!(j & (1 << S)) && ((jb >> j) & 1)) re(j);
-            }
-        } else {
-            if (jb == ALL) {
+            for (int j = 0; j < NA; ++j)
+                if (!(j & (1 << S))) f(a[j], a[j | (1 << S)], SWAP && j != 0);
+        }
+        if (!is(jb, ALL)) each(f);
+    };
+    if (is(kind, AD_RE))
+        most([&](T& v0, T& v1, bool) {
+            const R x = u[4] * v0.x, y = u[4] * v0.y;
+            v0.x = mad(u[2], v1.x, u[0] * v0.x);
+            v0.y = mad(u[2], v1.y, u[0] * v0.y);
+            v1.x = mad(u[6], v1.x, x);
+            v1.y = mad(u[6], v1.y, y);
+        });
+    if (is(kind, AD_RX))
+        most([&](T& v0, T& v1, bool) {
+            const R x = u[5] * v0.y, y = u[5] * v0.x;
+            v0.x = mad(-u[3], v1.y, u[0] * v0.x);
+            v0.y = mad(u[3], v1.x, u[0] * v0.y);
+            v1.x = mad(u[6], v1.x, -x);
+            v1.y = mad(u[6], v1.y, y);
+        });
+    if (is(kind, AD_DG))
+        most([&](T& v0, T& v1, bool sw) {
+            const R t = u[1] * v0.y, x = v0.x;
+            v0.y = sw ? mad(u[0], v0.y, u[1] * x) : mad(u[1], x, u[0] * v0.y);
+            v0.x = mad(u[0], x, -t);
+            const R r = mad(-u[7], v1.y, u[6] * v1.x);
+            v1.y = mad(u[7], v1.x, u[6] * v1.y);
+            asm volatile("" : "+v"(v1.y));
+            v1.x = move_to(r);
+        });
+    if (is(kind, AD_MOVE)) op_move<(1 << S)>(a, jb);
+    if (is(kind, AD_MAT))
+        each([&](T& v0, T& v1, bool sw) {
+            auto re = [&](int i) {
+                return mad(-u[i + 3], v1.y, mad(u[i + 2], v1.x, mad(u[i], v0.x, -(u[i + 1] * v0.y))));
+            };
+            auto im = [&](int i) {
+                const R t = sw ? mad(u[i], v0.y, u[i + 1] * v0.x) : mad(u[i + 1], v0.x, u[i] * v0.y);
+                return mad(u[i + 3], v1.x, mad(u[i + 2], v1.y, t));
+            };
+            T o0{re(0), im(0)}, o1{re(4), im(4)};
+            asm volatile("" : "+v"(o0.x), "+v"(o0.y), "+v"(o1.x), "+v"(o1.y));
+            v0 = T{move_to(o0.x), move_to(o0.y)};
+            v1 = T{move_to(o1.x), move_to(o1.y)};
+        });
+}
+
+// A step on one state.
+template <typename R, int RS, bool ADJ, bool SWAP, int NA, typename T>
+__device__ __forceinline__ void adj_step(T (&a)[NA], const R* u, uint32_t kind, uint32_t slot, uint32_t jb, bool act) {
+    uint32_t on = act;
+    asm volatile("" : "+v"(on));
+    if (on) {
+        if (is(kind, AD_SIGN)) {
 #pragma unroll
-                for (int j = 0; j < NA; ++j)
-                    if (!(j & (1 << S))) dg(j);
-            } else {
-#pragma unroll
-                for (int j = 0; j < NA; ++j)
-                    if (!(j & (1 << S)) && ((jb >> j) & 1)) dg(j);
+            for (int j = 0; j < NA; ++j) {
+                const uint32_t f = (jb << (31 - j)) & 0x80000000u;
+                a[j].x = flip_sign(a[j].x, f);
+                a[j].y = flip_sign(a[j].y, f);
             }
         }
+        if (is(slot, 0)) adj_apply<R, 0, ADJ, SWAP, NA>(a, u, kind, jb);
+        if constexpr (RS > 1)
+            if (is(slot, 1)) adj_apply<R, 1, ADJ, SWAP, NA>(a, u, kind, jb);
+        if constexpr (RS > 2)
+            if (is(slot, 2)) adj_apply<R, 2, ADJ, SWAP, NA>(a, u, kind, jb);
+        if constexpr (RS > 3)
+            if (is(slot, 3)) adj_apply<R, 3, ADJ, SWAP, NA>(a, u, kind, jb);
     }
 }
 
@@ -225,7 +282,11 @@ __global__ __launch_bounds__(256, REV ? 2 : 4) void k_adj_pass(typename AC2<R>::
     using T = typename AC2<R>::T;
     using V16 = typename GT<R>::V16;
     using V2 = typename Vec2<R>::V;
+    // (constant address space: the stores to the states do not touch these)
     typedef uint32_t U8 __attribute__((ext_vector_type(8), aligned(4)));
+    typedef const __attribute__((address_space(4))) uint32_t* CW;
+    typedef const __attribute__((address_space(4))) U8* C8;
+    typedef const __attribute__((address_space(4))) R* CR;
     constexpr int EP = GT<R>::EP, NA = 1 << RS;
     constexpr int NIT = NA >= EP ? NA / EP : 1;                // 16-byte pieces per thread
     constexpr int PB = NIT == 1 ? 0 : EP == 2 ? RS - 1 : RS;   // bits of the piece index
@@ -281,14 +342,14 @@ __global__ __launch_bounds__(256, REV ? 2 : 4) void k_adj_pass(typename AC2<R>::
             }
         }
         __syncthreads();
-        const uint32_t* __restrict__ p = table + A.words;
+        CW p = (CW)table + A.words;
         for (uint32_t r = 0; r < A.nrounds; ++r) {
-            const U8 hd = *(const U8*)p;
+            const U8 hd = *(C8)p;
             const uint32_t nops = p[8];
             p += sizeof(AdjRound) / 4;
             // the head one record ahead, the matrix of the record at hand
             // while the head after it is on its way
-            U8 h = *(const U8*)p;
+            U8 h = *(C8)p;
             uint32_t le = tid;                                 // a zero inserted at every slot
 #pragma unroll
             for (int k = 0; k < RS; ++k) le = ((le & ~(hd[k] - 1)) << 1) | (le & (hd[k] - 1));
@@ -316,7 +377,7 @@ __global__ __launch_bounds__(256, REV ? 2 : 4) void k_adj_pass(typename AC2<R>::
             }
             R m[8];
             auto matrix = [&](uint32_t idx) {
-                const R* __restrict__ q = mats + ((size_t)idx * batch + b) * 8;
+                CR q = (CR)mats + ((size_t)idx * batch + b) * 8;
 #pragma unroll
                 for (int i = 0; i < 8; ++i) m[i] = q[i];
             };
@@ -324,45 +385,31 @@ __global__ __launch_bounds__(256, REV ? 2 : 4) void k_adj_pass(typename AC2<R>::
             for (uint32_t oi = 0; oi < nops; ++oi) {
                 const U8 cur = h;
                 R u[8];
-                if constexpr (REV) {                           // the adjoint
-                    u[0] = m[0]; u[1] = -m[1]; u[2] = m[4]; u[3] = -m[5];
-                    u[4] = m[2]; u[5] = -m[3]; u[6] = m[6]; u[7] = -m[7];
-                } else {
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) u[i] = m[i];
-                }
+                for (int i = 0; i < 8; ++i) u[i] = m[i];
                 p += sizeof(AdjOp) / 4;
-                h = *(const U8*)p;                             // (after the last record: in bounds, not used)
+                h = *(C8)p;                                    // (after the last record: in bounds, not used)
                 if ((w & cur[4]) == cur[5]) {
                     const bool act = live && (le & cur[2]) == cur[3];
                     const uint32_t jb = cur[1], kind = cur[0] & ~3u, slot = cur[0] & 3u, need = cur[7] & 7u;
                     const uint32_t at = acc0 + 8 * (wave * A.nsum + (cur[7] >> 3) - 1);
-                    if (kind == AD_SIGN) {
-                        if (act) {
-#pragma unroll
-                            for (int j = 0; j < NA; ++j) {
-                                const uint32_t f = (jb << (31 - j)) & 0x80000000u;
-                                a[j].x = flip_sign(a[j].x, f);
-                                a[j].y = flip_sign(a[j].y, f);
-                                if constexpr (REV) {
-                                    l[j].x = flip_sign(l[j].x, f);
-                                    l[j].y = flip_sign(l[j].y, f);
-                                }
-                            }
+                    // (the sums first, by themselves: what changes the
+                    // amplitudes is one region of its own)
+                    if constexpr (REV) {
+                        if (need) {
+#define QVM_ADJ_SUM(SL)                                                                           \
+    if constexpr (SL < RS)                                                                        \
+        if (is(slot, SL)) {                                                                       \
+            if (need & 1) adj_sum<1, SL, NA>(a, l, jb, act, at, lane);                            \
+            if (need & 2) adj_sum<2, SL, NA>(a, l, jb, act, at + 8 * (need & 1), lane);           \
+            if (need & 4) adj_sum<3, SL, NA>(a, l, jb, act, at + 8 * __popc(need & 3), lane);     \
+        }
+                            QVM_ADJ_SUM(0) QVM_ADJ_SUM(1) QVM_ADJ_SUM(2) QVM_ADJ_SUM(3)
+#undef QVM_ADJ_SUM
                         }
                     }
-#define QVM_ADJ_SLOT(SL)                                                                      \
-    else if (RS == SL + 1 || slot == SL) {                                                    \
-        constexpr int S = SL < RS ? SL : 0;                                                   \
-        if constexpr (REV)                                                                    \
-            if (need) adj_sums<S, NA>(a, l, need, jb, act, at, lane);                         \
-        if (act) {                                                                            \
-            adj_apply<R, S, NA>(a, u, kind, jb);                                              \
-            if constexpr (REV) adj_apply<R, S, NA>(l, u, kind, jb);                           \
-        }                                                                                     \
-    }
-                    QVM_ADJ_SLOT(0) QVM_ADJ_SLOT(1) QVM_ADJ_SLOT(2) QVM_ADJ_SLOT(3)
-#undef QVM_ADJ_SLOT
+                    adj_step<R, RS, REV, false, NA>(a, u, kind, slot, jb, act);
+                    if constexpr (REV) adj_step<R, RS, true, sizeof(R) == 4, NA>(l, u, kind, slot, jb, act);
                 }
                 matrix(oi + 1 < nops ? h[6] : 0);
             }
@@ -400,173 +447,6 @@ __global__ __launch_bounds__(256, REV ? 2 : 4) void k_adj_pass(typename AC2<R>::
             for (uint32_t v = 0; v < nw; ++v) s += gld<double>(acc0 + 8 * (v * A.nsum + i));
             part[((size_t)(A.row0 + i) * nblk + blockIdx.x) * batch + b] = s;
         }
-    }
-}
-
-// The reverse sweep in complex64: one launch per group.  A thread owns one
-// item, the 16 amplitudes of psi and of lambda that differ only in the
-// group's slot bits (at most four target qubits; controls may sit on any
-// qubit), held in registers for the whole group: one read and one write of
-// each state.  Controls on slot bits are tests of the register index, others
-// one test of the item's base index.  Bound by arithmetic (the gradient terms
-// in double precision): at 20 qubits, batch 64 a group of ten gates takes 605
-// us for 2 GiB read and written, which alone take 335.  635 us before the
-// wave's sum left LDS and records were read ahead.  Tiles of both states in
-// LDS (k_adj_pass) took 600, and shorter forms for matrices with zeros 585,
-// but what the compiler contracts into fused multiply-adds differs from one
-// pair of registers to the next here, so other code rounds lambda otherwise
-// (gradients off by 1e-7 of their size): the products stay as they are.
-struct AdjOpDev {
-    uint64_t cout;     // control bits outside the slots
-    int32_t slot;      // target slot
-    int32_t cj;        // control bits among the slots, as a mask over slots
-    int32_t gate;      // row of the matrix table
-    int32_t gen;       // 1/2/3 = X/Y/Z generator of a trainable gate, 0 fixed
-    int32_t tix;       // index among the group's trainable gates
-    int32_t pad;
-};
-
-struct AdjGroupArgs {
-    uint64_t tbit[kAdjSlots];  // slot s <-> bit tbit[s] of the amplitude index
-    uint64_t tmask;    // OR of the slot bits
-    int32_t count, pad;
-    int32_t n_train, row0;   // trainable gates; gradient row of the first one
-};
-
-// Im( conj(l0) (G p)_0 + conj(l1) (G p)_1 ) in double for G = X, Y, Z.
-__device__ __forceinline__ double gen_term(int gen, const float2& a0, const float2& a1, const float2& l0,
-                                           const float2& l1) {
-    const double p0r = a0.x, p0i = a0.y, p1r = a1.x, p1i = a1.y;
-    const double q0r = l0.x, q0i = l0.y, q1r = l1.x, q1i = l1.y;
-    if (gen == 1) return (q0r * p1i - q0i * p1r) + (q1r * p0i - q1i * p0r);   // X: (p1, p0)
-    if (gen == 2) return -(q0r * p1r + q0i * p1i) + (q1r * p0r + q1i * p0i);  // Y: (-i p1, i p0)
-    return (q0r * p0i - q0i * p0r) - (q1r * p1i - q1i * p1r);                  // Z: (p0, -p1)
-}
-
-__device__ __forceinline__ void mul2(const float* m, float2& v0, float2& v1) {
-    float2 o0, o1;
-    o0.x = m[0] * v0.x - m[1] * v0.y + m[2] * v1.x - m[3] * v1.y;
-    o0.y = m[0] * v0.y + m[1] * v0.x + m[2] * v1.y + m[3] * v1.x;
-    o1.x = m[4] * v0.x - m[5] * v0.y + m[6] * v1.x - m[7] * v1.y;
-    o1.y = m[4] * v0.y + m[5] * v0.x + m[6] * v1.y + m[7] * v1.x;
-    v0 = o0;
-    v1 = o1;
-}
-
-// The wave's sum, in lane 63: register-to-register moves, rows of 16 lanes
-// first, as six exchanges through LDS held up the wave for every gate.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_add(double v) {
-    const uint64_t u = __double_as_longlong(v);
-    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (uint32_t)u, CTRL, ROWS, 0xf, true);
-    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (uint32_t)(u >> 32), CTRL, ROWS, 0xf, true);
-    return v + __longlong_as_double((uint64_t)hi << 32 | lo);
-}
-__device__ __forceinline__ double wave_total(double v) {
-    v = dpp_add<0x111, 0xf>(v);      // row_shr:1
-    v = dpp_add<0x112, 0xf>(v);
-    v = dpp_add<0x114, 0xf>(v);
-    v = dpp_add<0x118, 0xf>(v);
-    v = dpp_add<0x142, 0xa>(v);      // row_bcast:15 into rows 1 and 3
-    return dpp_add<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
-}
-
-// One gate on target slot S of the registers (pairs j0, j0 | 2^S).  Returns
-// the thread's gradient term (trainable gate) before the update.
-template <int NA, int S>
-__device__ __forceinline__ double adj_slot(float2 (&a)[NA], float2 (&l)[NA], const float* m, int cj, bool cok, int gen) {
-    double g = 0;
-#pragma unroll
-    for (int j0 = 0; j0 < NA; ++j0) {
-        if (j0 & (1 << S)) continue;
-        const int j1 = j0 | (1 << S);
-        if (!(cok && (j0 & cj) == cj)) continue;
-        if (gen) g += gen_term(gen, a[j0], a[j1], l[j0], l[j1]);
-        mul2(m, l[j0], l[j1]);
-        mul2(m, a[j0], a[j1]);
-    }
-    return g;
-}
-
-template <int r>
-__global__ __launch_bounds__(kAdjThreads) void k_adj_group(float2* __restrict__ psi, float2* __restrict__ lam,
-                                                           uint64_t state_len, uint64_t items, AdjGroupArgs A,
-                                                           const AdjOpDev* __restrict__ ops,
-                                                           const float* __restrict__ mats, int batch,
-                                                           double* __restrict__ part) {
-    constexpr int NA = 1 << r;
-    __shared__ double acc[kAdjMaxTrain * (kAdjThreads / 64)];
-    const int b = blockIdx.y;
-    float2* P = psi + (size_t)b * state_len;
-    float2* Lm = lam + (size_t)b * state_len;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for (int i = threadIdx.x; i < A.n_train * (kAdjThreads / 64); i += kAdjThreads) acc[i] = 0;
-    __syncthreads();
-    uint64_t off[NA];
-#pragma unroll
-    for (int j = 0; j < NA; ++j) {
-        uint64_t o = 0;
-#pragma unroll
-        for (int s = 0; s < r; ++s)
-            if (j & (1 << s)) o |= A.tbit[s];
-        off[j] = o;
-    }
-    const uint64_t stride = (uint64_t)gridDim.x * kAdjThreads;
-    // the loop bound is uniform over the wave, so every lane takes part in
-    // the wave reductions; lanes past the end hold zeros and store nothing
-    for (uint64_t w0 = (uint64_t)blockIdx.x * kAdjThreads + wave * 64; w0 < items; w0 += stride) {
-        const uint64_t w = w0 + lane;
-        const bool act = w < items;
-        const uint64_t base = act ? place(w, ~A.tmask) : 0;
-        float2 a[NA], l[NA];
-#pragma unroll
-        for (int j = 0; j < NA; ++j) {
-            a[j] = act ? P[base | off[j]] : float2{0, 0};
-            l[j] = act ? Lm[base | off[j]] : float2{0, 0};
-        }
-        // the record two gates ahead, the matrix one ahead
-        AdjOpDev next = ops[A.count - 1], after = ops[max(A.count - 2, 0)];
-        float mn[8];
-        auto matrix = [&](int gate) {
-            const float* md = mats + ((size_t)gate * batch + b) * 8;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) mn[i] = md[i];
-        };
-        matrix(next.gate);
-        for (int oi = 0; oi < A.count; ++oi) {
-            const AdjOpDev op = next;
-            float m[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) m[i] = mn[i];
-            next = after;
-            matrix(next.gate);
-            after = ops[max(A.count - 3 - oi, 0)];
-            const bool cok = act && (base & op.cout) == op.cout;
-            const int gen = op.gen;
-            double g = 0;
-            switch (op.slot) {
-                case 0: g = adj_slot<NA, 0>(a, l, m, op.cj, cok, gen); break;
-                case 1: if constexpr (r > 1) g = adj_slot<NA, (r > 1 ? 1 : 0)>(a, l, m, op.cj, cok, gen); break;
-                case 2: if constexpr (r > 2) g = adj_slot<NA, (r > 2 ? 2 : 0)>(a, l, m, op.cj, cok, gen); break;
-                default: if constexpr (r > 3) g = adj_slot<NA, (r > 3 ? 3 : 0)>(a, l, m, op.cj, cok, gen); break;
-            }
-            if (gen) {
-                g = wave_total(g);
-                if (lane == 63) acc[op.tix * (kAdjThreads / 64) + wave] += g;
-            }
-        }
-        if (act) {
-#pragma unroll
-            for (int j = 0; j < NA; ++j) {
-                P[base | off[j]] = a[j];
-                Lm[base | off[j]] = l[j];
-            }
-        }
-    }
-    __syncthreads();
-    for (int t = threadIdx.x; t < A.n_train; t += kAdjThreads) {
-        const double* v = acc + t * (kAdjThreads / 64);
-        part[((size_t)(A.row0 + t) * kAdjBlocks + blockIdx.x) * batch + b] = (v[0] + v[1]) + (v[2] + v[3]);
     }
 }
 
@@ -635,11 +515,6 @@ __global__ __launch_bounds__(256) void k_adj_mats(const AdjRunDev* __restrict__ 
         for (int k = 0; k < 8; ++k) u[k] = t[k];
     }
     for (int k = 0; k < 8; ++k) mats[i * 8 + k] = (R)u[k];
-    if constexpr (sizeof(R) == 4) {                            // and their adjoints
-        R* d = mats + ((size_t)nruns * batch + i) * 8;
-        d[0] = (R)u[0]; d[1] = (R)-u[1]; d[2] = (R)u[4]; d[3] = (R)-u[5];
-        d[4] = (R)u[2]; d[5] = (R)-u[3]; d[6] = (R)u[6]; d[7] = (R)-u[7];
-    }
 }
 
 // The gradients of a run's gates from its three sums: last gate first, with
@@ -834,7 +709,7 @@ struct AdjStep {
     uint32_t need;                   // Paulis its gradients take (0: nothing trainable)
     int run;                         // row of the matrix table (AD_MAT, AD_RE, AD_DG)
     int row;                         // first row of its gradient sums, -1: none
-    bool matrix() const { return kind < AD_MOVE; }
+    bool matrix() const { return kind != AD_MOVE && kind != AD_SIGN; }
 };
 
 // merge: consecutive uncontrolled gates on a qubit as one step (complex128).
@@ -858,7 +733,7 @@ std::vector<AdjStep> adj_steps(const std::vector<AdjGate>& G, bool merge) {
         for (uint64_t m = g.cmask | s.xq; m; m &= m - 1) open[__builtin_ctzll(m)] = -1;
         if (joins) open[g.target] = (int)out.size();
         if (g.pidx >= 0) {
-            s.kind = g.gen == 2 ? AD_RE : g.gen == 3 ? AD_DG : AD_MAT;
+            s.kind = g.gen == 1 ? AD_RX : g.gen == 2 ? AD_RE : AD_DG;
         } else {
             const bool diag = g.u[1] == zero && g.u[2] == zero, off = g.u[0] == zero && g.u[3] == zero;
             bool re = true;
@@ -909,11 +784,11 @@ uint64_t adj_fill(uint64_t sm, uint64_t qmask, int rs) {
 // or a slot is free.
 struct AdjGroup {
     std::vector<int> steps;          // in program order
-    std::vector<int> slots;          // target qubits, as they came
+    uint64_t slots;                  // targets, and the highest other qubits if they are fewer than r
     int train;
 };
 
-std::vector<AdjGroup> adj_groups(const std::vector<AdjStep>& S, int r) {
+std::vector<AdjGroup> adj_groups(const std::vector<AdjStep>& S, int n, int r) {
     std::vector<AdjGroup> out;
     std::vector<char> done(S.size(), 0);
     size_t left = S.size(), first = 0;
@@ -931,7 +806,6 @@ std::vector<AdjGroup> adj_groups(const std::vector<AdjStep>& S, int r) {
                 blocked |= q;
                 continue;
             }
-            if (!(t & tb)) g.slots.push_back(S[i].target);
             t |= tb;
             g.steps.push_back((int)i);
             done[i] = 1;
@@ -939,32 +813,31 @@ std::vector<AdjGroup> adj_groups(const std::vector<AdjStep>& S, int r) {
             g.train += S[i].need != 0;
         }
         while (first < S.size() && done[first]) ++first;
+        g.slots = adj_fill(t, (1ull << n) - 1, r);
         out.push_back(std::move(g));
     }
     return out;
 }
 
-// complex64, forward: a group is a round, and consecutive groups share a pass
-// while their targets and the low bits fit in the tile.
-std::vector<AdjPassPlan> adj_passes_ordered(const std::vector<AdjGroup>& groups, int n, int L, int c, int r) {
+// complex64: a group is a round, and consecutive groups share a pass while
+// their slots and the low bits fit in the tile.
+std::vector<AdjPassPlan> adj_passes_ordered(const std::vector<AdjGroup>& groups, int n, int L, int c) {
     std::vector<AdjPassPlan> out;
-    size_t ops = 0;
+    size_t ops = 0, sums = 0;
     for (const AdjGroup& g : groups) {
-        uint64_t t = 0;
-        for (int q : g.slots) t |= 1ull << q;
-        if (out.empty() || pc(out.back().qmask | t) > L || ops + g.steps.size() > (size_t)kAdjMaxOps) {
+        if (out.empty() || pc(out.back().qmask | g.slots) > L || ops + g.steps.size() > (size_t)kAdjMaxOps ||
+            sums + g.train > (size_t)kAdjMaxSums) {
             out.push_back(AdjPassPlan{(1ull << std::min(c, n)) - 1, {}, {}, {}});
-            ops = 0;
+            ops = sums = 0;
         }
-        out.back().qmask |= t;
+        out.back().qmask |= g.slots;
         out.back().rounds.push_back(g.steps);
-        out.back().slots.push_back(t);
+        out.back().slots.push_back(g.slots);
         ops += g.steps.size();
+        sums += g.train;
     }
-    for (AdjPassPlan& P : out) {
+    for (AdjPassPlan& P : out)
         for (int q = 0; q < n && pc(P.qmask) < std::min(L, n); ++q) P.qmask |= 1ull << q;
-        for (uint64_t& t : P.slots) t = adj_fill(t, P.qmask, r);
-    }
     return out;
 }
 
@@ -995,7 +868,14 @@ std::vector<AdjPassPlan> adj_passes_free(const std::vector<AdjStep>& S, int n, i
 
 // The rounds of a pass, forward or undone.
 AdjPassPlan adj_rounds(const std::vector<AdjStep>& S, AdjPassPlan P, bool rev, int rs) {
-    if (P.steps.empty()) return P;   // (complex64 has them already)
+    if (P.steps.empty()) {           // complex64 has them already
+        if (rev) {
+            std::reverse(P.rounds.begin(), P.rounds.end());
+            std::reverse(P.slots.begin(), P.slots.end());
+            for (auto& r : P.rounds) std::reverse(r.begin(), r.end());
+        }
+        return P;
+    }
     std::vector<int> left = P.steps, next;
     if (rev) std::reverse(left.begin(), left.end());
     while (!left.empty()) {
@@ -1019,10 +899,9 @@ AdjPassPlan adj_rounds(const std::vector<AdjStep>& S, AdjPassPlan P, bool rev, i
     return P;
 }
 
-std::vector<AdjPassPlan> adj_passes(const std::vector<AdjStep>& S, const std::vector<AdjGroup>& groups, int n,
-                                    qvm_dtype dt) {
+std::vector<AdjPassPlan> adj_passes(const std::vector<AdjStep>& S, int n, qvm_dtype dt) {
     if (dt == QVM_C64)
-        return adj_passes_ordered(groups, n, std::min(n, adj_width<float>()), GT<float>::C, std::min(n, adj_slots<float>()));
+        return adj_passes_ordered(adj_groups(S, n, std::min(n, adj_slots<float>())), n, std::min(n, adj_width<float>()), GT<float>::C);
     return adj_passes_free(S, n, std::min(n, adj_width<double>()), GT<double>::C);
 }
 
@@ -1071,41 +950,6 @@ void adj_records(const std::vector<AdjStep>& S, const AdjPassPlan& P, int rs, si
     }
 }
 
-// Slots of a group in k_adj_group: its targets as they came, then the highest
-// other qubits, so that the item index runs over the low bits and a wave's
-// loads stay contiguous.
-std::vector<int> adj_slot_bits(const AdjGroup& g, int n, int r) {
-    std::vector<int> bits = g.slots;
-    uint64_t t = 0;
-    for (int q : bits) t |= 1ull << q;
-    for (int q = n - 1; (int)bits.size() < r && q >= 0; --q)
-        if (!((t >> q) & 1)) bits.push_back(q);
-    return bits;
-}
-
-void adj_group_ops(const std::vector<AdjStep>& S, const std::vector<AdjGate>& G, const AdjGroup& g,
-                   const std::vector<int>& bits, uint32_t row0, std::vector<uint32_t>& tab) {
-    for (int i : g.steps) {
-        const AdjStep& s = S[i];
-        const AdjGate& gate = G[s.gates[0]];
-        AdjOpDev o{};
-        o.gate = s.run;
-        o.cout = s.cmask;
-        for (size_t k = 0; k < bits.size(); ++k) {
-            if (bits[k] == s.target) o.slot = (int)k;
-            if ((s.cmask >> bits[k]) & 1) {
-                o.cj |= 1 << k;
-                o.cout &= ~(1ull << bits[k]);
-            }
-        }
-        o.gen = gate.pidx >= 0 ? gate.gen : 0;
-        o.tix = s.need ? s.row - (int)row0 : -1;
-        const size_t at = tab.size();
-        tab.resize(at + sizeof(o) / 4);
-        memcpy(&tab[at], &o, sizeof(o));
-    }
-}
-
 }  // namespace
 
 template <typename R>
@@ -1121,9 +965,7 @@ static qvm_status adjoint_t(int n, int batch, const std::vector<AdjGate>& G, int
     qvm_sv* sv = &dummy;      // for the error macros only
     std::vector<AdjStep> S = adj_steps(G, sizeof(R) == 8);
     const int rs = std::min(n, adj_slots<R>());
-    std::vector<AdjGroup> groups;
-    if (sizeof(R) == 4) groups = adj_groups(S, rs);
-    const std::vector<AdjPassPlan> passes = adj_passes(S, groups, n, sizeof(R) == 4 ? QVM_C64 : QVM_C128);
+    const std::vector<AdjPassPlan> passes = adj_passes(S, n, sizeof(R) == 4 ? QVM_C64 : QVM_C128);
     // run and gradient rows in pass order; a pass's gradient rows are consecutive
     std::vector<AdjRunDev> runs;
     std::vector<AdjGateDev> gates;
@@ -1137,6 +979,7 @@ static qvm_status adjoint_t(int n, int batch, const std::vector<AdjGate>& G, int
     for (const AdjPassPlan& P : passes)
         for (int i : steps_of(P)) {
             AdjStep& s = S[i];
+            if (!s.matrix()) continue;
             s.run = (int)runs.size();
             AdjRunDev rd{(uint32_t)gates.size(), 0};
             if (s.need) {
@@ -1194,32 +1037,21 @@ static qvm_status adjoint_t(int n, int batch, const std::vector<AdjGate>& G, int
     struct Rec { size_t at; uint64_t qmask; uint32_t rounds, row0, nsum; };
     std::vector<std::vector<uint32_t>> tabs;      // alive until the stream is waited for
     std::vector<Rec> recs;
-    const size_t total = passes.size() + (!want_grad ? 0 : sizeof(R) == 4 ? groups.size() : passes.size());
+    const size_t total = (want_grad ? 2 : 1) * passes.size();
     auto prepare = [&](size_t from) -> qvm_status {
         std::vector<uint32_t> t, one;
         for (size_t q = recs.size(); q < total; ++q) {
             const bool rev = q >= passes.size();
-            Rec r{0, 0, 0, ~0u, 0};
-            auto sums = [&](const std::vector<int>& steps) {
-                for (int i : steps)
+            const AdjPassPlan P = adj_rounds(S, passes[rev ? total - 1 - q : q], rev, rs);
+            Rec r{0, P.qmask, (uint32_t)P.rounds.size(), ~0u, 0};
+            for (const auto& rd : P.rounds)
+                for (int i : rd)
                     if (S[i].need) {
                         r.row0 = std::min(r.row0, (uint32_t)S[i].row);
                         r.nsum += (uint32_t)pc(S[i].need);
                     }
-            };
             one.clear();
-            if (rev && sizeof(R) == 4) {
-                const AdjGroup& g = groups[total - 1 - q];
-                sums(g.steps);
-                adj_group_ops(S, G, g, adj_slot_bits(g, n, rs), r.row0, one);
-            } else {
-                const AdjPassPlan P = adj_rounds(S, passes[rev ? total - 1 - q : q], rev, rs);
-                r.qmask = P.qmask;
-                r.rounds = (uint32_t)P.rounds.size();
-                for (const auto& rd : P.rounds) sums(rd);
-                adj_records(S, P, rs, sizeof(T), r.row0, one);
-            }
-            one.resize((one.size() + 1) & ~size_t(1));
+            adj_records(S, P, rs, sizeof(T), r.row0, one);
             if (t.size() + one.size() + pad > cap) break;
             r.at = t.size();
             t.insert(t.end(), one.begin(), one.end());
@@ -1270,53 +1102,22 @@ static qvm_status adjoint_t(int n, int batch, const std::vector<AdjGate>& G, int
         const size_t lds = (sizeof(T) << A.L) * (rev ? 2 : 1) + (size_t)A.nsum * (threads / 64) * sizeof(double);
         const dim3 grid(rev ? std::min(nblk, A.ntiles) : A.ntiles, (unsigned)batch);
 #define QVM_ADJ_LAUNCH(RR, REV)                                                                            \
-    hipLaunchKernelGGL((k_adj_pass<R, RR, REV>), grid, dim3(threads), lds, stream, psi, lam, A, dtab, mats, \
-                       (uint32_t)batch, nblk, gpart);
-        if (!rev) {
-            switch (rs) {
-                case 1: QVM_ADJ_LAUNCH(1, false) break;
-                case 2: QVM_ADJ_LAUNCH(2, false) break;
-                case 3: QVM_ADJ_LAUNCH(3, false) break;
-                default: if constexpr (sizeof(R) == 4) { QVM_ADJ_LAUNCH(4, false) } break;
-            }
-        } else if constexpr (sizeof(R) == 8) {
-            const qvm_status st = rs == 3 ? lds_limit((const void*)k_adj_pass<R, 3, true>) : QVM_OK;
-            if (st) return st;
-            switch (rs) {
-                case 1: QVM_ADJ_LAUNCH(1, true) break;
-                case 2: QVM_ADJ_LAUNCH(2, true) break;
-                default: QVM_ADJ_LAUNCH(3, true) break;
-            }
-        }
-#undef QVM_ADJ_LAUNCH
-        QVM_LAUNCH_CHECK(sv);
-        return QVM_OK;
-    };
-    auto launch_group = [&](size_t q) -> qvm_status {
-        if (q >= recs.size()) {
-            qvm_status st = prepare(q);
+    {                                                                                                      \
+        hipLaunchKernelGGL((k_adj_pass<R, RR, REV>), grid, dim3(threads), lds, stream, psi, lam, A, dtab,  \
+                           mats, (uint32_t)batch, nblk, gpart);                                            \
+    }
+        if (rev && rs == adj_slots<R>()) {       // (fewer slots: tiny states)
+            const qvm_status st = lds_limit((const void*)k_adj_pass<R, adj_slots<R>(), true>);
             if (st) return st;
         }
-        const AdjGroup& g = groups[total - 1 - q];
-        AdjGroupArgs A{};
-        const std::vector<int> bits = adj_slot_bits(g, n, rs);
-        for (int k = 0; k < rs; ++k) A.tmask |= A.tbit[k] = 1ull << bits[k];
-        A.count = (int32_t)g.steps.size();
-        A.n_train = g.train;
-        A.row0 = g.train ? (int32_t)recs[q].row0 : 0;
-        const AdjOpDev* ops = (const AdjOpDev*)(dtab + recs[q].at);
-        const R* adj = mats + nrun * (size_t)batch * 8;
-        const dim3 grid(kAdjBlocks, (unsigned)batch);
-#define QVM_ADJ_LAUNCH(RR)                                                                              \
-    hipLaunchKernelGGL((k_adj_group<RR>), grid, blk, 0, stream, psi, lam, N, N >> RR, A, ops, adj, batch, gpart);
-        if constexpr (sizeof(R) == 4) {
-            switch (rs) {
-                case 1: QVM_ADJ_LAUNCH(1) break;
-                case 2: QVM_ADJ_LAUNCH(2) break;
-                case 3: QVM_ADJ_LAUNCH(3) break;
-                default: QVM_ADJ_LAUNCH(4) break;
-            }
-        }
+#define QVM_ADJ_CASE(RR)                                  \
+    case RR:                                              \
+        if constexpr (RR <= adj_slots<R>()) {             \
+            if (rev) QVM_ADJ_LAUNCH(RR, true) else QVM_ADJ_LAUNCH(RR, false) \
+        }                                                 \
+        break;
+        switch (rs) { QVM_ADJ_CASE(1) QVM_ADJ_CASE(2) QVM_ADJ_CASE(3) QVM_ADJ_CASE(4) }
+#undef QVM_ADJ_CASE
 #undef QVM_ADJ_LAUNCH
         QVM_LAUNCH_CHECK(sv);
         return QVM_OK;
@@ -1346,16 +1147,14 @@ static qvm_status adjoint_t(int n, int batch, const std::vector<AdjGate>& G, int
         return QVM_OK;
     }
     // reverse sweep; blocks per element: as many partials as there is room for
-    if (sizeof(R) == 4) {
-        nblk = kAdjBlocks;
-    } else if (nsum) {
+    if (nsum) {
         const size_t room = std::min<size_t>(kAdjBlocks, nocc * kAdjBlocks / nsum);
         while (2 * nblk <= room) nblk *= 2;
         // (fewer than nblk tiles: every block still has its partial)
         nblk = (uint32_t)std::min<uint64_t>(nblk, std::max<uint64_t>(1, N >> std::min(n, adj_width<R>())));
     }
     for (size_t q = passes.size(); q < total; ++q) {
-        qvm_status st = sizeof(R) == 4 ? launch_group(q) : launch_pass(q);
+        qvm_status st = launch_pass(q);
         if (st) return st;
     }
     if (nsum) {
@@ -1484,7 +1283,7 @@ qvm_status qvm_adjoint_group_count(int n, qvm_dtype dt, const qvm_gate* gates, s
     qvm_status st = adj_prepare(n, 1, gates, n_gates, param_index, n_params, 1, &z, &z, &c, G, terms);
     if (st) return st;
     const int r = std::min(n, dt == QVM_C64 ? adj_slots<float>() : adj_slots<double>());
-    *n_groups = (int32_t)adj_groups(adj_steps(G, false), r).size();
+    *n_groups = (int32_t)adj_groups(adj_steps(G, false), n, r).size();
     return QVM_OK;
 }
 
@@ -1498,10 +1297,7 @@ qvm_status qvm_adjoint_pass_count(int n, qvm_dtype dt, const qvm_gate* gates, si
     const double c = 0;
     qvm_status st = adj_prepare(n, 1, gates, n_gates, param_index, n_params, 1, &z, &z, &c, G, terms);
     if (st) return st;
-    const std::vector<AdjStep> S = adj_steps(G, dt == QVM_C128);
-    std::vector<AdjGroup> groups;
-    if (dt == QVM_C64) groups = adj_groups(S, std::min(n, adj_slots<float>()));
-    *n_passes = (int32_t)adj_passes(S, groups, n, dt).size();
+    *n_passes = (int32_t)adj_passes(adj_steps(G, dt == QVM_C128), n, dt).size();
     return QVM_OK;
 }
 
