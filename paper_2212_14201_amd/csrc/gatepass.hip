@@ -104,6 +104,7 @@ struct PassArgs {
     uint32_t words;         // offset of the pass's records in the table
     uint32_t direct;        // bit 0: the first round loads from memory, bit 1: the last one stores there
     uint32_t top[kSlots];   // positions of the four highest tile bits (a thread's pieces), ascending
+    uint32_t lines;         // 128-byte lines of the records
 };
 
 // A pass that also measures: the reduced density matrix of four tile bits
@@ -116,6 +117,7 @@ struct RdmArgs {
     uint32_t pad;
 };
 
+constexpr uint32_t kWarmGroups = 512;            // workgroups that read the records ahead: two per CU
 constexpr uint32_t kPutWords = 4000;              // 16,000 bytes of records per k_put launch
 struct PutArgs {
     uint32_t* dst;
@@ -346,6 +348,14 @@ __global__ __launch_bounds__(RS == 4 && sizeof(R) == 8 ? 256 : 512, RS == 4 && s
     const bool live = tid < nt;
     T a[kAmps];
     D4 rr = {0, 0, 0, 0}, ri = {0, 0, 0, 0};                   // RDM: sums of the workgroup's tiles
+    if (blockIdx.x < kWarmGroups) {
+        // the records into L2 while the tile is on its way: they were
+        // written on another die (200 mixed gates, 17 qubits, complex64, ten
+        // passes of 64 workgroups: 179 -> 165 us)
+        uint32_t x = 0;
+        for (uint32_t i = tid; i < A.lines; i += blockDim.x) x ^= table[A.words + 32 * i];
+        asm volatile("" ::"v"(x));
+    }
     for (uint32_t w = blockIdx.x;;) {
     const uint64_t base = place(w, ~A.qmask);
     // stream in: pieces tid + nt i of the tile, all in flight, then to LDS.
@@ -1074,6 +1084,7 @@ qvm_status launch_pass(qvm_sv* sv, PassBuf& buf, const std::vector<GGate>& G, co
     qvm_status st = put_words(sv, buf.dev + buf.used, tab.data(), tab.size());
     if (st) return st;
     buf.used += tab.size();
+    A.lines = (uint32_t)(tab.size() / 32);
     const unsigned threads = std::max(64u, 1u << (L - rs));
     size_t lds = A.direct == 3 && A.nrounds == 1 ? 0 : sizeof(T) << L;
     unsigned grid = 1u << (n - L);
@@ -1119,20 +1130,24 @@ qvm_status launch_pass(qvm_sv* sv, PassBuf& buf, const std::vector<GGate>& G, co
 // Amplitudes per thread (as a power of two) and widest tile of a pass.
 //
 // Below 21 qubits a pass has few tiles, and the time of one wave through its
-// gates counts: 8 amplitudes a thread instead of 16, and tiles that give 16
-// to 128 workgroups, as far as the passes that smaller tiles need (each two
-// launches) pay.  From 21 qubits on the chip is full and the fewest passes win.
-// Measured, microseconds a call with the host's part, 8 / 16 amplitudes:
-//   12 qubits, 350 gates, complex128, tiles of 2^12     211 / 234
-//   16 qubits, 188 gates, complex64, 2^10 / 2^13        122 / 129
-//   17 qubits, 200 mixed gates, complex64, 2^11 / 2^13  203 / 248
-//   20 qubits, 236 gates, complex128, 2^12              167 / 193
-//   23 qubits, 204 gates, complex64, 2^12 / 2^13        364 / 319
-//   25 qubits, 400 gates, complex64, 2^12 / 2^13        2137 / 1744
-//   28 qubits, 332 gates, complex128, 2^12              29.9 / 27.5 ms
+// gates counts: 8 amplitudes a thread instead of 16; from 13 to 16 qubits
+// also tiles of 2^11, for twice the workgroups, as far as the passes that
+// smaller tiles need (each two launches) pay.  From 21 qubits on the chip is
+// full and the fewest passes win.  Measured, microseconds a call (calls one
+// after another), tiles of 2^10 / 2^11 / 2^12 with 8 amplitudes | the widest
+// with 16:
+//   12 qubits, 200 mixed gates, complex64        161 / 140 / 128 | 153
+//   14 qubits, 200 mixed gates, complex64        186 / 163 / 170 | 199
+//   14 qubits, 200 mixed gates, complex128       189 / 184 / 195 | 219
+//   16 qubits, 188 gates in layers, complex128    91 /  89 /  93 |  94
+//   17 qubits, 200 mixed gates, complex64        200 / 187 / 185 | 227
+//   18 qubits, 212 gates in layers, complex64    107 / 100 /  92 | 106
+//   20 qubits, 236 gates in layers, complex128   164 / 152 / 128 | 129
+//   22 qubits, 352 rotations, CNOTs, complex64   390 / 355 / 340 | 298
+//   28 qubits, 332 gates in layers, complex128             29.9 ms | 27.5 ms
 int pass_slots(int n) { return n <= 20 ? 3 : 4; }
 template <typename R> int pass_width(int n) {
-    return std::min(n, n <= 12 ? 12 : n <= 16 ? 10 : n <= 19 ? 11 : n <= 20 ? 12 : GT<R>::LMAX);
+    return std::min(n, n > 20 ? GT<R>::LMAX : n > 12 && n <= 16 ? 11 : 12);
 }
 
 // Passes over the gates of G in order until none is left, or, with bits to
