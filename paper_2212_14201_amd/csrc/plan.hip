@@ -94,34 +94,43 @@ struct qvm_plan {
 namespace qvm {
 namespace {
 
-// y = G x for one gate on a small register (block-local bit positions).
-void apply_small(std::vector<cd>& v, int k_reg, const cd* u, int k, const int* pos, uint64_t cm) {
-    const uint64_t N = 1ull << k_reg;
-    const int dim = 1 << k;
+// G applied to every column of a small register's matrix (block-local bit
+// positions; re and im: N rows of N entries).  All columns at once: a loop
+// over them is vector code, where one column after the other took a third of
+// a plan's time (248 gates in 47 blocks: 44 of 128 us, now 28).
+void apply_small(double* __restrict__ re, double* __restrict__ im, int k_reg, const cd* u, int k, const int* pos,
+                 uint64_t cm, std::vector<double>& in) {
+    const int N = 1 << k_reg, dim = 1 << k;
     uint64_t tm = 0;
     for (int r = 0; r < k; ++r) tm |= 1ull << pos[r];
-    cd in[64];
-    uint64_t idx[64];
-    for (uint64_t b = 0; b < N; ++b) {
+    in.resize((size_t)2 * dim * N);
+    for (uint64_t b = 0; b < (uint64_t)N; ++b) {
         if ((b & tm) || ((b & cm) != cm)) continue;
+        size_t row[64];
         for (int j = 0; j < dim; ++j) {
             uint64_t o = b;
             for (int r = 0; r < k; ++r)
                 if ((j >> r) & 1) o |= 1ull << pos[r];
-            idx[j] = o;
-            in[j] = v[o];
+            row[j] = o * N;
+            std::copy(re + row[j], re + row[j] + N, in.begin() + (size_t)2 * j * N);
+            std::copy(im + row[j], im + row[j] + N, in.begin() + (size_t)(2 * j + 1) * N);
         }
         for (int i = 0; i < dim; ++i) {
             // plain real arithmetic (finite operands; std::complex's product
             // would call the library's NaN-recovering routine per term)
-            double sr = 0, si = 0;
+            double* __restrict__ sr = re + row[i];
+            double* __restrict__ si = im + row[i];
+            std::fill(sr, sr + N, 0.0);
+            std::fill(si, si + N, 0.0);
             for (int j = 0; j < dim; ++j) {
                 const double ar = u[i * dim + j].real(), ai = u[i * dim + j].imag();
-                const double br = in[j].real(), bi = in[j].imag();
-                sr += ar * br - ai * bi;
-                si += ar * bi + ai * br;
+                const double* __restrict__ br = in.data() + (size_t)2 * j * N;
+                const double* __restrict__ bi = br + N;
+                for (int c = 0; c < N; ++c) {
+                    sr[c] += ar * br[c] - ai * bi[c];
+                    si[c] += ar * bi[c] + ai * br[c];
+                }
             }
-            v[idx[i]] = cd(sr, si);
         }
     }
 }
@@ -131,26 +140,20 @@ std::vector<cd> block_matrix(const std::vector<PGate>& G, const std::vector<int>
                              const std::vector<int>& qubits) {
     const int k = (int)qubits.size();
     const int dim = 1 << k;
-    std::vector<cd> M((size_t)dim * dim, cd(0, 0));
-    std::map<int, int> pos;
-    for (int r = 0; r < k; ++r) pos[qubits[r]] = r;
-    // each gate's targets and controls in block bit positions, once
-    struct Placed { const PGate* g; int p[QVM_MAX_K]; uint64_t cm; };
-    std::vector<Placed> pl(gates.size());
-    for (size_t i = 0; i < gates.size(); ++i) {
-        const PGate& g = G[gates[i]];
-        pl[i].g = &g;
-        for (int r = 0; r < g.k; ++r) pl[i].p[r] = pos.at(g.t[r]);
-        pl[i].cm = 0;
-        for (uint64_t m = g.cmask; m; m &= m - 1) pl[i].cm |= 1ull << pos.at(__builtin_ctzll(m));
+    int place[QVM_MAX_QUBITS];
+    for (int r = 0; r < k; ++r) place[qubits[r]] = r;
+    std::vector<double> re((size_t)dim * dim, 0.0), im((size_t)dim * dim, 0.0), work;
+    for (int r = 0; r < dim; ++r) re[(size_t)r * dim + r] = 1.0;
+    for (int gi : gates) {
+        const PGate& g = G[gi];
+        int p[QVM_MAX_K];
+        for (int r = 0; r < g.k; ++r) p[r] = place[g.t[r]];
+        uint64_t cm = 0;
+        for (uint64_t m = g.cmask; m; m &= m - 1) cm |= 1ull << place[__builtin_ctzll(m)];
+        apply_small(re.data(), im.data(), k, g.u.data(), g.k, p, cm, work);
     }
-    std::vector<cd> col(dim);
-    for (int c = 0; c < dim; ++c) {
-        std::fill(col.begin(), col.end(), cd(0, 0));
-        col[c] = 1.0;
-        for (const Placed& x : pl) apply_small(col, k, x.g->u.data(), x.g->k, x.p, x.cm);
-        for (int r = 0; r < dim; ++r) M[(size_t)r * dim + c] = col[r];
-    }
+    std::vector<cd> M((size_t)dim * dim);
+    for (size_t e = 0; e < M.size(); ++e) M[e] = cd(re[e], im[e]);
     return M;
 }
 
