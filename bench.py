@@ -9,7 +9,8 @@ transform, then 30 layers of random U3 on every qubit plus a CZ brick
                     passes (MFMA blocks, diagonal runs, remapping) ->
                     <Z_q> for all q, <Z_q Z_q+1>, an 8-qubit marginal,
                     1,024 samples, renormalisation (FP64 readouts)
-  plain complex128: init |x> -> one kernel per gate -> <Z_q> for all q
+  plain complex128: init |x> -> gate by gate, the gates that share a tile's
+                    qubits in one pass over the state -> <Z_q> for all q
 
 The reported value is the fused complex64 path's end-to-end gates/s
 (planning included, as the paper adds optimisation time to the total).
@@ -34,9 +35,10 @@ MFMA_PEAK = {"f32": 157.3e12, "f64": 78.6e12}
 
 
 def plain_bytes(gates, n, elem_bytes):
-    """Algorithmic bytes of the plain per-gate path: every amplitude a gate
-    changes is read and written once (dense: all; X/CNOT/SWAP moves: half;
-    phase gates: the matching quarter; 2^-c for c controls)."""
+    """Bytes of a gate list applied with a pass of its own for every gate:
+    every amplitude a gate changes is read and written once (dense: all;
+    X/CNOT/SWAP moves: half; phase gates: the matching quarter; 2^-c for c
+    controls)."""
     N = float(1 << n)
     tot = 0.0
     for g in gates:
@@ -66,7 +68,17 @@ KERNEL_SOURCES = {
     "phase": ["paper_2212_14201_amd/csrc/gates.hip"],
     "swappair": ["paper_2212_14201_amd/csrc/gates.hip"],
     "tile": ["paper_2212_14201_amd/csrc/tile.hip", "paper_2212_14201_amd/csrc/tile.hpp"],
+    "gates": ["paper_2212_14201_amd/csrc/gatepass.hip", "paper_2212_14201_amd/csrc/gatepass.hpp",
+              "paper_2212_14201_amd/csrc/tile.hpp"],
 }
+# kernel classes of qvm_run
+GATE_KERNELS = ("gates", "dense1", "dense2", "dense3", "diag", "phase", "swappair")
+
+
+def executed(stats, runs):
+    """Passes and bytes of one qvm_run, from the launches recorded over `runs`."""
+    use = [v for k, v in stats.items() if k in GATE_KERNELS]
+    return sum(v["launches"] for v in use) / runs, sum(v["bytes"] for v in use) / runs
 
 
 def stored_traffic(kernel, launches_bytes):
@@ -221,7 +233,7 @@ def layered_configs(torch, planner, records):
     plain path and the fused path, with errors against the oracle's stored
     values."""
     import numpy as np
-    from paper_2212_14201_amd import qvm
+    from paper_2212_14201_amd import profiling, qvm
     from workloads import SEEDS, config_circuit
     out = {}
     for name, reps in (("layered12", 50), ("layered28", 2)):
@@ -264,9 +276,12 @@ def layered_configs(torch, planner, records):
             rec = {"run_ms": secs * 1e3, "host_ms_per_call": wall * 1e3, "gates_per_s": G / secs,
                    "error_vs_oracle": err}
             if path.startswith("plain"):
-                gb = plain_bytes(gates, n, 8 if dtype == "c64" else 16)
+                profiling.begin(sv)
+                sv.run(ga)
+                extra["passes"], gb = executed(profiling.end(sv), 1)
                 rec["effective_GBs"] = gb / secs / 1e9
                 rec["frac_of_hbm_peak"] = rec["effective_GBs"] / HBM_PEAK_GBS
+                rec["per_gate_equivalent_GB"] = plain_bytes(gates, n, 8 if dtype == "c64" else 16) / 1e9
             else:
                 rec["effective_GBs"] = extra["passes"] * 2.0 * (1 << n) * (8 if dtype == "c64" else 16) / secs / 1e9
             rec.update(extra)
@@ -310,10 +325,9 @@ def copy_bandwidth(torch, nbytes, reps=3):
 def adjoint_measure(torch, reps=2):
     """Batched adjoint gradients: 20 qubits, complex64, 16 layers of RY, RZ
     and a CNOT ladder (640 parameters, 944 gates), a 40-term Pauli sum, a
-    batch of 64 parameter vectors.  Algorithmic bytes per batch element:
-    start state (1 write), forward gates (read + write of what each
-    changes), the Pauli sum (read psi, write lambda), the value (read both)
-    and the reverse sweep (read + write of psi and lambda per gate)."""
+    batch of 64 parameter vectors.  per_gate_equivalent: the bytes with a pass
+    of its own for every gate (read + write of what it changes, of psi and
+    lambda in reverse)."""
     import numpy as np
     from paper_2212_14201_amd import adjoint
     from workloads import SEEDS, hardware_efficient_ansatz, random_pauli_sum
@@ -332,15 +346,15 @@ def adjoint_measure(torch, reps=2):
     per_gate = 5.0 * S
     for g in gates:
         per_gate += 6.0 * S * 0.5 ** len(g.controls)
-    # executed passes: the start state (write), each gate group forward
-    # (read + write psi) and in reverse (read + write psi and lambda), the
-    # Pauli sum (read psi, write lambda) and the value (read both)
-    groups = prob.group_count()
-    executed = S + groups * 2.0 * S + 2.0 * S + 2.0 * S + groups * 4.0 * S
+    # executed: each pass forward (read + write psi; the first writes only)
+    # and in reverse (read + write psi and lambda), the Pauli sum (read psi,
+    # write lambda) and the value (read both)
+    passes = prob.pass_count()
+    moved = (2.0 * passes - 1.0) * S + 2.0 * S + 2.0 * S + passes * 4.0 * S
     return {"workload": "20 qubits, complex64, 944 gates (640 RY/RZ + 304 CNOT), 40 Pauli terms, "
                         "batch 64", "ms_per_batch": dt * 1e3, "gradients_per_s": B * P / dt,
-            "gate_groups": groups,
-            "effective_GBs": executed * B / dt / 1e9, "frac_of_hbm_peak": executed * B / dt / 1e9 / HBM_PEAK_GBS,
+            "gate_groups": prob.group_count(), "passes": passes,
+            "effective_GBs": moved * B / dt / 1e9, "frac_of_hbm_peak": moved * B / dt / 1e9 / HBM_PEAK_GBS,
             "per_gate_equivalent_GB_per_batch": per_gate * B / 1e9}
 
 
@@ -520,8 +534,9 @@ def main():
            "fused_c64": fused_info}
     if plain is not None:
         prun = float(np.mean([r["plain_run_s"] for r in recs]))
-        pbytes = plain_bytes(gates, n, 16)
-        out["plain_c128"] = {"run_ms": prun * 1e3, "gates_per_s": G / prun,
+        ppasses, pbytes = executed({k[5:]: v for k, v in kstats.items() if k.startswith("c128:")}, args.steps)
+        out["plain_c128"] = {"run_ms": prun * 1e3, "gates_per_s": G / prun, "passes": ppasses,
+                             "per_gate_equivalent_GB_per_run": plain_bytes(gates, n, 16) / 1e9,
                              "effective_GBs": pbytes / prun / 1e9,
                              "frac_of_hbm_peak": pbytes / prun / 1e9 / HBM_PEAK_GBS}
         out["speedup_fused_c64_vs_plain_c128"] = prun / fused_run
@@ -591,7 +606,7 @@ def main():
                 "error_vs_oracle": out["fused_c64"]["error_vs_oracle"]}]
     if "plain_c128" in out:
         records.append({"config": "qft30", "seed": SEEDS["qft30"], "path": "plain_c128", "dtype": "c128",
-                        "n": n, "gates": G, "passes": G, "ms": out["plain_c128"]["run_ms"],
+                        "n": n, "gates": G, "passes": out["plain_c128"]["passes"], "ms": out["plain_c128"]["run_ms"],
                         "GBs": out["plain_c128"]["effective_GBs"],
                         "hbm_frac": out["plain_c128"]["frac_of_hbm_peak"],
                         "error_vs_oracle": out["plain_c128"]["error_vs_oracle"]})
