@@ -73,19 +73,6 @@ __device__ __forceinline__ uint32_t sw(uint32_t e) { return tile_swizzle(e); }
 // the constant).
 __device__ __forceinline__ uint32_t sw_add(uint32_t swa, uint32_t b) { return (swa ^ (sw(b) ^ b)) + b; }
 
-// A 16-byte piece of two complex64 elements (2m, 2m + 1) as it sits in LDS:
-// at the slot pair of sw(2m), swapped when that slot is odd (the swizzle
-// keeps the pair adjacent but may reverse it).  Its own inverse.
-template <int EP, typename V>
-__device__ __forceinline__ V pair_order(V v, uint32_t s) {
-    if constexpr (EP == 2) {
-        const bool odd = (s & 1u) != 0;
-        return odd ? V{v[2], v[3], v[0], v[1]} : v;
-    } else {
-        return v;
-    }
-}
-
 // w with a zero inserted at every set bit of `fixed` (the tile bits), one
 // run of consecutive set bits at a time: the tile's base index from its
 // workgroup index.
@@ -211,6 +198,33 @@ __device__ __forceinline__ T lds_ld(uint32_t off) {
 template <typename T>
 __device__ __forceinline__ void lds_st(uint32_t off, T v) {
     *(__attribute__((address_space(3))) T*)(size_t)off = v;
+}
+
+// A 16-byte piece of the tile to and from LDS slot s.  complex64: elements 2m
+// and 2m + 1 sit in adjacent slots in either order (the swizzle), each moved
+// by itself (as 16 bytes, exchanged where the slot is odd, it took four
+// selects a piece: vector instructions hold up the matrix ones here, and a
+// 30-qubit run takes 171.6 ms with them, 171.1 without).
+template <typename R>
+__device__ __forceinline__ void piece_st(uint32_t s, typename TT<R>::V16 v) {
+    using V2 = typename TT<R>::V2;
+    if constexpr (TT<R>::EP == 2) {
+        lds_st<V2>(8 * s, V2{v[0], v[1]});
+        lds_st<V2>(8 * (s ^ 1u), V2{v[2], v[3]});
+    } else {
+        lds_st<typename TT<R>::V16>(16 * s, v);
+    }
+}
+template <typename R>
+__device__ __forceinline__ typename TT<R>::V16 piece_ld(uint32_t s) {
+    using V2 = typename TT<R>::V2;
+    using V16 = typename TT<R>::V16;
+    if constexpr (TT<R>::EP == 2) {
+        const V2 a = lds_ld<V2>(8 * s), b = lds_ld<V2>(8 * (s ^ 1u));
+        return V16{a[0], a[1], b[0], b[1]};
+    } else {
+        return lds_ld<V16>(16 * s);
+    }
 }
 
 // exp(2 pi i a / 2^32) from the LDS cis table (at byte address tab): the
@@ -865,7 +879,7 @@ __device__ __forceinline__ void tile_pass(R* __restrict__ psi, const PassDesc& p
 #pragma unroll
             for (int it = 0; it < BATCH; ++it) {
                 const uint32_t s = sw_add(se0, (uint32_t)EP * NT * (uint32_t)(b0 + it));
-                *(V16*)(lds + 2 * (s & ~(uint32_t)(EP - 1))) = pair_order<EP>(v[it], s);
+                piece_st<R>(s, v[it]);
             }
         }
     }
@@ -963,7 +977,7 @@ __device__ __forceinline__ void tile_pass(R* __restrict__ psi, const PassDesc& p
 #pragma unroll
                 for (int it = 0; it < BATCH; ++it) {
                     const uint32_t s = sw_add(ss0, (uint32_t)EP * NT * (uint32_t)(b0 + it));
-                    v[it] = pair_order<EP>(*(const V16*)(lds + 2 * (s & ~(uint32_t)(EP - 1))), s);
+                    v[it] = piece_ld<R>(s);
                 }
             } else {
 #pragma unroll
