@@ -152,7 +152,7 @@ class GateArray:
                 self._keep.append(u)
             try:
                 pack(arr, i * _GATE.size, kind, len(g.targets), *g.targets, *_NONE[len(g.targets)],
-                     _ctrl_mask(ctl) if ctl else 0, *ps, *_NIL[len(ps)], u.ctypes.data if u is not None else 0)
+                     _ctrl_mask(ctl) if len(ctl) else 0, *ps, *_NIL[len(ps)], u.ctypes.data if u is not None else 0)
             except (struct.error, IndexError, TypeError, ValueError):
                 self._record(arr[i], kind, g.targets, ctl, list(ps), u)
 

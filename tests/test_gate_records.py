@@ -33,7 +33,8 @@ def fields(arr, n):
 @pytest.mark.parametrize("gates", [
     random_mixed_circuit(9, 120, 3, kmax=3, max_ctrl=2), layered_u3_cz(6, 3, 4), [],
     [Gate("x", [np.int64(3)], (np.int32(1), 2)), Gate("rz", (0,), (), [np.float32(0.5)]), Gate("u3", (1.0,), (), (1, 2, 3)),
-     Gate("p", (True,), (), (0.25, 7.0, 8.0, 9.0)), Gate("z", (2**31 + 5,), (70,)), Gate("h", (-1,))]],
+     Gate("p", (True,), (), (0.25, 7.0, 8.0, 9.0)), Gate("z", (2**31 + 5,), (70,)), Gate("h", (-1,)),
+     Gate("x", np.array([1]), np.array([0])), Gate("rx", np.array([2]), np.array([1, 3]), np.array([0.0]))]],
     ids=["mixed", "layered", "empty", "odd"])
 def test_records(gates):
     ga = qvm.GateArray(gates)
