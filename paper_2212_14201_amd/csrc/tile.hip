@@ -592,6 +592,11 @@ __device__ __forceinline__ void tile_diagrun(R* __restrict__ lds, const DSub* __
             const DSub& d = subs[q];
             if ((base & d.omask) != d.oval) continue;
             const bool hlo = (t & d.lmask & LOWM) == (d.lval & LOWM);
+            // no lane of the wave matches (a term on index bits 6 to 8, which
+            // tell the waves apart): its factor is 1.  26 qubits, 30 layers of
+            // random gates, complex128: 10.94 -> 10.84 ms; 12 qubits of
+            // layered gates, complex64: 147.5 -> 145.2 us
+            if (!__builtin_amdgcn_ballot_w64(hlo)) continue;
             const uint32_t rows = d.rows >> i0;     // bit i: element i of this sweep matches
             if (d.neg) {
                 // factor -1 where the low bits match: a sign flip
