@@ -599,14 +599,17 @@ __device__ __forceinline__ void tile_diagrun(R* __restrict__ lds, const DSub* __
             if (!__builtin_amdgcn_ballot_w64(hlo)) continue;
             const uint32_t rows = d.rows >> i0;     // bit i: element i of this sweep matches
             if (d.neg) {
-                // factor -1 where the low bits match: a sign flip
-                const R sg = hlo ? (R)-1 : (R)1;
+                // factor -1 where the low bits match: a sign flip, by xor with a
+                // mask per element (a multiplication per element needs selects
+                // on top).  The circuits above: 10.80 -> 10.73 ms and
+                // 147.1 -> 145.9 us
+                using TU = typename Turn<R>::T;
+                const TU sg = hlo ? (TU)1 << (8 * sizeof(TU) - 1) : (TU)0;
 #pragma unroll
                 for (int i = 0; i < NPT; ++i) {
-                    if ((rows >> i) & 1) {
-                        xr[i] *= sg;
-                        xi[i] *= sg;
-                    }
+                    const TU f = sg & ((TU)0 - (TU)((rows >> i) & 1));
+                    xr[i] = flip_if(xr[i], f);
+                    xi[i] = flip_if(xi[i], f);
                 }
                 continue;
             }
