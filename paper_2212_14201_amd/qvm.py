@@ -140,7 +140,9 @@ class GateArray:
         # the other way
         arr, pack = self.arr, _GATE.pack_into
         for i, g in enumerate(gates):
-            kind, ps, ctl = KIND[g.name], g.params, g.controls
+            # (a tuple of the parameters first: they may be an iterator, and the
+            # record may be written twice)
+            kind, ps, ctl = KIND[g.name], tuple(g.params), g.controls
             if params is not None:
                 pidx = getattr(g, "pidx", -1)
                 if pidx is not None and pidx >= 0:
@@ -154,7 +156,7 @@ class GateArray:
                 pack(arr, i * _GATE.size, kind, len(g.targets), *g.targets, *_NONE[len(g.targets)],
                      _ctrl_mask(ctl) if len(ctl) else 0, *ps, *_NIL[len(ps)], u.ctypes.data if u is not None else 0)
             except (struct.error, IndexError, TypeError, ValueError):
-                self._record(arr[i], kind, g.targets, ctl, list(ps), u)
+                self._record(arr[i], kind, g.targets, ctl, ps, u)
 
     @staticmethod
     def _record(rec, kind, targets, controls, ps, u):

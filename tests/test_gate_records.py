@@ -58,3 +58,21 @@ def test_refused():
             qvm.GateArray([bad])
     with pytest.raises(IndexError):
         qvm.GateArray([Gate("rz", (0,), (), (0.0,), 5)], np.zeros(2))
+
+
+@pytest.mark.parametrize("again", [
+    lambda v: map(float, v), lambda v: (x for x in v), lambda v: reversed(v[::-1]), iter,
+    lambda v: dict.fromkeys(v).keys()], ids=["map", "generator", "reversed", "iterator", "keys"])
+def test_iterators(again):
+    """Parameters and controls that can be read once only; a fourth parameter
+    (not held by a record) sends the record the other way."""
+    ps, cs = [0.1, 0.2, 0.3], [3, 1, 2]
+    make = lambda f: [Gate("u3", (0,), (), f(ps)), Gate("rx", (0,), f(cs), f(ps[1:2])),  # noqa: E731
+                      Gate("u3", (4.0,), f(cs), f(ps)), Gate("p", (0,), (), f(ps + [7.0]))]
+    arr, _ = by_field(make(list))
+    assert fields(qvm.GateArray(make(again)).arr, 4) == fields(arr, 4)
+
+
+def test_indexed_parameter_of_a_gate_without_parameters():
+    with pytest.raises(TypeError):               # (a gate's own parameters have to be a sequence all the same)
+        qvm.GateArray([Gate("ry", (2,), (), None, 0)], [0.7])
