@@ -187,11 +187,14 @@ qvm_status qvm_run_trajectory(qvm_sv* sv, const qvm_gate* gates, size_t n_gates,
                               int32_t* branches);
 
 /* Apply a gate list in order with the plain per-gate path, in one call (the
- * per-gate call overhead the paper measures at small n is paid once).  Each
- * gate is applied with its own matrix (consecutive uncontrolled one-target
- * gates on a qubit as their product, formed in double precision); gates
- * share passes over the state, so two gates that commute because they share
- * no qubit, or are both diagonal on the qubits they share, may trade places.
+ * per-gate call overhead the paper measures at small n is paid once).
+ * Consecutive uncontrolled one-target gates on a qubit are applied as their
+ * product (formed in extended precision), one-target phases where the next
+ * gate needs them.  Every other gate is applied with its own matrix; in
+ * complex64 a unitary one-target gate as the rotation and the phases that
+ * make it up.  Gates share passes over the state, so two gates that commute
+ * because they share no qubit, or are both diagonal on the qubits they share,
+ * may trade places.
  * The list is validated in full before anything is enqueued.  Asynchronous;
  * uses the workspace's plan area. */
 qvm_status qvm_run(qvm_sv* sv, const qvm_gate* gates, size_t n_gates);

@@ -20,20 +20,20 @@
 //          16 amplitudes (32 or 64 VGPRs) keep four waves per SIMD in
 //          complex64 and two in complex128 (of 64 KiB tiles).
 //   record what a round applies at once: one gate, the signs that are due, or
-//          a LAYER, the factors and rotations that are due (pass_gates).
+//          a LAYER, the factors and the one-target gates that are due
+//          (pass_gates): in complex64 as rotations and phases, in complex128
+//          as the matrices they are.
 //
 // What bounds it: 28 qubits, complex128, 8 layers of U3 + CZ (332 gates):
 // 361 ms with one kernel per gate; 31.6 ms in 6 passes with a dense 2 x 2
-// product per U3, of which the passes' traffic takes 8 ms; 27.7 ms with
-// rotations and phases (a third of the multiply-adds) in a record each, and
-// no faster when these worked in place (a quarter fewer vector instructions):
-// then branches bound it, a dozen per record; 21.5 ms with LAYER and SIGNS
-// records.  Now the first pass (72 U3) issues vector instructions in 64% of
-// its cycles, and the last two are bound by HBM.
+// product and a record per gate, 27.5 with LAYER and SIGNS records (a dozen
+// branches to choose a record's op).  The FP64 multiply-adds alone take 12
+// ms, the passes' traffic 8.  (As rotations and phases, a third of the
+// multiply-adds, 21.6 ms, but further from the gates: pass_gates.)
 // 25 qubits, complex64, 4 layers of rotations + CNOTs (400 gates): 35.3 ms
 // with one kernel per gate, 1.92 with dense products, now 1.75 (11 passes,
 // whose traffic takes 0.92).  12 qubits, complex128, 20 layers (350 gates, one
-// workgroup): 1.38 ms, 0.187, now 0.126.
+// workgroup): 1.38 ms, 0.187, now 0.156.
 //
 // The list's records are written to the workspace by k_put kernels, which
 // carry them as kernel arguments: no copy from host memory that the caller
@@ -79,6 +79,12 @@ struct OpHead {
 };
 static_assert(sizeof(OpHead) == 32, "eight words");
 constexpr uint32_t kTable = 16;
+// Values of a LAYER record before its factors: complex64 two per slot (a
+// rotation), complex128 a 2 x 2 matrix for every slot in the mask.
+template <typename R>
+__host__ __device__ constexpr int layer_vals(uint32_t mask) {
+    return sizeof(R) == 4 ? 2 * kSlots : 8 * __builtin_popcount(mask);
+}
 struct SignCond {
     uint32_t jbits, tm, tv, om, ov, pad[3];
 };
@@ -190,6 +196,22 @@ __device__ __forceinline__ void op_turn(T (&a)[NA], R ta, R tb) {
     }
 }
 
+// A LAYER's matrix m on slot S, if S is in the mask jb, and the values of the
+// next one (after the last: in bounds, not used), loaded while it is applied.
+template <typename R, int S, typename T, int NA>
+__device__ __forceinline__ void op_next(T (&a)[NA], R (&m)[8], const R* __restrict__& mv, uint32_t jb) {
+    if (!(jb & (1u << S))) return;
+    R next[8];
+    mv += 8;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) next[i] = mv[i];
+#pragma unroll
+    for (int j = 0; j < NA; ++j)
+        if (!(j & (1 << S))) pair2<R>(m, a[j], a[j | (1 << S)]);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) m[i] = next[i];
+}
+
 // A record's head and its first 8 values, in scalar registers: the next
 // record is loaded while the current one is applied (a wave otherwise waits
 // for two dependent scalar loads per gate, 1,500 cycles of a 2,000-cycle
@@ -220,15 +242,25 @@ __device__ __forceinline__ void apply_op(T (&a)[NA], const OpHead& h, const Rec<
     if (!below(code, GP_SIGNS)) {
         if (is(code, GP_LAYER)) {
             if (jb & kTable) {
-                const R* __restrict__ f = mv + 2 * kSlots;
+                const R* __restrict__ f = mv + layer_vals<R>(jb & (kTable - 1));
 #pragma unroll
                 for (int j = 0; j < NA; ++j) phase1<R>(f[2 * j], f[2 * j + 1], a[j]);
             }
-            if (jb & 1) op_turn<R, 0>(a, rec.val(0), rec.val(1));
-            if (jb & 2) op_turn<R, 1>(a, rec.val(2), rec.val(3));
-            if (jb & 4) op_turn<R, 2>(a, rec.val(4), rec.val(5));
-            if constexpr (NA == 16)
-                if (jb & 8) op_turn<R, 3>(a, rec.val(6), rec.val(7));
+            if constexpr (sizeof(R) == 4) {
+                if (jb & 1) op_turn<R, 0>(a, rec.val(0), rec.val(1));
+                if (jb & 2) op_turn<R, 1>(a, rec.val(2), rec.val(3));
+                if (jb & 4) op_turn<R, 2>(a, rec.val(4), rec.val(5));
+                if constexpr (NA == 16)
+                    if (jb & 8) op_turn<R, 3>(a, rec.val(6), rec.val(7));
+            } else {
+                R m[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) m[i] = rec.val(i);
+                op_next<R, 0>(a, m, mv, jb);
+                op_next<R, 1>(a, m, mv, jb);
+                op_next<R, 2>(a, m, mv, jb);
+                if constexpr (NA == 16) op_next<R, 3>(a, m, mv, jb);
+            }
         }
         if (is(code, GP_SIGNS)) {
             // each register's sign: the parity of the conditions the thread meets
@@ -517,6 +549,18 @@ struct GGate {
     double frac;            // share of the amplitudes its own kernel would touch
 };
 
+// A gate as its pass applies it (pass_gates).
+struct PGate {
+    const LOp* op;
+    uint64_t xq, zq;
+    double frac;
+    bool lone;              // one-target, uncontrolled: a LAYER's, after pre
+    double a, b;            // complex64: its rotation
+    int npre;
+    int bit[4];
+    cd pre[4];
+};
+
 template <typename R>
 struct Emit {
     std::vector<uint32_t>& tab;
@@ -582,23 +626,32 @@ struct Emit {
         }
         return true;
     }
-    // factors f (or none) and rotations (a, b) of the slots in mask
-    void layer(const cd* f, uint32_t mask, const double (*ab)[2]) {
-        double v[2 * kSlots + (2 << kSlots)] = {};
-        for (int k = 0; k < kSlots; ++k)
-            if ((mask >> k) & 1) {
-                v[2 * k] = ab[k][0];
-                v[2 * k + 1] = ab[k][1];
+    // factors f (or none) and the gates (rotations or matrices) of the slots in mask
+    void layer(const cd* f, uint32_t mask, const PGate* const* at) {
+        double v[8 * kSlots + (2 << kSlots)] = {};
+        int nv = 0;
+        for (int k = 0; k < kSlots; ++k) {
+            if (!((mask >> k) & 1)) continue;
+            if constexpr (sizeof(R) == 4) {
+                v[2 * k] = at[k]->a;
+                v[2 * k + 1] = at[k]->b;
+            } else {
+                for (int e = 0; e < 4; ++e) {
+                    v[nv++] = at[k]->op->m[e].real();
+                    v[nv++] = at[k]->op->m[e].imag();
+                }
             }
+        }
+        nv = layer_vals<R>(mask);
         if (f)
             for (uint32_t j = 0; j < 1u << rs; ++j) {
-                v[2 * kSlots + 2 * j] = f[j].real();
-                v[2 * kSlots + 2 * j + 1] = f[j].imag();
+                v[nv++] = f[j].real();
+                v[nv++] = f[j].imag();
             }
         OpHead h{};
         h.code = GP_LAYER;
         h.jbits = mask | (f ? kTable : 0);
-        record(h, v, 2 * kSlots + (f ? 2 << rs : 0));
+        record(h, v, nv);
     }
     void signs(const std::vector<SignCond>& c) {
         OpHead h{};
@@ -697,43 +750,44 @@ struct Emit {
     }
 };
 
-// A pass's gates as its records take them.  A unitary one-target gate is
-// g diag(1, p) R diag(1, q), R a real rotation: R alone is a sequence of
-// shears (op_turn), and the phases join those of other gates.  A phase
-// waits on its bit (through gates that act diagonally on it, and through an
-// uncontrolled X as its conjugate) until a gate that acts otherwise on the
-// bit needs it applied (pre) or the pass ends; in a round the phases that
-// are due on the slots become one factor per register.  U3 layers with CZs between them so
-// take, per four gates, four rotations and one set of factors: 32 multiply-adds
-// per amplitude pair against the 64 (and 12 moves) of four dense gates.  Rounding:
-// against U3 gates exact in 80 bits (10 qubits, 12 layers, complex128) the
-// state is off by 0.9 to 0.95e-15, with dense products by 0.9 to 0.97e-15.
-struct PGate {
-    const LOp* op;
-    uint64_t xq, zq;
-    double frac;
-    bool turn;              // the rotation (a, b), after pre
-    double a, b;
-    int npre;
-    int bit[4];
-    cd pre[4];
-};
-
+// A pass's gates as its records take them.  Phases (diagonal one-target gates)
+// wait on their bit, through gates that act diagonally on it and, as the
+// inverse, through an uncontrolled X, until a gate that acts otherwise on the
+// bit needs them applied (pre) or the pass ends; in a round the phases that
+// are due on the slots become one factor per register.
+//
+// complex64: a unitary one-target gate is g diag(1, p) R diag(1, q), R a real
+// rotation: R alone is a sequence of shears (op_turn), and the phases join
+// those that wait.  U3 layers with CZs between them so take, per four gates,
+// four rotations and one set of factors: 32 multiply-adds per amplitude pair
+// against the 64 (and 12 moves) of four dense gates, which round more: lists
+// of 200 gates of every kind end 0.83 times as far from their matrices in 80
+// bits as with one dense kernel per gate.
+//
+// complex128: a one-target gate is its matrix.  A rotation and phases are not:
+// their own rounding, and what a matrix of rounded entries lacks of a unitary
+// one, is as large as the arithmetic's (explicit matrices ended 1.4 times as
+// far off, U3 gates 2.5 times).  With the matrices, phases in long double and
+// runs multiplied in long double it is 0.87 to 0.97 times (20 layers of U3 +
+// CZ, 11 qubits: 1.02e-15 of the norm, gate by gate 1.07e-15).
 bool unit(const cd& x) { return std::fabs(std::norm(x) - 1.0) < 4e-15; }
 cd mulc(const cd& a, const cd& b) {
     return cd(a.real() * b.real() - a.imag() * b.imag(), a.real() * b.imag() + a.imag() * b.real());
 }
 
-// A phase that is carried along, in long double: rounded at every gate, the
-// factor of all amplitudes alone would be off by more than the gates' own
-// rounding (332 gates: 4e-15 of the state's norm against 2e-15).
+// A complex number that is carried along, in long double: rounded at every
+// gate, the factor of all amplitudes alone would be off by as much as the
+// gates' own arithmetic.
 struct Phase {
     long double re = 1.0L, im = 0.0L;
     Phase() = default;
     Phase(long double r, long double i) : re(r), im(i) {}
     explicit Phase(const cd& x) : re(x.real()), im(x.imag()) {}
     bool one() const { return re == 1.0L && im == 0.0L; }
-    Phase conj() const { return Phase(re, -im); }
+    Phase inv() const {
+        const long double q = re * re + im * im;
+        return Phase(re / q, -im / q);
+    }
     void by(const Phase& o) {
         const long double r = re * o.re - im * o.im;
         im = re * o.im + im * o.re;
@@ -762,9 +816,9 @@ bool euler(const std::vector<cd>& u, Euler& e) {
     e.s = (double)(sqrtl(s2) / h);
     e.g = w[0];
     e.p = w[2];
-    e.p.by(w[0].conj());
+    e.p.by(w[0].inv());
     e.q = Phase(-w[1].re, -w[1].im);
-    e.q.by(w[0].conj());
+    e.q.by(w[0].inv());
     Phase d = e.g;
     d.by(e.p);
     d.by(e.q);
@@ -775,7 +829,8 @@ bool euler(const std::vector<cd>& u, Euler& e) {
 }
 
 // (own: ops that are not the list's)
-std::vector<PGate> pass_gates(const std::vector<GGate>& G, const std::vector<int>& ops, std::deque<LOp>& own) {
+// split: one-target gates as rotations and phases (complex64).
+std::vector<PGate> pass_gates(const std::vector<GGate>& G, const std::vector<int>& ops, std::deque<LOp>& own, bool split) {
     const cd one(1.0, 0.0), zero(0.0, 0.0);
     std::vector<PGate> out;
     out.reserve(ops.size() + 2);
@@ -786,14 +841,14 @@ std::vector<PGate> pass_gates(const std::vector<GGate>& G, const std::vector<int
             Phase f(o.phase);
             if (!o.cond_val) {
                 all.by(f);
-                f = f.conj();
+                f = f.inv();
             }
             ph[__builtin_ctzll(o.cond_mask)].by(f);
             continue;
         }
         if (o.cls == OP_DIAG && o.k == 1 && o.cmask == 0 && unit(o.m[0]) && unit(o.m[1])) {
             Phase f(o.m[1]);
-            f.by(Phase(o.m[0]).conj());
+            f.by(Phase(o.m[0]).inv());
             ph[o.t[0]].by(f);
             all.by(Phase(o.m[0]));
             continue;
@@ -805,12 +860,14 @@ std::vector<PGate> pass_gates(const std::vector<GGate>& G, const std::vector<int
         if (lone && o.m[0] == zero && o.m[3] == zero && unit(o.m[1]) && unit(o.m[2])) {
             // diag(m1, m2) X: all m1, then m2 / m1 on the bit
             after = Phase(o.m[2]);
-            after.by(Phase(o.m[1]).conj());
+            after.by(Phase(o.m[1]).inv());
             all.by(Phase(o.m[1]));
             own.push_back(classify(1, o.t, 0, {zero, one, one, zero}));
             g.op = &own.back();
+        } else if (lone && !split) {
+            g.lone = true;
         } else if (lone && euler(o.m, e)) {
-            g.turn = true;
+            g.lone = true;
             g.a = -e.s / (1.0 + e.c);
             g.b = e.s;
             all.by(e.g);
@@ -822,7 +879,7 @@ std::vector<PGate> pass_gates(const std::vector<GGate>& G, const std::vector<int
             if (ph[b].one()) continue;
             if (g.op->cls == OP_SWAPPAIR && g.xq == 1ull << b && !g.zq) {
                 all.by(ph[b]);
-                ph[b] = ph[b].conj();
+                ph[b] = ph[b].inv();
                 continue;
             }
             g.bit[g.npre] = b;
@@ -919,10 +976,10 @@ uint32_t round_records(Emit<R>& E, const std::vector<PGate>& P, const std::vecto
         wait.clear();
         wait_bits = 0;
     };
-    // the factors and signs due, with the rotations of the slots in mask
-    auto apply = [&](uint32_t mask, const double (*ab)[2]) {
-        const bool lone = items == 1 && !mask;   // one gate's factors: on its own registers only
-        const bool tab = items && !lone;
+    // the factors and signs due, with the one-target gates at of the slots in mask
+    auto apply = [&](uint32_t mask, const PGate* const* at) {
+        const bool one = items == 1 && !mask;    // one gate's factors: on its own registers only
+        const bool tab = items && !one;
         uint32_t nb = 0;
         for (int j = 0; j < NA; ++j) {
             if (tab) f[j] = mulc(f[j], fs[j]);
@@ -933,14 +990,14 @@ uint32_t round_records(Emit<R>& E, const std::vector<PGate>& P, const std::vecto
             E.signs(std::vector<SignCond>(signs.begin() + k, signs.begin() + std::min(signs.size(), k + kMaxSigns)));
             ++nops;
         }
-        if (lone) {
+        if (one) {
             nops += (uint32_t)E.gate(*single);
             flops += 3.0 * amps;
         }
         if (tab || mask) {
-            E.layer(tab ? f : nullptr, mask, ab);
+            E.layer(tab ? f : nullptr, mask, at);
             ++nops;
-            flops += (tab ? 6.0 : 0.0) * amps + 6.0 * amps * __builtin_popcount(mask);
+            flops += (tab ? 6.0 : 0.0) * amps + (sizeof(R) == 4 ? 6.0 : 16.0) * amps * __builtin_popcount(mask);
         }
         clear();
     };
@@ -954,33 +1011,29 @@ uint32_t round_records(Emit<R>& E, const std::vector<PGate>& P, const std::vecto
         }
         if (wait_bits & g.xq) release();
         pres(i);
-        uint64_t bx = g.turn ? 0 : g.xq, bz = (g.turn ? 0 : g.zq) | wait_bits;   // bits of gates passed over
+        uint64_t bx = g.lone ? 0 : g.xq, bz = (g.lone ? 0 : g.zq) | wait_bits;   // bits of gates passed over
         uint32_t mask = 0;
-        double ab[kSlots][2] = {};
-        auto rotate = [&](const PGate& q) {
+        const PGate* at[kSlots] = {};
+        uint64_t taken = 0;                      // slots in mask
+        auto take = [&](const PGate& q) {
             const int k = __builtin_ctz(E.slot_bits(q.xq));
             mask |= 1u << k;
-            ab[k][0] = q.a;
-            ab[k][1] = q.b;
+            at[k] = &q;
+            taken |= q.xq;
         };
-        uint64_t turned = 0;
-        if (g.turn) {
-            rotate(g);
-            turned = g.xq;
-        }
+        if (g.lone) take(g);
         for (size_t k = i + 1; k < now.size(); ++k) {
             if (used[k]) continue;
             const PGate& q = P[now[k]];
-            if (g.turn && q.turn && !(q.xq & (bx | bz | turned))) {
+            if (g.lone && q.lone && !(q.xq & (bx | bz | taken))) {
                 pres(k);
-                rotate(q);
-                turned |= q.xq;
+                take(q);
                 used[k] = 1;
                 continue;
             }
             // (factors due later that can be applied already)
-            if (items && q.npre && !(q.xq & (bx | turned))) pres(k);
-            if (items && !q.xq && !(q.zq & (bx | turned)) && E.slot_factors(*q.op, nullptr)) {
+            if (items && q.npre && !(q.xq & (bx | taken))) pres(k);
+            if (items && !q.xq && !(q.zq & (bx | taken)) && E.slot_factors(*q.op, nullptr)) {
                 factor(*q.op);
                 used[k] = 1;
                 continue;
@@ -988,8 +1041,8 @@ uint32_t round_records(Emit<R>& E, const std::vector<PGate>& P, const std::vecto
             bx |= q.xq;
             bz |= q.zq;
         }
-        apply(mask, ab);
-        if (!g.turn) {
+        apply(mask, at);
+        if (!g.lone) {
             nops += (uint32_t)E.gate(*g.op);
             const double touched = g.frac * amps;
             flops += g.op->cls == OP_DENSE ? touched * 8.0 * (1 << g.op->k) : g.op->cls == OP_SWAPPAIR ? 0.0 : 6.0 * touched;
@@ -1029,7 +1082,7 @@ qvm_status launch_pass(qvm_sv* sv, PassBuf& buf, const std::vector<GGate>& G, co
     }
     std::vector<uint32_t> tab;
     std::deque<LOp> own;
-    const std::vector<PGate> P = pass_gates(G, ops, own);
+    const std::vector<PGate> P = pass_gates(G, ops, own, sizeof(R) == 4);
     if (P.empty() && !measure) return QVM_OK;                   // (the gates undo each other)
     std::vector<int> left(P.size()), next, now;
     for (size_t i = 0; i < P.size(); ++i) left[i] = (int)i;
@@ -1138,13 +1191,13 @@ qvm_status launch_pass(qvm_sv* sv, PassBuf& buf, const std::vector<GGate>& G, co
 // with 16:
 //   12 qubits, 200 mixed gates, complex64        161 / 140 / 128 | 153
 //   14 qubits, 200 mixed gates, complex64        186 / 163 / 170 | 199
-//   14 qubits, 200 mixed gates, complex128       189 / 184 / 195 | 219
-//   16 qubits, 188 gates in layers, complex128    91 /  89 /  93 |  94
+//   14 qubits, 200 mixed gates, complex128       182 / 178 / 198 | 219
+//   16 qubits, 188 gates in layers, complex128    88 /  86 / 100 |  95
 //   17 qubits, 200 mixed gates, complex64        200 / 187 / 185 | 227
 //   18 qubits, 212 gates in layers, complex64    107 / 100 /  92 | 106
-//   20 qubits, 236 gates in layers, complex128   164 / 152 / 128 | 129
+//   20 qubits, 236 gates in layers, complex128   172 / 162 / 138 | 136
 //   22 qubits, 352 rotations, CNOTs, complex64   390 / 355 / 340 | 298
-//   28 qubits, 332 gates in layers, complex128             29.9 ms | 27.5 ms
+//   28 qubits, 332 gates in layers, complex128             28.1 ms | 26.6 ms
 int pass_slots(int n) { return n <= 20 ? 3 : 4; }
 template <typename R> int pass_width(int n) {
     return std::min(n, n > 20 ? GT<R>::LMAX : n > 12 && n <= 16 ? 11 : 12);
@@ -1195,27 +1248,29 @@ qvm_status run_segment(qvm_sv* sv, const std::vector<GGate>& G, uint64_t measure
 }
 
 // A gate list under construction: runs of uncontrolled one-target gates on a
-// bit become one gate (their product, in double precision).
+// bit become one gate (their product in long double, rounded once).
 class ListBuilder {
   public:
     ListBuilder() { std::fill(open_, open_ + QVM_MAX_QUBITS, -1); }
     void one(int bit, const cd* m) {
+        Phase x[4];
+        for (int e = 0; e < 4; ++e) x[e] = Phase(m[e]);
         if (open_[bit] < 0) {
             open_[bit] = (int)items_.size();
             Item it{};
             it.bit = bit;
-            std::copy(m, m + 4, it.m);
+            std::copy(x, x + 4, it.m);
             items_.push_back(std::move(it));
             return;
         }
-        cd* r = items_[open_[bit]].m;
-        cd p[4];
+        Phase* r = items_[open_[bit]].m;
+        Phase p[4];
         for (int a = 0; a < 2; ++a)
             for (int b = 0; b < 2; ++b) {
-                const cd x = m[2 * a], y = r[b], z = m[2 * a + 1], v = r[2 + b];
-                p[2 * a + b] =
-                    cd(x.real() * y.real() - x.imag() * y.imag() + z.real() * v.real() - z.imag() * v.imag(),
-                       x.real() * y.imag() + x.imag() * y.real() + z.real() * v.imag() + z.imag() * v.real());
+                Phase y = x[2 * a], z = x[2 * a + 1];
+                y.by(r[b]);
+                z.by(r[2 + b]);
+                p[2 * a + b] = Phase(y.re + z.re, y.im + z.im);
             }
         std::copy(p, p + 4, r);
     }
@@ -1233,7 +1288,8 @@ class ListBuilder {
         std::vector<cd> u;
         for (Item& it : items_) {
             if (it.bit >= 0) {
-                u.assign(it.m, it.m + 4);
+                u.resize(4);
+                for (int e = 0; e < 4; ++e) u[e] = it.m[e].value();
                 it.op = classify(1, &it.bit, 0, u);
             }
             if (it.op.cls == OP_PHASE && it.op.phase == cd(1.0, 0.0)) continue;      // identity
@@ -1245,7 +1301,7 @@ class ListBuilder {
   private:
     struct Item {
         int bit;                                 // >= 0: a run of one-target gates with product m
-        cd m[4];
+        Phase m[4];
         LOp op;
     };
     static GGate placed(LOp op) {
