@@ -476,8 +476,9 @@ __global__ __launch_bounds__(256) void k_marg_final(const double* __restrict__ p
 // The chunk sums (2^clog consecutive logical indices each) are the marginal
 // over the logical qubits from clog up.
 
-// Exclusive prefixes of the chunk sums inside groups of 1,024 chunks, and
-// the groups' totals (at most 256).
+// Exclusive prefixes of the chunk sums inside groups of 1,024 chunks (infinity
+// for a chunk of no probability: it is never drawn), and the groups' totals (at
+// most 256).
 constexpr uint32_t kGroup = 1024;
 __global__ __launch_bounds__(256) void k_scan_chunks(const double* __restrict__ csum, uint64_t nchunks,
                                                      double* __restrict__ prefix, double* __restrict__ gtot) {
@@ -497,16 +498,21 @@ __global__ __launch_bounds__(256) void k_scan_chunks(const double* __restrict__ 
     double run = threadIdx.x ? sh[threadIdx.x - 1] : 0.0;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        if (c0 + k < nchunks) prefix[c0 + k] = run;
+        if (c0 + k < nchunks) prefix[c0 + k] = v[k] > 0.0 ? run : __builtin_inf();
         run += v[k];
     }
     if (threadIdx.x == 255) gtot[blockIdx.x] = sh[255];
 }
 
-// One block per sample: the group and the chunk from the prefixes, then the
-// chunk is scanned in order.  With E = 16 elements per thread (chunks of
-// 4,096, up to 30 qubits) the probabilities stay in registers between the
-// sum and the search.
+// One block per sample: the last group and in it the last chunk whose offset is
+// at most the target, then the chunk is scanned in order.  Offsets are sums
+// associated in a tree and may decrease in the last place from one entry to
+// the next, or grow by it over entries without probability, so the highest
+// index that passes is taken (a bisection or a count would take them for
+// sorted), and only groups, chunks and amplitudes of some probability are
+// drawn: the first of them has offset 0 in its group, so one always passes.
+// With E = 16 elements per thread (chunks of 4,096, up to 30 qubits) the
+// probabilities stay in registers between the sum and the search.
 template <typename R, int E16>
 __global__ __launch_bounds__(256) void k_find(const typename C2r<R>::T* __restrict__ psi,
                                               int n, int clog, Perm P,
@@ -515,8 +521,8 @@ __global__ __launch_bounds__(256) void k_find(const typename C2r<R>::T* __restri
                                               const double* __restrict__ uni,
                                               uint64_t* __restrict__ out) {
     __shared__ double sh[256];
-    __shared__ unsigned long long best;
-    __shared__ unsigned cnt;
+    __shared__ unsigned long long best, last;     // first amplitude past the target; last of the chunk with any probability
+    __shared__ unsigned grp, chunk;               // 1 + the highest that passes
     const uint64_t N = 1ull << n;
     const uint64_t C = 1ull << clog;
     const uint32_t t = threadIdx.x;
@@ -529,30 +535,31 @@ __global__ __launch_bounds__(256) void k_find(const typename C2r<R>::T* __restri
             __syncthreads();
         }
     };
-    sh[t] = t < ngroups ? gtot[t] : 0.0;
+    const double mine = t < ngroups ? gtot[t] : 0.0;
+    sh[t] = mine;
     if (t == 0) {
         best = ~0ull;
-        cnt = 0;
+        last = 0;
+        grp = chunk = 0;
     }
     scan();
     const double target = uni[blockIdx.x] * sh[255];
-    // the last group whose offset is at most the target (offsets do not decrease)
-    if (t < ngroups && (t == 0 || sh[t - 1] <= target)) atomicAdd(&cnt, 1u);
+    if (mine > 0.0 && (t == 0 || sh[t - 1] <= target)) atomicMax(&grp, t + 1);
     __syncthreads();
-    const uint32_t g = cnt - 1;
+    if (grp == 0) {                                              // no probability at all, or not a number
+        if (t == 0) out[blockIdx.x] = target == 0.0 ? N - 1 : min(C, N - 1);
+        return;
+    }
+    const uint32_t g = grp - 1;
     const double goff = g ? sh[g - 1] : 0.0;
-    __syncthreads();
-    if (t == 0) cnt = 0;
-    __syncthreads();
-    // the last chunk of the group, likewise
-    unsigned mine = 0;
+    unsigned top = 0;
     for (uint32_t k = t; k < kGroup; k += 256) {
         const uint64_t c = (uint64_t)g * kGroup + k;
-        if (c < nchunks && (k == 0 || goff + prefix[c] <= target)) ++mine;
+        if (c < nchunks && goff + prefix[c] <= target) top = k + 1;
     }
-    if (mine) atomicAdd(&cnt, mine);
+    if (top) atomicMax(&chunk, top);
     __syncthreads();
-    const uint64_t c = (uint64_t)g * kGroup + (cnt - 1);
+    const uint64_t c = (uint64_t)g * kGroup + (chunk ? chunk - 1 : 0);
     const double coff = goff + prefix[c];
     const uint64_t E = C >= 256 ? C / 256 : 1;
     const uint64_t e0 = min((uint64_t)t * E, C);
@@ -576,29 +583,30 @@ __global__ __launch_bounds__(256) void k_find(const typename C2r<R>::T* __restri
     sh[t] = loc;
     scan();
     double run = coff + (t ? sh[t - 1] : 0.0);
-    uint64_t cand = ~0ull;
+    uint64_t cand = ~0ull, nz = 0;
     if constexpr (E16) {
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
             run += pr[k];
-            if (cand == ~0ull && run > target) cand = base + e0 + k;
+            if (cand == ~0ull && pr[k] > 0.0 && run > target) cand = base + e0 + k;
+            if (pr[k] > 0.0) nz = base + e0 + k;
         }
     } else {
         for (uint64_t e = e0; e < e1; ++e) {
-            run += prob(psi[pb0 | to_phys(e - e0, P)]);
-            if (run > target) {
+            const double x = prob(psi[pb0 | to_phys(e - e0, P)]);
+            run += x;
+            if (x > 0.0) nz = base + e;
+            if (x > 0.0 && run > target) {
                 cand = base + e;
                 break;
             }
         }
     }
     if (cand != ~0ull) atomicMin(&best, (unsigned long long)cand);
+    if (nz) atomicMax(&last, (unsigned long long)nz);
     __syncthreads();
-    if (t == 0) {
-        uint64_t r = best;
-        if (r == ~0ull) r = min(base + C, N - 1);
-        out[blockIdx.x] = r;
-    }
+    // (rounding may leave the target at or past the end of the chunk)
+    if (t == 0) out[blockIdx.x] = best != ~0ull ? best : last;
 }
 
 // ------------------------------------------------------------ amplitudes
