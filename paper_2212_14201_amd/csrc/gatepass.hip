@@ -1374,8 +1374,8 @@ qvm_status put_words(qvm_sv* sv, uint32_t* dst, const uint32_t* src, size_t n) {
     return QVM_OK;
 }
 
-// The gate list in segments: bounds the host's work lists and the scans of
-// the scheduler.
+// The gate list in segments (a noisy run's groups likewise): bounds the host's
+// work lists, the scans of the scheduler and a pass's records.
 constexpr size_t kSegment = 4096;
 
 qvm_status run_gates(qvm_sv* sv, const qvm_gate* gates, size_t n_gates) {
@@ -1542,8 +1542,8 @@ qvm_status run_trajectory(qvm_sv* sv, const qvm_gate* gates, size_t n_gates, con
         body.clear();
         later.clear();
         uint64_t grp = 0, held = 0;
-        size_t i = pos;
-        for (; i < n_gates; ++i) {
+        size_t i = pos, items = 0;               // (a branching adds at most one per qubit)
+        for (; i < n_gates && items < kSegment; ++i) {
             const uint64_t b = bits_of(i);
             const bool noisy = first[i + 1] > first[i];
             if (!grp && !noisy) {
@@ -1557,11 +1557,13 @@ qvm_status run_trajectory(qvm_sv* sv, const qvm_gate* gates, size_t n_gates, con
             if (!noisy && !(b & grp) && gates[i].kind != QVM_G_MATRIX) {
                 later.push_back(i);
                 held |= b;
+                ++items;
                 continue;
             }
             if ((b & held) || pc(grp | b) > kSlots || sv->n < kSlots) break;
             grp |= b;
             body.push_back(i);
+            items += 1 + std::min<size_t>(kSlots, first[i + 1] - first[i]);
         }
         pos = i;
         if (body.empty()) {

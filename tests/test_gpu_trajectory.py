@@ -111,6 +111,58 @@ def test_trajectory_on_a_permuted_layout(dtype):
     assert np.max(np.abs(sv.amplitudes() - want)) <= tol
 
 
+@pytest.mark.parametrize("n,dtype", [(4, "c128"), (4, "c64"), (6, "c128")])
+def test_groups_longer_than_a_segment(n, dtype):
+    """Thousands of noisy gates that never leave four qubits."""
+    rng = np.random.default_rng(n)
+    gates = []
+    for _ in range(5000):
+        a, b = (int(q) for q in rng.choice(4, 2, replace=False))
+        gates.append([Gate("ry", (a,), (), (float(rng.uniform(0, 6)),)), Gate("x", (a,), (b,)), Gate("h", (n - 1,))]
+                     [int(rng.choice(3, p=[0.3, 0.2, 0.5]))])
+    model = noise.NoiseModel([("ry", "depolarizing", {"p": 0.05}), ("cnot", "damping", {"p": 0.1})])
+    psi, us, want = oracle.basis_state(n, 0), [], []
+    for g in gates:
+        oracle.apply_matrix(psi, n, oracle.gate_matrix(g), g.targets, g.controls)
+        for ops in model.channels_for(g):
+            for q in tuple(g.targets) + tuple(g.controls):
+                w = onoise.branch_weights(psi, n, q, ops)
+                j = int(rng.choice(len(w), p=w / w.sum()))
+                us.append((np.sum(w[:j]) + 0.5 * w[j]) / w.sum())
+                psi, jj, _ = onoise.trajectory_step(psi, n, q, ops, us[-1])
+                want.append(jj)
+    sv = qvm.StateVector(n, dtype)
+    br = noise.run_trajectory(sv, gates, model, np.array(us))
+    assert br == want
+    tol = C128_TOL if dtype == "c128" else 2 * c64_bound([1] * (len(gates) + len(us)))
+    assert np.max(np.abs(sv.amplitudes() - psi)) <= tol
+
+
+def test_group_beyond_the_plan_area():
+    """Between two branchings, more dense gates on four qubits than the
+    workspace holds records for at once (36,000 of 1,056 bytes; 32 MiB)."""
+    n = 5
+    rng = np.random.default_rng(1)
+    ms = [np.linalg.qr(rng.normal(size=(8, 8)) + 1j * rng.normal(size=(8, 8)))[0] for _ in range(40)]
+    gates = [Gate("h", (0,))]
+    gates += [Gate("unitary", tuple(int(q) for q in rng.permutation(4)[:3]), (), (), -1, ms[int(rng.integers(40))])
+              for _ in range(36000)]
+    gates.append(Gate("h", (3,)))
+    k = noise.kraus_ops("depolarizing", p=0.9)
+    psi, us, want = oracle.basis_state(n, 0), [], []
+    for i, g in enumerate(gates):
+        oracle.apply_matrix(psi, n, oracle.gate_matrix(g), g.targets, g.controls)
+        if i in (0, len(gates) - 1):
+            w = onoise.branch_weights(psi, n, g.targets[0], k)
+            us.append((w[0] + 0.5 * w[1]) / w.sum())
+            psi, j, _ = onoise.trajectory_step(psi, n, g.targets[0], k, us[-1])
+            want.append(j)
+    first = [0] + [1] * (len(gates) - 1) + [2]
+    sv = qvm.StateVector(n, "c128")
+    assert sv.run_trajectory(gates, first, [0, 3], [0, 0], [k], us) == want == [1, 1]
+    assert np.max(np.abs(sv.amplitudes() - psi)) <= C128_TOL
+
+
 def test_argument_errors():
     sv = qvm.StateVector(5, "c128")
     g = [Gate("h", (0,))]
