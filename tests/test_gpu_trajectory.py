@@ -111,6 +111,33 @@ def test_trajectory_on_a_permuted_layout(dtype):
     assert np.max(np.abs(sv.amplitudes() - want)) <= tol
 
 
+@pytest.mark.parametrize("n,dtype", [(22, "c128"), (23, "c64")])
+def test_measuring_workgroups_take_several_tiles(n, dtype):
+    """1,024 tiles on 512 workgroups, a superposed state with coherences:
+    several groups, the first one's rounds straight from memory."""
+    rng = np.random.default_rng(n)
+    gates = [Gate("ry", (q,), (), (float(rng.uniform(0, 6)),)) for q in range(n)]
+    gates += [Gate("z", (q + 1,), (q,)) for q in range(0, n - 1, 2)] + [Gate("rx", (q,), (), (0.7 + q,)) for q in range(1, n, 3)]
+    gates += [Gate("x", (0,), (n - 1,)), Gate("x", (n - 5,), (n - 1,)), Gate("h", (5,)), Gate("x", (n - 2,), (7,)),
+              Gate("h", (n - 3,)), Gate("h", (1,))]
+    model = noise.NoiseModel([("cnot", "depolarizing", {"p": 0.5}), ("h", "damping", {"p": 0.4})])
+    psi, us, want = oracle.basis_state(n, 0), [], []
+    for g in gates:
+        oracle.apply_matrix(psi, n, oracle.gate_matrix(g), g.targets, g.controls)
+        for ops in model.channels_for(g):
+            for q in tuple(g.targets) + tuple(g.controls):
+                w = onoise.branch_weights(psi, n, q, ops)
+                j = len(us) % len(w)                         # (every branch is taken)
+                us.append((np.sum(w[:j]) + 0.5 * w[j]) / w.sum())
+                psi, jj, _ = onoise.trajectory_step(psi, n, q, ops, us[-1])
+                want.append(jj)
+    sv = qvm.StateVector(n, dtype)
+    br = noise.run_trajectory(sv, gates, model, np.array(us))
+    assert br == want
+    tol = C128_TOL if dtype == "c128" else 2 * c64_bound(gate_ks(gates) + [1] * len(br))
+    assert np.max(np.abs(sv.amplitudes() - psi)) <= tol
+
+
 @pytest.mark.parametrize("n,dtype", [(4, "c128"), (4, "c64"), (6, "c128")])
 def test_groups_longer_than_a_segment(n, dtype):
     """Thousands of noisy gates that never leave four qubits."""
