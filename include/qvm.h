@@ -176,7 +176,8 @@ qvm_status qvm_apply_kraus(qvm_sv* sv, int32_t qubit, int32_t n_ops, const doubl
  * operators one channel after the other, each as in qvm_apply_kraus.  The
  * weights of up to four qubits' branchings come from one measurement of
  * their joint density matrix (FP64), on which the gates and chosen operators
- * between are then played on the host.  Everything is validated before
+ * between are then played on the host; a branching that shares no measurement
+ * with another takes its qubit's.  Everything is validated before
  * anything is enqueued; errors as in qvm_run and qvm_apply_kraus (a branching
  * whose weights are all zero ends the run there, the gates and branchings
  * since the last measurement not applied).  Synchronizes the stream.  Uses

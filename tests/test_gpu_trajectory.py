@@ -111,6 +111,40 @@ def test_trajectory_on_a_permuted_layout(dtype):
     assert np.max(np.abs(sv.amplitudes() - want)) <= tol
 
 
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("n", [4, 9, 14, 21])
+def test_lone_branchings(n, dtype):
+    """One branching at a time: gates before it, on its qubits after it, on
+    others meanwhile, and a group of two after it; from a permuted layout."""
+    rng = np.random.default_rng(n)
+    first = layered_u3_cz(n, 2, 7)
+    a, b, c, d = (int(q) for q in rng.permutation(n)[:4])
+    gates = [Gate("h", (a,)), Gate("rx", (a,), (), (0.4,)), Gate("x", (b,), (a,)), Gate("u3", (d,), (), (1.0, 2.0, 3.0)),
+             Gate("z", (c,), (b,)), Gate("ry", (c,), (), (0.9,)), Gate("x", (d,), (c,)), Gate("h", (b,)), Gate("t", (b,)),
+             Gate("swap", (a, d)), Gate("h", (c,)), Gate("x", (a,), (b,)), Gate("h", (d,))]
+    at = {1: [a], 6: [c], 9: [a], 11: [b, a], 12: [d]}           # branchings after a gate
+    ks = [noise.kraus_ops("damping", p=0.4), noise.kraus_ops("depolarizing", p=0.6)]
+    psi = oracle.simulate(n, first)
+    heads, qubit, chan, us, want = [0], [], [], [], []
+    for i, g in enumerate(gates):
+        oracle.apply_matrix(psi, n, oracle.gate_matrix(g), g.targets, g.controls)
+        for q in at.get(i, []):
+            k = len(us) % 2
+            w = onoise.branch_weights(psi, n, q, ks[k])
+            j = len(us) % len(w)
+            us.append((np.sum(w[:j]) + 0.5 * w[j]) / w.sum())
+            psi, jj, _ = onoise.trajectory_step(psi, n, q, ks[k], us[-1])
+            qubit.append(q)
+            chan.append(k)
+            want.append(jj)
+        heads.append(len(us))
+    sv = qvm.StateVector(n, dtype)
+    qvm.Plan(first, n, dtype, k_max=3, tile_qubits=min(n, 7)).run(sv)
+    assert sv.run_trajectory(gates, heads, qubit, chan, ks, us) == want
+    tol = C128_TOL if dtype == "c128" else 2 * c64_bound(gate_ks(first + gates) + [1] * len(us))
+    assert np.max(np.abs(sv.amplitudes() - psi)) <= tol
+
+
 @pytest.mark.parametrize("n,dtype", [(22, "c128"), (23, "c64")])
 def test_measuring_workgroups_take_several_tiles(n, dtype):
     """1,024 tiles on 512 workgroups, a superposed state with coherences:
