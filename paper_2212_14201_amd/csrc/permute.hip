@@ -156,10 +156,11 @@ qvm_status permute_pass(qvm_sv* sv, uint64_t Q, const int* from) {
 
 }  // namespace
 
-// Swaps where they are cheaper: at 26 qubits, complex128, a swap of two bits
-// above the lowest three takes 0.17 ms, with one of those 0.4 (up to 0.58), a
-// pass 0.40 (units of 0.17 ms below).  Below 2^8 amplitudes a tile would not fill
-// the threads' pieces.
+// Swaps where they are cheaper, in units of a swap of two bits above the lowest
+// c (26 qubits: complex64 96 us, complex128 170 to 190): with the highest of
+// those c the swap moves half lines (155; 345), with a lower one shorter pieces
+// (285 to 420; 550 to 580); a pass takes 190; 375 to 400.  Below 2^8 amplitudes
+// a tile would not fill the threads' pieces.
 qvm_status reset_layout(qvm_sv* sv) {
     const int n = sv->n, c = sv->dt == QVM_C64 ? GT<float>::C : GT<double>::C;
     const int L = std::min(n, sv->dt == QVM_C64 ? GT<float>::LMAX : GT<double>::LMAX);
@@ -175,14 +176,14 @@ qvm_status reset_layout(qvm_sv* sv) {
     for (int q = 0; q < n; ++q)
         if (sim[q] != q) {
             const int p = (int)(std::find(sim, sim + n, q) - sim);
-            swaps += std::min(p, q) < c ? 2.4 : 1.0;
+            swaps += std::min(p, q) >= c ? 1.0 : std::min(p, q) == c - 1 ? 1.9 : 3.0;
             std::swap(sim[p], sim[q]);
         }
     if (n >= 8) {
         std::copy(cur, cur + n, sim);
         while (!home(sim)) {
             arrange(sim, n, next_tile(sim, n, L, c), from);
-            passes += 2.3;
+            passes += 2.2;
         }
     }
     if (n < 8 || swaps <= passes) {

@@ -10,6 +10,7 @@ from workloads import Gate
 pytestmark = pytest.mark.gpu
 
 qvm = pytest.importorskip("paper_2212_14201_amd.qvm")
+profiling = pytest.importorskip("paper_2212_14201_amd.profiling")
 
 
 @pytest.fixture(autouse=True)
@@ -44,3 +45,17 @@ def test_reset_layout(n, dtype):
         assert np.array_equal(sv.amplitudes(), want)
         assert np.array_equal(sv.amps.cpu().numpy().reshape(-1).view(state.dtype), want)
         print(f"n={n} {dtype} moved={moved}", flush=True)
+
+
+@pytest.mark.parametrize("dtype,bit", [("c64", 3), ("c128", 2)])
+def test_one_swap_with_the_highest_bit_of_a_line(dtype, bit):
+    """A layout one such swap away moves half of the state, not all of it."""
+    n = 20
+    sv = qvm.StateVector(n, dtype)
+    sv.init_basis(5)
+    qvm.Plan([Gate("swap", (bit, n - 1))], n, dtype, k_max=3, tile_qubits=12).run(sv)
+    profiling.begin(sv)
+    sv.reset_layout()
+    stats = profiling.end(sv)
+    assert stats["swappair"]["launches"] == 1
+    assert stats["swappair"]["bytes"] == (1 << n) * (8 if dtype == "c64" else 16)
