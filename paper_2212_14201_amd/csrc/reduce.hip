@@ -87,14 +87,20 @@ __global__ __launch_bounds__(256) void k_norm_partial(const typename C2r<R>::T* 
     using V = typename Piece<R>::V;
     constexpr int EP = Piece<R>::EP;
     __shared__ double sh[4];
-    const uint64_t np = N / EP, stride = (uint64_t)gridDim.x * 256;
+    const uint64_t np = N / EP, rows = (np + 255) / 256, per = (rows + gridDim.x - 1) / gridDim.x;
+    const uint64_t r0 = min(blockIdx.x * per, rows), r1 = min(r0 + per, rows);
     double s = 0;
-    for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < np; i += 4 * stride) {
-        V v[4];
+    // (a block's pieces one row after the other: 28 qubits, complex64, 330 us;
+    // strided over the grid 390)
+    for (uint64_t r = r0; r < r1; r += 8) {
+        V v[8];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] = i + k * stride < np ? ld_piece<V>(psi + EP * (i + k * stride)) : V{};
+        for (int k = 0; k < 8; ++k) {
+            const uint64_t i = (r + k) * 256 + threadIdx.x;
+            v[k] = r + k < r1 && i < np ? ld_piece<V>(psi + EP * i) : V{};
+        }
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
+        for (int k = 0; k < 8; ++k)
 #pragma unroll
             for (int e = 0; e < EP; ++e) s += sq(amp(v[k], e));
     }

@@ -83,3 +83,16 @@ def test_many_strings_take_several_launches():
     want = np.array([oracle.expect_pauli(psi, int(xs[i]), int(zs[i]))[0] for i in pick])
     assert np.max(np.abs(got[pick] - want)) <= 1e-13
     assert abs(tot - float(np.sum(got))) <= 1e-12
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("n", [1, 2, 8, 9, 17, 19, 20, 21, 24])
+def test_norm_at_every_row_count(n, dtype):
+    """Fewer rows than blocks, one, and some each."""
+    import torch
+    rng = np.random.default_rng(n)
+    v = rng.normal(size=2 << n).astype(np.float32 if dtype == "c64" else np.float64)
+    sv = qvm.StateVector(n, dtype)
+    sv.amps.copy_(torch.from_numpy(v).reshape(sv.amps.shape))
+    want = float(np.sum(v.astype(np.float64) ** 2))
+    assert abs(sv.norm() - want) <= 64 * 2.0 ** -53 * want
