@@ -402,15 +402,18 @@ struct MargArgs {
     uint32_t qlo;                     // marginal qubits inside the row
     uint32_t mh, segs, niter;         // marginal qubits above the row; 2^(seg bits); 2^(iter bits)
     uint8_t lo_out[12], hi_out[24];   // output bit of the k-th lowest bit of qlo / qhi
+    uint8_t hi_run;                   // hi_out ascends one by one
 };
 
+// x's bits on the set bits of mask, ascending, a run of them at a time.
 __device__ __forceinline__ uint64_t place_bits(uint64_t x, uint64_t mask) {
     uint64_t r = 0;
     while (mask) {
         const uint64_t low = mask & (~mask + 1);
-        if (x & 1) r |= low;
-        x >>= 1;
-        mask ^= low;
+        const uint64_t run = ((mask + low) & ~mask) - low;
+        r |= (x * low) & run;
+        x >>= __builtin_popcountll(run);
+        mask &= ~run;
     }
     return r;
 }
@@ -443,19 +446,25 @@ __global__ __launch_bounds__(256) void k_marg_partial(const typename C2r<R>::T* 
 #pragma unroll
                 for (int e = 0; e < EP; ++e) acc[e] += sq(amp(v[k], e));
         }
+    }
+    // fold the row's other bits: a piece's and a wave's in registers, the waves'
+    // when the buckets are read.  (The 16 highest of 24 qubits, complex128,
+    // 65,536 blocks of one row each: 260 us a level at a time in LDS, 220 so, 104
+    // with the block's bits placed a run at a time instead of one by one.)
+    if (EP == 2 && !(a.qlo & 1)) acc[0] += acc[EP - 1];
 #pragma unroll
-        for (int e = 0; e < EP; ++e) sum[EP * t + e] = acc[e];
+    for (int k = 0; k < 6; ++k) {
+        if ((a.qlo >> (EP - 1 + k)) & 1) continue;
+#pragma unroll
+        for (int e = 0; e < EP; ++e) acc[e] += __shfl_xor(acc[e], 1 << k, 64);
     }
+#pragma unroll
+    for (int e = 0; e < EP; ++e) sum[EP * t + e] = acc[e];
     __syncthreads();
-    // fold the row's other bits, highest first
-    for (uint32_t b = len >> 1; b; b >>= 1) {
-        if (a.qlo & b) continue;
-        for (uint32_t i = t; i < len; i += 256)
-            if (!(i & b)) sum[i] += sum[i | b];
-        __syncthreads();
-    }
-    uint32_t jh = 0;
-    for (uint32_t k = 0; k < a.mh; ++k) jh |= ((qi >> k) & 1u) << a.hi_out[k];
+    constexpr uint32_t W0 = EP << 6, W1 = EP << 7;
+    uint32_t jh = a.hi_run ? qi << a.hi_out[0] : 0;
+    if (!a.hi_run)
+        for (uint32_t k = 0; k < a.mh; ++k) jh |= ((qi >> k) & 1u) << a.hi_out[k];
     const uint32_t nlo = 1u << __popc(a.qlo);
     for (uint32_t i = t; i < nlo; i += 256) {
         uint32_t j = jh, e = 0, x = i, k = 0;
@@ -464,7 +473,14 @@ __global__ __launch_bounds__(256) void k_marg_partial(const typename C2r<R>::T* 
                 e |= m & (~m + 1);
                 j |= 1u << a.lo_out[k];
             }
-        part[(size_t)j * a.segs + seg] = sum[e];
+        double v = sum[e];
+        if (!(a.qlo & W0)) v += sum[e | W0];
+        if (!(a.qlo & W1)) {
+            double x = sum[e | W1];
+            if (!(a.qlo & W0)) x += sum[e | W1 | W0];
+            v += x;
+        }
+        part[(size_t)j * a.segs + seg] = v;
     }
 }
 
@@ -869,11 +885,15 @@ static qvm_status marginal_to(qvm_sv* sv, int m, const int* pq, double* dst, dou
         if ((rowm >> pq[r]) & 1) a.lo_out[__builtin_popcountll(a.qlo & below)] = (uint8_t)r;
         else a.hi_out[__builtin_popcountll(a.qhi & below)] = (uint8_t)r;
     }
-    // the other bits above the row: the highest split the sum over blocks
+    a.hi_run = 1;
+    for (uint32_t k = 1; k < a.mh; ++k) a.hi_run &= a.hi_out[k] == a.hi_out[0] + k;
+    // the other bits above the row: the highest split the sum over blocks, as
+    // long as a block keeps the four rows that it has in flight at once, and
+    // from 256 blocks on (one a CU) sixteen: their sums take another launch
     uint64_t rest = above & ~q;
     uint32_t sb = 0;
     const size_t nb = (size_t)1 << m;
-    while (rest && a.mh + sb < 11 && (nb << (sb + 1)) <= part_doubles) {
+    while (__builtin_popcountll(rest) > (a.mh + sb < 8 ? 2 : 4) && a.mh + sb < 11 && (nb << (sb + 1)) <= part_doubles) {
         const uint64_t top = 1ull << (63 - __builtin_clzll(rest));
         a.seg |= top;
         rest ^= top;

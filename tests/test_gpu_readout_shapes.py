@@ -86,6 +86,34 @@ def test_many_strings_take_several_launches():
 
 
 @pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("n", [1, 3, 8, 9, 10, 11, 13, 16, 18, 20, 24])
+def test_marginals_of_runs_of_qubits(n, dtype):
+    """Marginal qubits in one run and in several, at the bottom, across and
+    above a row, in ascending and in any other order: rows folded over every
+    set of their bits, sums in one launch and in two, few rows a block."""
+    import torch
+    rng = np.random.default_rng(n)
+    v = rng.normal(size=(1 << n, 2)) / np.sqrt(2.0 ** (n + 1))
+    v = v.astype(np.float32 if dtype == "c64" else np.float64)
+    sv = qvm.StateVector(n, dtype)
+    sv.amps.copy_(torch.from_numpy(v).reshape(sv.amps.shape))
+    p = np.sum(v.astype(np.longdouble) ** 2, axis=1)            # (numpy adds along an axis one by one: in 80 bits)
+    sets = {tuple(range(m)) for m in (1, 4, 7, 9, 12)} | {tuple(range(n - m, n)) for m in (1, 4, 8, 12, 16)}
+    sets |= {tuple(range(n - 1, max(n - 9, -1), -1)), tuple(range(0, n, 3)), tuple(range(5, min(n, 12))),
+             (n - 1,) + tuple(range(0, n - 1, 4)), tuple(range(6, min(n, 10))) + tuple(range(12, n))}
+    for qs in sets:
+        qs = tuple(q for q in qs if 0 <= q < n)
+        if not qs or len(set(qs)) < len(qs) or len(qs) > 18:
+            continue
+        axes = p.reshape((2,) * n).sum(axis=tuple(n - 1 - q for q in range(n) if q not in qs))
+        kept = sorted(qs, reverse=True)
+        want = axes.transpose([kept.index(q) for q in reversed(qs)]).reshape(-1)
+        got = sv.probabilities(list(qs))
+        # sums of at most 2^24 positive terms in a tree
+        assert np.max(np.abs(got - want) / want) <= 64 * 2.0 ** -53, (qs, np.max(np.abs(got - want) / want))
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
 @pytest.mark.parametrize("n", [1, 2, 8, 9, 17, 19, 20, 21, 24])
 def test_norm_at_every_row_count(n, dtype):
     """Fewer rows than blocks, one, and some each."""
