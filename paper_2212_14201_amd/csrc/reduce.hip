@@ -799,10 +799,13 @@ static qvm_status pauli_t(qvm_sv* sv, const std::vector<PauliTerm>& terms, doubl
     std::vector<size_t> order;                                   // term of each column
     auto flush = [&]() -> qvm_status {
         if (jobs.empty()) return QVM_OK;
-        // blocks per job: about 4,096 in all, within the rows of a job and the partials
+        // blocks per job: about 4,096 in all, with eight rows or more each unless
+        // that leaves fewer than 256 (one string, 22 qubits: complex64 49 us with
+        // two rows, 41 with eight; complex128 52 and 46), within the partials
         const uint64_t rows = sv->n - 1 > LB ? 1ull << (sv->n - 1 - LB) : 1;
         uint64_t nb = 4096 / jobs.size();
-        nb = std::min<uint64_t>({std::max<uint64_t>(nb, 1), rows, (uint64_t)kRedBlocks * kRedSlots / order.size()});
+        const uint64_t most = std::max<uint64_t>(rows / 8, std::min<uint64_t>(rows, 256));
+        nb = std::min<uint64_t>({std::max<uint64_t>(nb, 1), most, (uint64_t)kRedBlocks * kRedSlots / order.size()});
         PauliJob* dj = (PauliJob*)io(sv);
         double* res = (double*)(io(sv) + kPauliJobs * sizeof(PauliJob));
         qvm_status st = put_words(sv, (uint32_t*)dj, (const uint32_t*)jobs.data(), jobs.size() * sizeof(PauliJob) / 4);
