@@ -709,11 +709,25 @@ struct AdjStep {
     uint32_t need;                   // Paulis its gradients take (0: nothing trainable)
     int run;                         // row of the matrix table (AD_MAT, AD_RE, AD_DG)
     int row;                         // first row of its gradient sums, -1: none
+    bool fence = false;              // not unitary: no other step passes it
     bool matrix() const { return kind != AD_MOVE && kind != AD_SIGN; }
 };
 
+// Unitary to the rounding of the states' type.  The sums of two gates that
+// commute may be taken in either order because undoing a unitary leaves them
+// as they are; undoing any other matrix, by its adjoint, changes them.
+bool adj_unitary(const std::vector<cd>& u, qvm_dtype dt) {
+    const double tol = dt == QVM_C64 ? 1e-6 : 1e-13;
+    for (int a = 0; a < 2; ++a)
+        for (int b = 0; b < 2; ++b) {
+            const cd d = std::conj(u[a]) * u[b] + std::conj(u[2 + a]) * u[2 + b];
+            if (!(std::abs(d - (a == b ? 1.0 : 0.0)) < tol)) return false;
+        }
+    return true;
+}
+
 // merge: consecutive uncontrolled gates on a qubit as one step (complex128).
-std::vector<AdjStep> adj_steps(const std::vector<AdjGate>& G, bool merge) {
+std::vector<AdjStep> adj_steps(const std::vector<AdjGate>& G, bool merge, qvm_dtype dt) {
     std::vector<AdjStep> out;
     int open[QVM_MAX_QUBITS];
     std::fill(open, open + QVM_MAX_QUBITS, -1);
@@ -730,7 +744,9 @@ std::vector<AdjStep> adj_steps(const std::vector<AdjGate>& G, bool merge) {
             continue;
         }
         AdjStep s{{(int)i}, g.target, g.cmask, 1ull << g.target, g.cmask, AD_MAT, 0, -1, -1};
-        for (uint64_t m = g.cmask | s.xq; m; m &= m - 1) open[__builtin_ctzll(m)] = -1;
+        s.fence = g.pidx < 0 && !g.named && !adj_unitary(g.u, dt);
+        for (uint64_t m = s.fence ? ~0ull : g.cmask | s.xq; m; m &= m - 1)
+            if (__builtin_ctzll(m) < QVM_MAX_QUBITS) open[__builtin_ctzll(m)] = -1;
         if (joins) open[g.target] = (int)out.size();
         if (g.pidx >= 0) {
             s.kind = g.gen == 1 ? AD_RX : g.gen == 2 ? AD_RE : AD_DG;
@@ -819,6 +835,33 @@ std::vector<AdjGroup> adj_groups(const std::vector<AdjStep>& S, int n, int r) {
     return out;
 }
 
+void adj_shift(AdjGroup& g, int by) {
+    for (int& i : g.steps) i += by;
+}
+void adj_shift(AdjPassPlan& P, int by) {
+    for (int& i : P.steps) i += by;
+    for (auto& r : P.rounds)
+        for (int& i : r) i += by;
+}
+
+// make (groups or passes of a list of steps) of each part between fences and
+// of each fence, one after the other.
+template <typename F>
+auto adj_fenced(const std::vector<AdjStep>& S, F make) -> decltype(make(S)) {
+    auto fence = [](const AdjStep& s) { return s.fence; };
+    if (std::none_of(S.begin(), S.end(), fence)) return make(S);
+    decltype(make(S)) out;
+    for (auto a = S.begin(); a != S.end();) {
+        const auto b = a->fence ? a + 1 : std::find_if(a, S.end(), fence);
+        for (auto& x : make(std::vector<AdjStep>(a, b))) {
+            adj_shift(x, (int)(a - S.begin()));
+            out.push_back(std::move(x));
+        }
+        a = b;
+    }
+    return out;
+}
+
 // complex64: a group is a round, and consecutive groups share a pass while
 // their slots and the low bits fit in the tile.
 std::vector<AdjPassPlan> adj_passes_ordered(const std::vector<AdjGroup>& groups, int n, int L, int c) {
@@ -900,9 +943,11 @@ AdjPassPlan adj_rounds(const std::vector<AdjStep>& S, AdjPassPlan P, bool rev, i
 }
 
 std::vector<AdjPassPlan> adj_passes(const std::vector<AdjStep>& S, int n, qvm_dtype dt) {
-    if (dt == QVM_C64)
-        return adj_passes_ordered(adj_groups(S, n, std::min(n, adj_slots<float>())), n, std::min(n, adj_width<float>()), GT<float>::C);
-    return adj_passes_free(S, n, std::min(n, adj_width<double>()), GT<double>::C);
+    return adj_fenced(S, [&](const std::vector<AdjStep>& part) {
+        if (dt == QVM_C64)
+            return adj_passes_ordered(adj_groups(part, n, std::min(n, adj_slots<float>())), n, std::min(n, adj_width<float>()), GT<float>::C);
+        return adj_passes_free(part, n, std::min(n, adj_width<double>()), GT<double>::C);
+    });
 }
 
 // Records of one pass; row0: the first row of its sums.
@@ -963,7 +1008,7 @@ static qvm_status adjoint_t(int n, int batch, const std::vector<AdjGate>& G, int
     const uint64_t N = 1ull << n;
     qvm_sv dummy{};
     qvm_sv* sv = &dummy;      // for the error macros only
-    std::vector<AdjStep> S = adj_steps(G, sizeof(R) == 8);
+    std::vector<AdjStep> S = adj_steps(G, sizeof(R) == 8, sizeof(R) == 4 ? QVM_C64 : QVM_C128);
     const int rs = std::min(n, adj_slots<R>());
     const std::vector<AdjPassPlan> passes = adj_passes(S, n, sizeof(R) == 4 ? QVM_C64 : QVM_C128);
     // run and gradient rows in pass order; a pass's gradient rows are consecutive
@@ -1283,7 +1328,9 @@ qvm_status qvm_adjoint_group_count(int n, qvm_dtype dt, const qvm_gate* gates, s
     qvm_status st = adj_prepare(n, 1, gates, n_gates, param_index, n_params, 1, &z, &z, &c, G, terms);
     if (st) return st;
     const int r = std::min(n, dt == QVM_C64 ? adj_slots<float>() : adj_slots<double>());
-    *n_groups = (int32_t)adj_groups(adj_steps(G, false), n, r).size();
+    *n_groups = (int32_t)adj_fenced(adj_steps(G, false, dt), [&](const std::vector<AdjStep>& part) {
+                    return adj_groups(part, n, r);
+                }).size();
     return QVM_OK;
 }
 
@@ -1297,7 +1344,7 @@ qvm_status qvm_adjoint_pass_count(int n, qvm_dtype dt, const qvm_gate* gates, si
     const double c = 0;
     qvm_status st = adj_prepare(n, 1, gates, n_gates, param_index, n_params, 1, &z, &z, &c, G, terms);
     if (st) return st;
-    *n_passes = (int32_t)adj_passes(adj_steps(G, dt == QVM_C128), n, dt).size();
+    *n_passes = (int32_t)adj_passes(adj_steps(G, dt == QVM_C128, dt), n, dt).size();
     return QVM_OK;
 }
 

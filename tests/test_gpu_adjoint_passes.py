@@ -62,3 +62,30 @@ def test_any_gates(n, count, batch, dtype):
         err = max(abs(f[b] - fo), float(np.max(np.abs(g[b] - go))))
         print(f"n={n} {dtype} gates={len(gates)} b={b} err={err:.2e} tol={tol:.2e}", flush=True)
         assert err <= tol
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("n,count", [(2, 24), (5, 60), (9, 80), (12, 100), (14, 120)])
+def test_matrices_that_are_not_unitary(n, count, dtype):
+    """The sweep undoes a matrix by its adjoint.  For one that is not unitary
+    the sums of gates on other qubits must then be taken in program order."""
+    gates, P = any_gates(n, count, 700 + n)
+    rng = np.random.default_rng(n)
+    for at in sorted(rng.integers(0, len(gates), 3), reverse=True):
+        m = np.array([[1.0, 0.3j], [-0.2, 0.8]]) + 0.1 * rng.normal(size=(2, 2))
+        gates.insert(int(at), Gate("unitary", (int(rng.integers(n)),), (), (), -1, m / np.linalg.norm(m, 2)))
+    gates += [Gate(r, (q,), (), (0.0,), P + 2 * q + i) for q in range(n) for i, r in enumerate(("rx", "ry"))]
+    P += 2 * n
+    gates.insert(len(gates) - n, Gate("unitary", (n - 1,), (0,) if n > 2 else (), (), -1, np.array([[0.5, 0.2], [0.1, 0.9]]) + 0j))
+    xs, zs = rng.integers(0, 1 << n, (2, 5)).astype(np.uint64)
+    cs = rng.normal(size=5)
+    theta = rng.uniform(-3, 3, (2, P))
+    f, g = adj.AdjointProblem(n, gates, P, xs, zs, cs, 2, dtype).run(theta)
+    csum = float(np.sum(np.abs(cs)))
+    share = max(sum(x.pidx == p for x in gates) for p in range(P))
+    tol = (1e-12 * (1 + csum) if dtype == "c128" else 2 * c64_bound([1] * (3 * len(gates)) + [2] * 5) * csum) * share
+    for b in range(2):
+        fo, go = oracle.adjoint(n, gates, theta[b], xs, zs, cs)
+        err = max(abs(f[b] - fo), float(np.max(np.abs(g[b] - go))))
+        print(f"n={n} {dtype} gates={len(gates)} b={b} err={err:.2e} tol={tol:.2e}", flush=True)
+        assert err <= tol
