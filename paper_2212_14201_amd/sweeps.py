@@ -81,15 +81,20 @@ def sweep_gates(ns, dtypes=("c128", "c64"), count=32, seed=7):
         for n in ns:
             sv = qvm.StateVector(n, dtype, init=0)
             for kind in GATE_KINDS:
-                # one kernel per gate (a list given to run() shares passes)
-                gates = gate_list(kind, n, count, seed + n)
-                for g in gates:
-                    sv.apply(g)                             # warm-up
+                # one kernel per gate (a list given to run() shares passes):
+                # the records are built before, so the interval holds the
+                # library's calls alone
+                arrays = [qvm.GateArray([g]) for g in gate_list(kind, n, count, seed + n)]
+                records = [ga.ptr() for ga in arrays]
+                apply, h = qvm.lib().qvm_apply, sv.handle
+                for r in records:
+                    qvm.check(apply(h, r))        # warm-up
                 e0, e1 = _events()
                 e0.record()
-                for g in gates:
-                    sv.apply(g)
+                bad = [s for s in [apply(h, r) for r in records] if s]
                 e1.record()
+                if bad:
+                    qvm.check(bad[0])
                 torch.cuda.synchronize()
                 ms = e0.elapsed_time(e1) / count
                 gbs = 2.0 * (1 << n) * eb * touched_fraction(kind) / (ms / 1e3) / 1e9

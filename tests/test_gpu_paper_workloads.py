@@ -87,3 +87,27 @@ def test_sweep_gate_kinds(dtype):
         tol = C128_TOL if dtype == "c128" else c64_bound(gate_ks(gates))
         print(f"{kind} {dtype}: max-abs {err:.2e} tol {tol:.1e}", flush=True)
         assert err <= tol, kind
+
+
+def test_gate_sweep_times_the_library_alone(monkeypatch):
+    """No record is built between the sweep's events."""
+    from paper_2212_14201_amd import sweeps
+    timing = []
+
+    class Event:
+        def record(self):
+            timing.append(self)
+
+        def elapsed_time(self, other):
+            return 1.0
+
+    build = qvm.GateArray.__init__
+
+    def watched(self, *args, **kw):
+        assert len(timing) % 2 == 0, "a record built inside the timed interval"
+        build(self, *args, **kw)
+
+    monkeypatch.setattr(sweeps, "_events", lambda: (Event(), Event()))
+    monkeypatch.setattr(qvm.GateArray, "__init__", watched)
+    rows = list(sweeps.sweep_gates([5], dtypes=("c64",), count=4))
+    assert len(rows) == len(sweeps.GATE_KINDS) and len(timing) == 2 * len(rows)
