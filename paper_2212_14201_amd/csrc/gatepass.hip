@@ -925,8 +925,7 @@ uint32_t round_records(Emit<R>& E, const std::vector<PGate>& P, const std::vecto
     std::vector<SignCond> signs;
     int items = 0;                               // in f
     const LOp* single = nullptr;
-    std::vector<LOp> hold;
-    hold.reserve(4);
+    std::deque<LOp> hold;                        // the phases in f that no gate of P is
     auto clear = [&]() {
         std::fill(f, f + NA, one);
         std::fill(fs, fs + NA, one);
@@ -952,12 +951,8 @@ uint32_t round_records(Emit<R>& E, const std::vector<PGate>& P, const std::vecto
             o.cls = OP_PHASE;
             o.cond_mask = o.cond_val = 1ull << q.bit[b];
             o.phase = q.pre[b];
-            if (hold.size() < hold.capacity()) {
-                hold.push_back(o);
-                factor(hold.back());
-            } else {
-                factor(o);
-            }
+            hold.push_back(o);
+            factor(hold.back());
         }
     };
     auto release = [&]() {
