@@ -105,7 +105,10 @@ size_t qvm_workspace_bytes(int n_qubits, qvm_dtype dt);
 
 /* Bind a state of n qubits (1..QVM_MAX_QUBITS) to caller memory: amps_dev
  * holds 2^n amplitudes of dtype dt (256-byte aligned), work_dev at least
- * qvm_workspace_bytes(n, dt) bytes.  hip_stream may be NULL.  The amplitudes
+ * qvm_workspace_bytes(n, dt) bytes.  A workspace belongs to one state at a
+ * time: readouts, plans, noisy runs and gate lists (qvm_run) all use it, so
+ * two states that share one race unless their calls are ordered, by one
+ * stream or by waiting.  hip_stream may be NULL.  The amplitudes
  * are not initialised; call qvm_init_basis.  The logical-to-physical qubit
  * layout starts as the identity. */
 qvm_status qvm_sv_create(int n_qubits, qvm_dtype dt, void* amps_dev,
@@ -409,16 +412,17 @@ qvm_status qvm_simplify(const qvm_gate* in, size_t n_in, int n_qubits, qvm_gate*
 
 /* ------------------------------------------------------------- gradients */
 
-/* Number of gate groups of a circuit: gates applied to amplitudes a thread
- * holds in registers (up to 4 target qubits per group for complex64, 3 for
- * complex128).  Same gate, parameter index and error rules as
- * qvm_adjoint_expect_grad.  Host-only. */
+/* Number of gate groups of a circuit: gates applied one by one to amplitudes a
+ * thread holds in registers, up to 4 target qubits per group for complex64, 3
+ * for complex128.  The complex64 sweeps run these groups; the complex128
+ * sweeps merge runs of gates and choose their own rounds
+ * (qvm_adjoint_pass_count says what either costs).  Same gate, parameter index
+ * and error rules as qvm_adjoint_expect_grad.  Host-only. */
 qvm_status qvm_adjoint_group_count(int n_qubits, qvm_dtype dt, const qvm_gate* gates, size_t n_gates,
                                    const int32_t* param_index, int n_params, int32_t* n_groups);
 
-/* Number of passes over psi the forward sweep takes (consecutive groups share
- * a pass while their qubits fit a tile), for callers that account for its
- * traffic.  The reverse sweep passes over psi and lambda as often.  Rules as
+/* Number of passes over psi the forward sweep takes (gates share a pass while
+ * their qubits fit a tile), for callers that account for its traffic.  The reverse sweep passes over psi and lambda as often.  Rules as
  * above.  Host-only. */
 qvm_status qvm_adjoint_pass_count(int n_qubits, qvm_dtype dt, const qvm_gate* gates, size_t n_gates,
                                   const int32_t* param_index, int n_params, int32_t* n_passes);

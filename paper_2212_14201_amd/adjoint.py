@@ -61,7 +61,8 @@ class AdjointProblem:
                                     dtype=torch.uint8, device=self.device)
 
     def group_count(self):
-        """Gate groups of the sweep (gates applied in registers together)."""
+        """Gate groups (gates applied in registers together) of the complex64
+        sweep; the complex128 sweep has none of its own (pass_count)."""
         return self._count(_declare().qvm_adjoint_group_count)
 
     def pass_count(self):
