@@ -593,16 +593,15 @@ __device__ __forceinline__ void tile_diagrun(R* __restrict__ lds, const DSub* __
             if ((base & d.omask) != d.oval) continue;
             const bool hlo = (t & d.lmask & LOWM) == (d.lval & LOWM);
             // no lane of the wave matches (a term on index bits 6 to 8, which
-            // tell the waves apart): its factor is 1.  26 qubits, 30 layers of
-            // random gates, complex128: 10.94 -> 10.84 ms; 12 qubits of
-            // layered gates, complex64: 147.5 -> 145.2 us
+            // tell the waves apart): its factor is 1.  A plan's passes alone:
+            // 26 qubits, 300 random gates, complex128 10.09 -> 9.99 ms; 12
+            // qubits, 350 gates in layers, complex64 86.7 -> 86.0 us
             if (!__builtin_amdgcn_ballot_w64(hlo)) continue;
             const uint32_t rows = d.rows >> i0;     // bit i: element i of this sweep matches
             if (d.neg) {
                 // factor -1 where the low bits match: a sign flip, by xor with a
                 // mask per element (a multiplication per element needs selects
-                // on top).  The circuits above: 10.80 -> 10.73 ms and
-                // 147.1 -> 145.9 us
+                // on top).  The plans above: 9.99 -> 9.91 ms and 86.0 -> 84.3 us
                 using TU = typename Turn<R>::T;
                 const TU sg = hlo ? (TU)1 << (8 * sizeof(TU) - 1) : (TU)0;
 #pragma unroll
